@@ -36,8 +36,8 @@ inline size_t align256(size_t v) { return (v + 255u) & ~(size_t)255u; }
 // Byte offsets of every array inside the workspace.
 struct Layout {
   size_t status;
-  size_t soa[2][7];  // x y z px py pz id, for the two buffers: C x cap block
-                     // slots, then n spill slots
+  size_t rec[2], id[2];  // records and ids of the two buffers: C x cap block
+                         // slots, then n spill slots
   size_t count[2];   // per-cell particle counts of the two buffers
   size_t spill_desc[2];      // SpillDesc of each buffer
   size_t spill_cell[2], spill_ocell[2], spill_hdr[2];
@@ -74,8 +74,8 @@ Layout make_layout(int64_t n_cells, uint32_t cap, int64_t n) {
   // the two buffers are laid out alike (every array of buffer 1 at one
   // distance from its twin in buffer 0)
   for (int b = 0; b < 2; ++b) {
-    for (int a = 0; a < 6; ++a) L.soa[b][a] = take((slots + sn) * sizeof(double));
-    L.soa[b][6] = take((slots + sn) * sizeof(uint32_t));
+    L.rec[b] = take((slots + sn) * 6u * sizeof(double));
+    L.id[b] = take((slots + sn) * sizeof(uint32_t));
     L.count[b] = take(cc * sizeof(uint32_t));
     L.spill_desc[b] = take(sizeof(SpillDesc));
     L.spill_cell[b] = take(sn * sizeof(uint32_t));
@@ -481,14 +481,8 @@ int init_context(cuba_ctx *c, const Derived &d, const cuba_params *params, int64
   char *ws = (char *)workspace;
   c->status = (DevStatus *)(ws + L.status);
   for (int b = 0; b < 2; ++b) {
-    SoA &st = c->buf[b].st;
-    st.x = (double *)(ws + L.soa[b][0]);
-    st.y = (double *)(ws + L.soa[b][1]);
-    st.z = (double *)(ws + L.soa[b][2]);
-    st.px = (double *)(ws + L.soa[b][3]);
-    st.py = (double *)(ws + L.soa[b][4]);
-    st.pz = (double *)(ws + L.soa[b][5]);
-    st.id = (uint32_t *)(ws + L.soa[b][6]);
+    c->buf[b].st.rec = (double *)(ws + L.rec[b]);
+    c->buf[b].st.id = (uint32_t *)(ws + L.id[b]);
     c->buf[b].count = (uint32_t *)(ws + L.count[b]);
     c->buf[b].cap = d.cap;
     c->buf[b].sp = (SpillDesc *)(ws + L.spill_desc[b]);
@@ -509,11 +503,9 @@ int init_context(cuba_ctx *c, const Derived &d, const cuba_params *params, int64
   }
   // the kernels derive one buffer's arrays from the other's by a single
   // byte distance: every array of buffer 1 lies that far from its twin
-  const ptrdiff_t shift = (char *)c->buf[1].st.x - (char *)c->buf[0].st.x;
-  for (int a = 0; a < 7; ++a)
-    if ((ptrdiff_t)(L.soa[1][a] - L.soa[0][a]) != shift)
-      return fail(CUBA_EINVAL, "internal: buffers not laid out alike");
-  if ((ptrdiff_t)(L.count[1] - L.count[0]) != shift ||
+  const ptrdiff_t shift = (char *)c->buf[1].st.rec - (char *)c->buf[0].st.rec;
+  if ((ptrdiff_t)(L.id[1] - L.id[0]) != shift ||
+      (ptrdiff_t)(L.count[1] - L.count[0]) != shift ||
       (ptrdiff_t)(L.spill_desc[1] - L.spill_desc[0]) != shift)
     return fail(CUBA_EINVAL, "internal: buffers not laid out alike");
   c->offsets = (uint32_t *)(ws + L.offsets);

@@ -27,9 +27,11 @@ constexpr uint32_t kErrPairIndex = 8u;  // a cell too full for the 32-bit pair i
 // 92 682; the bound is kept one lower, where the oracle puts it).
 constexpr uint32_t kMaxPairIndexCell = 92681u;
 
-// Structure-of-arrays particle state (FP64 position and momentum, u32 id).
-struct SoA {
-  double *x, *y, *z, *px, *py, *pz;
+// Particle state by slot: records of six doubles (px py pz x y z; 48 bytes,
+// 16-byte aligned) and, in an array of its own, the u32 ids (the collision
+// kernels read a cell's ids before anything else).
+struct Slots {
+  double *rec;
   uint32_t *id;
 };
 
@@ -61,7 +63,7 @@ __host__ __device__ inline uint32_t spill_set(uint32_t binning_step) {
 
 // A binned state with a fixed capacity per cell (see SpillDesc).
 struct Cells {
-  SoA st;
+  Slots st;
   uint32_t *count;
   uint32_t cap;
   SpillDesc *sp;

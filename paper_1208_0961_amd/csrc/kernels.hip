@@ -1,7 +1,8 @@
 // kernels.hip -- gfx950 kernels of the PIC Boltzmann step (arXiv:1208.0961).
 //
-// State layout: two structure-of-arrays buffers with a fixed capacity of
-// `cap` slots per cell; cell c owns slots [c cap, c cap + count[c]).  One
+// State layout: two buffers with a fixed capacity of `cap` slots per cell;
+// a slot is a 48-byte record (px py pz x y z) and an id in an array of its
+// own; cell c owns slots [c cap, c cap + count[c]).  One
 // buffer holds the current state, the other receives the next binning.
 //
 // A step t is stream + reflect + bin (Eq. (2), walls, cells), then the
@@ -57,13 +58,15 @@ constexpr int cell_waves() {
 template <typename T>
 using gptr = __attribute__((address_space(1))) T *;
 
-struct GSoA {
-  gptr<double> x, y, z, px, py, pz;
+// The particles' records (six doubles: px py pz x y z, 16-byte aligned) and
+// ids.
+struct GState {
+  gptr<double> rec;
   gptr<uint32_t> id;
 };
 
 struct GCells {
-  GSoA st;
+  GState st;
   gptr<uint32_t> count;
   uint32_t cap;
   SpillDesc *sp;
@@ -72,12 +75,7 @@ struct GCells {
 
 __device__ __forceinline__ GCells to_global(const Cells &c) {
   GCells g;
-  g.st.x = (gptr<double>)c.st.x;
-  g.st.y = (gptr<double>)c.st.y;
-  g.st.z = (gptr<double>)c.st.z;
-  g.st.px = (gptr<double>)c.st.px;
-  g.st.py = (gptr<double>)c.st.py;
-  g.st.pz = (gptr<double>)c.st.pz;
+  g.st.rec = (gptr<double>)c.st.rec;
   g.st.id = (gptr<uint32_t>)c.st.id;
   g.count = (gptr<uint32_t>)c.count;
   g.cap = c.cap;
@@ -141,26 +139,65 @@ __device__ __forceinline__ uint32_t xcd_runs(uint32_t b, uint32_t nblocks) {
   return s * kSuper + (r % kXcds) * kRun + r / kXcds;
 }
 
+// One particle in registers.
+struct Particle {
+  double x, y, z, px, py, pz;
+  uint32_t id;
+};
+
+// A record is 48 contiguous bytes, moved as three 16-byte accesses: a
+// scattered particle touches one or two cache lines instead of one in each
+// of six arrays, and so does a cell of a few particles.  Against six arrays
+// of doubles: the 32^3 fm^3 set's step 1.92 -> 1.49 ms, its stream-bin 1.95
+// -> 1.15 ms and its initial binning 5.88 -> 2.00 ms; 0.33 M particles in
+// 160 000 cells 49 -> 35 us a step; cells of ~100 particles 2-3 % (their
+// contiguous accesses were whole lines before, their movers' were not).
+// Two waves per cell at ~400 particles a cell lost 1.5 %.
+typedef double Double2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ gptr<Double2> record(const GState &st, size_t o) {
+  return (gptr<Double2>)(st.rec + 6u * o);
+}
+
+__device__ __forceinline__ Particle load_particle(const GState &st, size_t o) {
+  const gptr<Double2> r = record(st, o);
+  const Double2 a = r[0], b = r[1], c = r[2];
+  return Particle{b.y, c.x, c.y, a.x, a.y, b.x, st.id[o]};
+}
+
+__device__ __forceinline__ void put_particle(const GState &st, size_t o, const Particle &q) {
+  const gptr<Double2> r = record(st, o);
+  r[0] = Double2{q.px, q.py};
+  r[1] = Double2{q.pz, q.x};
+  r[2] = Double2{q.y, q.z};
+  st.id[o] = q.id;
+}
+
+__device__ __forceinline__ void load_momentum(const GState &st, size_t o, double &px, double &py,
+                                              double &pz) {
+  const Double2 a = record(st, o)[0];
+  px = a.x;
+  py = a.y;
+  pz = st.rec[6u * o + 2u];
+}
+
+__device__ __forceinline__ void put_momentum(const GState &st, size_t o, double px, double py,
+                                             double pz) {
+  record(st, o)[0] = Double2{px, py};
+  st.rec[6u * o + 2u] = pz;
+}
+
 // A particle that took slot `slot` >= cap of cell c2 goes to a spill slot
 // of dst, tagged with its cell; the one particle that takes slot cap lists
 // the cell among the overflowing ones.  The spill slots hold every particle
 // of the context, so the index check only guards against an internal error.
 __device__ __forceinline__ void spill_particle(const GCells &dst, uint32_t c2, uint32_t slot,
-                                               double x, double y, double z, double px,
-                                               double py, double pz, uint32_t id,
-                                               DevStatus *status) {
+                                               const Particle &q, DevStatus *status) {
   SpillDesc *const sp = dst.sp;
   uint32_t *const h = sp->hdr + 2u * dst.q;
   const uint32_t i = atomicAdd(&h[0], 1u);
   if (i < sp->capacity) {
-    const size_t o = sp->base + i;
-    dst.st.x[o] = x;
-    dst.st.y[o] = y;
-    dst.st.z[o] = z;
-    dst.st.px[o] = px;
-    dst.st.py[o] = py;
-    dst.st.pz[o] = pz;
-    dst.st.id[o] = id;
+    put_particle(dst.st, sp->base + i, q);
     sp->cell[i] = c2;
   } else {
     atomicOr(&status->err, kErrSpill);
@@ -168,36 +205,22 @@ __device__ __forceinline__ void spill_particle(const GCells &dst, uint32_t c2, u
   if (slot == dst.cap) sp->ocell[atomicAdd(&h[1], 1u)] = c2;
 }
 
-// Stores particle (r, p, id) at slot `slot` of cell c2 of dst: in the
-// cell's block, or past its capacity in the spill region.
-__device__ __forceinline__ void store_at_slot(const GCells &dst, uint32_t c2, uint32_t slot,
-                                              bool active, double x, double y, double z,
-                                              double px, double py, double pz, uint32_t id,
-                                              DevStatus *status) {
-  if (active) {
-    if (slot < dst.cap) {
-      const size_t o = (size_t)c2 * dst.cap + slot;
-      dst.st.x[o] = x;
-      dst.st.y[o] = y;
-      dst.st.z[o] = z;
-      dst.st.px[o] = px;
-      dst.st.py[o] = py;
-      dst.st.pz[o] = pz;
-      dst.st.id[o] = id;
-    } else {
-      spill_particle(dst, c2, slot, x, y, z, px, py, pz, id, status);
-    }
-  }
+// Stores a particle at slot `slot` of cell c2 of dst: in the cell's block,
+// or past its capacity in the spill region.
+__device__ __forceinline__ void store_particle(const GCells &dst, uint32_t c2, uint32_t slot,
+                                               const Particle &q, DevStatus *status) {
+  if (slot < dst.cap)
+    put_particle(dst.st, (size_t)c2 * dst.cap + slot, q);
+  else
+    spill_particle(dst, c2, slot, q, status);
 }
 
-// Appends particle (r, p, id) to cell c2 of dst (a slot by the
-// wave-aggregated counter atomic).
+// Appends a particle to cell c2 of dst (a slot by the wave-aggregated
+// counter atomic).
 __device__ __forceinline__ void append(const GCells &dst, uint32_t c2, bool active,
-                                       double x, double y, double z, double px,
-                                       double py, double pz, uint32_t id,
-                                       DevStatus *status) {
+                                       const Particle &q, DevStatus *status) {
   const uint32_t slot = aggregated_fetch_add(dst.count, c2, active);
-  store_at_slot(dst, c2, slot, active, x, y, z, px, py, pz, id, status);
+  if (active) store_particle(dst, c2, slot, q, status);
 }
 
 // The buffer laid out like c, `shift` bytes away.
@@ -213,12 +236,7 @@ __device__ __forceinline__ GCells dst_of(const GCells &src, int64_t shift, uint3
 
 __device__ __forceinline__ GCells shifted(const GCells &c, int64_t shift) {
   GCells d;
-  d.st.x = shift_ptr(c.st.x, shift);
-  d.st.y = shift_ptr(c.st.y, shift);
-  d.st.z = shift_ptr(c.st.z, shift);
-  d.st.px = shift_ptr(c.st.px, shift);
-  d.st.py = shift_ptr(c.st.py, shift);
-  d.st.pz = shift_ptr(c.st.pz, shift);
+  d.st.rec = shift_ptr(c.st.rec, shift);
   d.st.id = shift_ptr(c.st.id, shift);
   d.count = shift_ptr(c.count, shift);
   d.cap = c.cap;
@@ -229,32 +247,6 @@ __device__ __forceinline__ GCells shifted(const GCells &c, int64_t shift) {
 
 __device__ __forceinline__ GCells dst_of(const GCells &src, int64_t shift, uint32_t t) {
   return binning(shifted(src, shift), t + 1u);
-}
-
-// One particle in registers.
-struct Particle {
-  double x, y, z, px, py, pz;
-  uint32_t id;
-};
-
-__device__ __forceinline__ Particle load_particle(const GSoA &st, size_t o) {
-  return Particle{st.x[o], st.y[o], st.z[o], st.px[o], st.py[o], st.pz[o], st.id[o]};
-}
-
-__device__ __forceinline__ void store_particle(const GCells &dst, uint32_t c2, uint32_t slot,
-                                               const Particle &q, DevStatus *status) {
-  if (slot < dst.cap) {
-    const size_t o = (size_t)c2 * dst.cap + slot;
-    dst.st.x[o] = q.x;
-    dst.st.y[o] = q.y;
-    dst.st.z[o] = q.z;
-    dst.st.px[o] = q.px;
-    dst.st.py[o] = q.py;
-    dst.st.pz[o] = q.pz;
-    dst.st.id[o] = q.id;
-  } else {
-    spill_particle(dst, c2, slot, q.x, q.y, q.z, q.px, q.py, q.pz, q.id, status);
-  }
 }
 
 // Appends two particles per lane (a and b, up to 128 per wave) to cells ca
@@ -358,7 +350,7 @@ __global__ __launch_bounds__(kBlock) void k_init_bin(
     if (!ok) atomicOr(&status->err, kErrRange);
     cell = cell_id(g, a, b, c);
   }
-  append(dst, cell, active, a, b, c, qa, qb, qc, (uint32_t)i, status);
+  append(dst, cell, active, Particle{a, b, c, qa, qb, qc, (uint32_t)i}, status);
 }
 
 // Cells holding more than 8, 16, 32 and 64 particles, added into over[4]:
@@ -408,7 +400,7 @@ __device__ __forceinline__ void stream_spilled(const GCells &src, const GCells &
       c2 = cell_id(g, q.x, q.y, q.z);
       if (trace_cell) trace_cell[q.id] = c2;
     }
-    append(dst, c2, hit, q.x, q.y, q.z, q.px, q.py, q.pz, q.id, status);
+    append(dst, c2, hit, q, status);
   }
 }
 
@@ -470,21 +462,15 @@ __device__ __forceinline__ void cells_stream_bin(const GCells &src, const GCells
   for (uint32_t j0 = 0; __ballot(j0 < n) != 0; j0 += G) {
     const uint32_t j = j0 + gl;
     const bool active = j < n;
-    double x = 0, y = 0, z = 0, px = 0, py = 0, pz = 0;
-    uint32_t id = 0, c2 = 0;
+    Particle q{};
+    uint32_t c2 = 0;
     if (active) {
-      x = src.st.x[base + j];
-      y = src.st.y[base + j];
-      z = src.st.z[base + j];
-      px = src.st.px[base + j];
-      py = src.st.py[base + j];
-      pz = src.st.pz[base + j];
-      id = src.st.id[base + j];
-      advance<true>(g, x, y, z, px, py, pz);
-      c2 = cell_id(g, x, y, z);
-      if (trace_cell) trace_cell[id] = c2;
+      q = load_particle(src.st, base + j);
+      advance<true>(g, q.x, q.y, q.z, q.px, q.py, q.pz);
+      c2 = cell_id(g, q.x, q.y, q.z);
+      if (trace_cell) trace_cell[q.id] = c2;
     }
-    append(dst, c2, active, x, y, z, px, py, pz, id, status);
+    append(dst, c2, active, q, status);
   }
   if (in_range && gl == 0) src.count[c] = 0u;
 }
@@ -654,7 +640,7 @@ __device__ __forceinline__ void cell_sync() {
 // canonical indices lane + 64 j.  One wave; see cell_sync for kBlockSync.
 template <bool kTrace, bool kBlockSync = true>
 __device__ __forceinline__ void resolve_filtered(
-    uint32_t nf, const CellView &cv, const PairArgs &pa, const GSoA &st,
+    uint32_t nf, const CellView &cv, const PairArgs &pa, const GState &st,
     const uint16_t *s_perm, uint32_t *s_filt, uint32_t *s_claim,
     uint32_t &nclaim, uint32_t &claimed_bits, uint32_t &n_acc,
     const TraceArgs &tr, DevStatus *status) {
@@ -667,9 +653,10 @@ __device__ __forceinline__ void resolve_filtered(
     uint32_t a, b;
     pair_of_index(k, cv.n, a, b);
     const size_t ia = cv.at(s_perm[a]), ib = cv.at(s_perm[b]);
-    const double P = p22(st.px[ia], st.py[ia], st.pz[ia], st.px[ib], st.py[ib],
-                         st.pz[ib], pa.kfac);
-    const bool acc = u < P;
+    double ax, ay, az, bx, by, bz;
+    load_momentum(st, ia, ax, ay, az);
+    load_momentum(st, ib, bx, by, bz);
+    const bool acc = u < p22(ax, ay, az, bx, by, bz, pa.kfac);
     n_acc += acc ? 1u : 0u;
     s_filt[i] = acc ? (0x80000000u | (a << 10) | b) : 0u;
     if (kTrace && acc && tr.cand) {
@@ -716,7 +703,7 @@ __device__ __forceinline__ void resolve_filtered(
 template <bool kResolve, bool kTrace, bool kBlockSync, uint32_t kFiltCap>
 __device__ __forceinline__ uint32_t test_pairs(
     uint32_t k_begin, uint32_t k_end, const CellView &cv, const PairArgs &pa,
-    const GSoA &st, const uint16_t *s_perm, uint32_t *filt, uint32_t &nf,
+    const GState &st, const uint16_t *s_perm, uint32_t *filt, uint32_t &nf,
     uint32_t *s_claim, uint32_t &nclaim, uint32_t &claimed_bits, uint32_t &n_acc,
     const TraceArgs &tr, DevStatus *status) {
   static_assert(kFiltCap >= 256, "filter buffer");
@@ -930,7 +917,7 @@ __device__ void large_cell_step(const GCells &src, const GCells &dst, const Cell
   uint32_t *const perm = const_cast<uint32_t *>(cv.sidx) + (n - cv.cap);
   uint32_t *const claims = perm + n;
   uint32_t *const bits = claims + n / 2u + 1u;
-  const GSoA &st = src.st;
+  const GState &st = src.st;
   uint32_t npairs = 0;  // < 2^32 below the pair-index bound
   uint32_t nclaim = 0, n_acc = 0;
   if (n > kMaxPairIndexCell) {
@@ -965,8 +952,10 @@ __device__ void large_cell_step(const GCells &src, const GCells &dst, const Cell
         uint32_t a, b;
         pair_of_index64(k, n, a, b);
         const size_t ia = cv.at_spill(perm[a]), ib = cv.at_spill(perm[b]);
-        acc = uniform53(w.w0, w.w1) <
-              p22(st.px[ia], st.py[ia], st.pz[ia], st.px[ib], st.py[ib], st.pz[ib], pa.kfac);
+        double ax, ay, az, bx, by, bz;
+        load_momentum(st, ia, ax, ay, az);
+        load_momentum(st, ib, bx, by, bz);
+        acc = uniform53(w.w0, w.w1) < p22(ax, ay, az, bx, by, bz, pa.kfac);
         if (kTrace && acc && tr.cand) {
           const uint32_t slot = atomicAdd(&tr.counts[0], 1u);
           if (slot < tr.cand_cap) {
@@ -1009,15 +998,12 @@ __device__ void large_cell_step(const GCells &src, const GCells &dst, const Cell
       pair_of_index64(k, n, a, b);
       const Words4 w = philox10(k, cv.c, cv.t, 1u, pa.key0, pa.key1);
       const size_t ia = cv.at_spill(perm[a]), ib = cv.at_spill(perm[b]);
-      double ax = st.px[ia], ay = st.py[ia], az = st.pz[ia];
-      double bx = st.px[ib], by = st.py[ib], bz = st.pz[ib];
+      double ax, ay, az, bx, by, bz;
+      load_momentum(st, ia, ax, ay, az);
+      load_momentum(st, ib, bx, by, bz);
       scatter_pair(ax, ay, az, bx, by, bz, uniform53(w.w0, w.w1), uniform53(w.w2, w.w3));
-      st.px[ia] = ax;
-      st.py[ia] = ay;
-      st.pz[ia] = az;
-      st.px[ib] = bx;
-      st.py[ib] = by;
-      st.pz[ib] = bz;
+      put_momentum(st, ia, ax, ay, az);
+      put_momentum(st, ib, bx, by, bz);
       if (kTrace && tr.claim) {
         const uint32_t slot = atomicAdd(&tr.counts[1], 1u);
         if (slot < tr.claim_cap) {
@@ -1053,13 +1039,15 @@ __device__ void large_cell_step(const GCells &src, const GCells &dst, const Cell
         advance<true>(g_l, q.x, q.y, q.z, q.px, q.py, q.pz);
         c2 = cell_id(g_l, q.x, q.y, q.z);
       }
-      append(dst, c2, active, q.x, q.y, q.z, q.px, q.py, q.pz, q.id, status);
+      append(dst, c2, active, q, status);
     }
     if (lane == 0) src.count[cv.c] = 0u;
   } else if (obs) {
     for (uint32_t j = lane; j < n; j += 64u) {
       const size_t o = cv.at_spill(j);
-      obs_add(st.px[o], st.py[o], st.pz[o], se, sp, sxx);
+      double px, py, pz;
+      load_momentum(st, o, px, py, pz);
+      obs_add(px, py, pz, se, sp, sxx);
     }
   }
   if (obs) obs_write_wave(obs, cv.c, n, se, sp, sxx);
@@ -1146,7 +1134,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     }
   }
   const uint32_t n = cv.n;
-  const GSoA &st = src.st;
+  const GState &st = src.st;
   // observation sums only for one wave per cell (the batch's shape)
   double *const ob = kW == 1 ? obs : nullptr;
 
@@ -1322,12 +1310,8 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
         ja = s_perm[a];
         jb = s_perm[b];
         const size_t ia = cv.at(ja), ib = cv.at(jb);
-        ax = st.px[ia];
-        ay = st.py[ia];
-        az = st.pz[ia];
-        bx = st.px[ib];
-        by = st.py[ib];
-        bz = st.pz[ib];
+        load_momentum(st, ia, ax, ay, az);
+        load_momentum(st, ib, bx, by, bz);
         scatter_pair(ax, ay, az, bx, by, bz, uc, uphi);
         if (mom_lds) {
           s_mx[2u * i] = ax;
@@ -1339,12 +1323,8 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
           s_cmap[ja] = (uint8_t)(2u * i + 1u);
           s_cmap[jb] = (uint8_t)(2u * i + 2u);
         } else {
-          st.px[ia] = ax;
-          st.py[ia] = ay;
-          st.pz[ia] = az;
-          st.px[ib] = bx;
-          st.py[ib] = by;
-          st.pz[ib] = bz;
+          put_momentum(st, ia, ax, ay, az);
+          put_momentum(st, ib, bx, by, bz);
         }
         if (kTrace && tr.claim) {
           const uint32_t slot = atomicAdd(&tr.counts[1], 1u);
@@ -1378,31 +1358,24 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     for (uint32_t j0 = wv * 64u; j0 < n; j0 += kT) {
       const uint32_t j = j0 + lane;
       const bool active = j < n;
-      double x = 0, y = 0, z = 0, px = 0, py = 0, pz = 0;
-      uint32_t id = 0, c2 = 0, dir = 13u;
+      Particle q{};
+      uint32_t c2 = 0, dir = 13u;
       bool near = true;
       if (active) {
-        const size_t o = cv.at(j);
-        x = st.x[o];
-        y = st.y[o];
-        z = st.z[o];
-        px = st.px[o];
-        py = st.py[o];
-        pz = st.pz[o];
-        id = st.id[o];
+        q = load_particle(st, cv.at(j));
         if (mom_lds) {
           const uint32_t m = s_cmap[j];
           if (m != 0u) {
-            px = s_mx[m - 1u];
-            py = s_my[m - 1u];
-            pz = s_mz[m - 1u];
+            q.px = s_mx[m - 1u];
+            q.py = s_my[m - 1u];
+            q.pz = s_mz[m - 1u];
           }
         }
-        if (ob) obs_add(px, py, pz, se, sp, sxx);
-        advance<true>(g_l, x, y, z, px, py, pz);
-        const int32_t ix = axis_index(x, g_l.dx[0], g_l.n[0]);
-        const int32_t iy = axis_index(y, g_l.dx[1], g_l.n[1]);
-        const int32_t iz = axis_index(z, g_l.dx[2], g_l.n[2]);
+        if (ob) obs_add(q.px, q.py, q.pz, se, sp, sxx);
+        advance<true>(g_l, q.x, q.y, q.z, q.px, q.py, q.pz);
+        const int32_t ix = axis_index(q.x, g_l.dx[0], g_l.n[0]);
+        const int32_t iy = axis_index(q.y, g_l.dx[1], g_l.n[1]);
+        const int32_t iz = axis_index(q.z, g_l.dx[2], g_l.n[2]);
         c2 = (uint32_t)((ix * g_l.n[1] + iy) * g_l.n[2] + iz);
         const int32_t dx = ix - cx, dy = iy - cy, dz = iz - cz;
         // a move of less than a cell edge crosses at most one face per axis
@@ -1411,9 +1384,9 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
       }
       if (__ballot(!near) == 0ull) {
         const uint32_t slot = neighbour_fetch_add(dst.count, cv.c, sx, sy, dir, active, s_dir);
-        store_at_slot(dst, c2, slot, active, x, y, z, px, py, pz, id, status);
+        if (active) store_particle(dst, c2, slot, q, status);
       } else {
-        append(dst, c2, active, x, y, z, px, py, pz, id, status);
+        append(dst, c2, active, q, status);
       }
     }
     if (tid == 0) src.count[cv.c] = 0u;
@@ -1422,7 +1395,9 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     double se = 0.0, sp = 0.0, sxx = 0.0;
     for (uint32_t j = lane; j < n; j += 64u) {
       const size_t o = cv.at(j);
-      obs_add(st.px[o], st.py[o], st.pz[o], se, sp, sxx);
+      double px, py, pz;
+      load_momentum(st, o, px, py, pz);
+      obs_add(px, py, pz, se, sp, sxx);
     }
     obs_write_wave(ob, cv.c, n, se, sp, sxx);
   }
@@ -1480,21 +1455,20 @@ __device__ __forceinline__ uint64_t small_cells_step(const GCells &src, const GC
   const bool mine = small && gl < n;
   const size_t o = (size_t)c * src.cap + gl;
   __syncthreads();  // a previous call's readers of lds are done
+  double qx = 0, qy = 0, qz = 0;
   {
     uint32_t id = kNone;  // ids are below 2^32 - 1, so kNone ranks after all
     if (mine) {
-      lds.x[lane] = src.st.x[o];
-      lds.y[lane] = src.st.y[o];
-      lds.z[lane] = src.st.z[o];
-      id = src.st.id[o];
+      const Particle q = load_particle(src.st, o);
+      lds.x[lane] = q.x;
+      lds.y[lane] = q.y;
+      lds.z[lane] = q.z;
+      qx = q.px;
+      qy = q.py;
+      qz = q.pz;
+      id = q.id;
     }
     lds.id[lane] = id;
-  }
-  double qx = 0, qy = 0, qz = 0;
-  if (mine) {
-    qx = src.st.px[o];
-    qy = src.st.py[o];
-    qz = src.st.pz[o];
   }
   __syncthreads();
   uint32_t r = 0;
@@ -1605,11 +1579,7 @@ __device__ __forceinline__ uint64_t small_cells_step(const GCells &src, const GC
     px = lo ? ax : bx;
     py = lo ? ay : by;
     pz = lo ? az : bz;
-    if (!kFused) {
-      src.st.px[o] = px;
-      src.st.py[o] = py;
-      src.st.pz[o] = pz;
-    }
+    if (!kFused) put_momentum(src.st, o, px, py, pz);
   }
 
   if (obs) {  // the cell's sums over its G lanes, written by its first lane
@@ -1640,7 +1610,7 @@ __device__ __forceinline__ uint64_t small_cells_step(const GCells &src, const GC
       advance<true>(g, x, y, z, px, py, pz);
       c2 = cell_id(g, x, y, z);
     }
-    append(dst, c2, mine, x, y, z, px, py, pz, id, status);
+    append(dst, c2, mine, Particle{x, y, z, px, py, pz, id}, status);
     if (small && gl == 0) src.count[c] = 0u;
   }
   return __ballot(in_range && !small && !overflowing && gl == 0);
@@ -1842,13 +1812,14 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
       uint32_t id = kNone;
       if (mine) {
         const size_t o = (size_t)c * src.cap + gl;
-        lds.x[lane] = src.st.x[o];
-        lds.y[lane] = src.st.y[o];
-        lds.z[lane] = src.st.z[o];
-        lds.px[lane] = src.st.px[o];  // by lane until ranked
-        lds.py[lane] = src.st.py[o];
-        lds.pz[lane] = src.st.pz[o];
-        id = src.st.id[o];
+        const Particle q = load_particle(src.st, o);
+        lds.x[lane] = q.x;
+        lds.y[lane] = q.y;
+        lds.z[lane] = q.z;
+        lds.px[lane] = q.px;  // by lane until ranked
+        lds.py[lane] = q.py;
+        lds.pz[lane] = q.pz;
+        id = q.id;
       }
       lds.id[lane] = id;
     }
@@ -1919,10 +1890,7 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
       py = lo ? ay : by;
       pz = lo ? az : bz;
       if (!kFused) {
-        const size_t o = (size_t)c * src.cap + gl;
-        src.st.px[o] = px;
-        src.st.py[o] = py;
-        src.st.pz[o] = pz;
+        put_momentum(src.st, (size_t)c * src.cap + gl, px, py, pz);
       }
     }
     if (kFused) {
@@ -1937,7 +1905,7 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
         advance<true>(g_l, x, y, z, px, py, pz);
         c2 = cell_id(g_l, x, y, z);
       }
-      append(dst, c2, mine, x, y, z, px, py, pz, id, status);
+      append(dst, c2, mine, Particle{x, y, z, px, py, pz, id}, status);
     }
     base = end;
   }
@@ -2224,7 +2192,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<k
   const uint32_t s = (E->cur ^ (j & 1u)) & 1u;
   const uint32_t t = E->t + j - 1u;
   const GCells src = binning(to_global(E->buf[s]), t);
-  const int64_t shift = (const char *)E->buf[s ^ 1u].st.x - (const char *)E->buf[s].st.x;
+  const int64_t shift = (const char *)E->buf[s ^ 1u].st.rec - (const char *)E->buf[s].st.rec;
   const PairArgs pa = E->pa;
   cell_step<kFused, false, kCap>(src, dst_of(src, shift, t), unit - E->cell_begin, t,
                                  pa, E->g, E->status, TraceArgs{}, lds, nullptr,
@@ -2259,8 +2227,8 @@ __global__ __launch_bounds__(kBlock) void k_observe_cells(Cells cur_arg, uint32_
   const size_t base = (size_t)c * cur.cap;
   double se = 0.0, sp = 0.0, sxx = 0.0;
   for (uint32_t j = lane; j < n; j += 64) {
-    const double px = cur.st.px[base + j], py = cur.st.py[base + j],
-                 pz = cur.st.pz[base + j];
+    double px, py, pz;
+    load_momentum(cur.st, base + j, px, py, pz);
     const double e = norm3(px, py, pz);
     se += e;
     sp += px;
@@ -2272,7 +2240,8 @@ __global__ __launch_bounds__(kBlock) void k_observe_cells(Cells cur_arg, uint32_
     for (uint32_t i = lane; i < ns; i += 64) {
       if (spl->cell[i] != c) continue;
       const size_t o = spl->base + i;
-      const double px = cur.st.px[o], py = cur.st.py[o], pz = cur.st.pz[o];
+      double px, py, pz;
+      load_momentum(cur.st, o, px, py, pz);
       const double e = norm3(px, py, pz);
       se += e;
       sp += px;
@@ -2385,27 +2354,26 @@ __global__ __launch_bounds__(kBlock) void k_gather_by_id(Cells cur_arg, uint32_t
   const uint32_t n = occupancy(cur, c);
   const size_t base = (size_t)c * cur.cap;
   for (uint32_t j = lane; j < n; j += 64) {
-    const uint32_t id = cur.st.id[base + j];
-    x[id] = cur.st.x[base + j];
-    y[id] = cur.st.y[base + j];
-    z[id] = cur.st.z[base + j];
-    px[id] = cur.st.px[base + j];
-    py[id] = cur.st.py[base + j];
-    pz[id] = cur.st.pz[base + j];
+    const Particle q = load_particle(cur.st, base + j);
+    x[q.id] = q.x;
+    y[q.id] = q.y;
+    z[q.id] = q.z;
+    px[q.id] = q.px;
+    py[q.id] = q.py;
+    pz[q.id] = q.pz;
   }
   if (cur.count[c] > cur.cap) {  // overflowing: its spilled members
     const SpillDesc *const spl = cur.sp;
     const uint32_t ns = min(spl->hdr[2u * cur.q], spl->capacity);
     for (uint32_t i = lane; i < ns; i += 64) {
       if (spl->cell[i] != c) continue;
-      const size_t o = spl->base + i;
-      const uint32_t id = cur.st.id[o];
-      x[id] = cur.st.x[o];
-      y[id] = cur.st.y[o];
-      z[id] = cur.st.z[o];
-      px[id] = cur.st.px[o];
-      py[id] = cur.st.py[o];
-      pz[id] = cur.st.pz[o];
+      const Particle q = load_particle(cur.st, spl->base + i);
+      x[q.id] = q.x;
+      y[q.id] = q.y;
+      z[q.id] = q.z;
+      px[q.id] = q.px;
+      py[q.id] = q.py;
+      pz[q.id] = q.pz;
     }
   }
 }
@@ -2535,7 +2503,7 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
                      const TraceArgs &tr, hipStream_t s, const SideStream *side,
                      const StepDevice &dev) {
   const dim3 block(64);
-  const int64_t shift = (int64_t)((const char *)dst.st.x - (const char *)src.st.x);
+  const int64_t shift = (int64_t)((const char *)dst.st.rec - (const char *)src.st.rec);
   // one kernel: timing events ride on its dispatch (no packets of their own
   // between launches)
   if (lanes == kTwoWavesPerCell && !kTrace) {
@@ -2560,7 +2528,7 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
   switch (lanes) {
     case kPackedCells:
       hipLaunchKernelGGL((k_step_packed<kFused, kTrace>), grid, block, 0, s, src,
-                         (int64_t)((const char *)dst.st.x - (const char *)src.st.x), n_cells, t,
+                         (int64_t)((const char *)dst.st.rec - (const char *)src.st.rec), n_cells, t,
                          pa, dev.g, status, tr);
       break;
     case 8:
@@ -2582,7 +2550,7 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
   hipStream_t so = side ? side->stream : s;
   if (dev.over_span == 1)
     hipLaunchKernelGGL((k_step_over<kFused, kTrace, kCap>), dim3(n_cells), block, 0, so, src,
-                       (int64_t)((const char *)dst.st.x - (const char *)src.st.x), thr, t,
+                       (int64_t)((const char *)dst.st.rec - (const char *)src.st.rec), thr, t,
                        pa, dev.g, status, tr);
   else
     hipLaunchKernelGGL((k_step_large<kFused, kTrace, kCap>), dim3((n_cells + 63) / 64), block,
