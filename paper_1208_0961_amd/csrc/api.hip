@@ -133,6 +133,7 @@ int derive(const cuba_params *p, int64_t n, Derived &d) {
     d.g.L[k] = p->box[k];
     d.g.n[k] = p->cells[k];
     d.g.dx[k] = p->box[k] / (double)p->cells[k];
+    d.g.rdx[k] = 1.0 / d.g.dx[k];
     // Sec. 5: dt below the cell edge, so a particle moves at most one cell
     if (!(p->dt < d.g.dx[k])) return fail(CUBA_EINVAL, "dt must be below every cell edge");
   }

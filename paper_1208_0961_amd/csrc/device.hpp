@@ -95,12 +95,49 @@ __device__ __forceinline__ double uniform53(uint32_t lo, uint32_t hi) {
 struct Geometry {
   double L[3];   // box edges
   double dx[3];  // cell edges L_d / n_d
+  double rdx[3]; // their rounded reciprocals
   int32_t n[3];  // cells per axis
   double dt;
 };
 
 __device__ __forceinline__ double norm3(double a, double b, double c) {
   return __builtin_sqrt((a * a + b * b) + c * c);
+}
+
+__device__ __forceinline__ uint32_t high_word(double v) {
+  return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32);
+}
+
+// v = p / e, every component correctly rounded.  The three quotients share
+// one reciprocal: r = 1/e by two Newton steps, then per component
+// q = p r and q + (p - e q) r, which rounds correctly when no intermediate
+// leaves the normal range (Markstein, IBM J. Res. Dev. 34, 1990).  With
+// |p_d| >= 2^-500 and e <= 2^250 (hence e >= 2^-500) every intermediate is
+// normal: r lies in [2^-250, 2^500], |q| in [2^-750, 1], and the remainder
+// is a multiple of 2^-605, so exact.  Other lanes (a component of
+// zero, say) divide.  Three full divisions scale, fix up and invert e three
+// times.  With cell_axes below: the full tube's 12-step event 20.2 -> 19.8
+// ms, the 3-D tube's 50 steps 5.05 -> 4.95 ms, small batched events 31.7 ->
+// 30.3 ms, 2 M particles at 12 a cell 9.32 -> 9.06 ms.
+__device__ __forceinline__ void unit_velocity(double px, double py, double pz, double e,
+                                              double &vx, double &vy, double &vz) {
+  const uint32_t hx = high_word(px) & 0x7FFFFFFFu, hy = high_word(py) & 0x7FFFFFFFu,
+                 hz = high_word(pz) & 0x7FFFFFFFu;
+  const uint32_t lo = min(min(hx, hy), hz);
+  constexpr uint32_t kMin = (1023u - 500u) << 20, kMax = (1023u + 250u) << 20;
+  if (__builtin_expect(lo >= kMin && high_word(e) < kMax, 1)) {
+    double r = __builtin_amdgcn_rcp(e);
+    r = __builtin_fma(r, __builtin_fma(-e, r, 1.0), r);
+    r = __builtin_fma(r, __builtin_fma(-e, r, 1.0), r);
+    const double qx = px * r, qy = py * r, qz = pz * r;
+    vx = __builtin_fma(__builtin_fma(-e, qx, px), r, qx);
+    vy = __builtin_fma(__builtin_fma(-e, qy, py), r, qy);
+    vz = __builtin_fma(__builtin_fma(-e, qz, pz), r, qz);
+  } else {
+    vx = px / e;
+    vy = py / e;
+    vz = pz / e;
+  }
 }
 
 // Free streaming over dt, then specular reflection at the walls 0 and L_d.
@@ -111,7 +148,8 @@ __device__ __forceinline__ void advance(const Geometry &g, double &x, double &y,
   if (kStream) {
     const double e = norm3(px, py, pz);
     if (e != 0.0) {
-      const double vx = px / e, vy = py / e, vz = pz / e;
+      double vx, vy, vz;
+      unit_velocity(px, py, pz, e, vx, vy, vz);
       x = x + vx * g.dt;
       y = y + vy * g.dt;
       z = z + vz * g.dt;
@@ -146,12 +184,34 @@ __device__ __forceinline__ int32_t axis_index(double q, double d, int32_t n) {
   return i > n - 1 ? n - 1 : i;
 }
 
+// The axis indices of a position, floor(q / d) with the rounded quotient,
+// clamped.  t = q RN(1/d) lies within 2^-51 t of q / d, so where t is at
+// least 2^-20 from an integer (and below 2^31, as any n is) the two have
+// the same floor; otherwise (about 4 waves in 10 000; also NaN and huge
+// positions, whose fraction is 0 or NaN) the lane divides.
+__device__ __forceinline__ void cell_axes(const Geometry &g, double x, double y, double z,
+                                          int32_t &ix, int32_t &iy, int32_t &iz) {
+  const double tx = x * g.rdx[0], ty = y * g.rdx[1], tz = z * g.rdx[2];
+  constexpr double kFar = 0.5 - 0x1p-20;
+  const bool far = __builtin_fabs(__builtin_amdgcn_fract(tx) - 0.5) < kFar &&
+                   __builtin_fabs(__builtin_amdgcn_fract(ty) - 0.5) < kFar &&
+                   __builtin_fabs(__builtin_amdgcn_fract(tz) - 0.5) < kFar;
+  if (__builtin_expect(far, 1)) {
+    ix = min(max((int32_t)tx, 0), g.n[0] - 1);  // (truncation: a negative t clamps to 0)
+    iy = min(max((int32_t)ty, 0), g.n[1] - 1);
+    iz = min(max((int32_t)tz, 0), g.n[2] - 1);
+  } else {
+    ix = axis_index(x, g.dx[0], g.n[0]);
+    iy = axis_index(y, g.dx[1], g.n[1]);
+    iz = axis_index(z, g.dx[2], g.n[2]);
+  }
+}
+
 // x-major cell id.
 __device__ __forceinline__ uint32_t cell_id(const Geometry &g, double x, double y,
                                            double z) {
-  const int32_t ix = axis_index(x, g.dx[0], g.n[0]);
-  const int32_t iy = axis_index(y, g.dx[1], g.n[1]);
-  const int32_t iz = axis_index(z, g.dx[2], g.n[2]);
+  int32_t ix, iy, iz;
+  cell_axes(g, x, y, z, ix, iy, iz);
   return (uint32_t)((ix * g.n[1] + iy) * g.n[2] + iz);
 }
 

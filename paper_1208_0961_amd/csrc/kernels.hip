@@ -1442,9 +1442,8 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
         }
         if (ob) obs_add(q.px, q.py, q.pz, se, sp, sxx);
         advance<true>(g_l, q.x, q.y, q.z, q.px, q.py, q.pz);
-        const int32_t ix = axis_index(q.x, g_l.dx[0], g_l.n[0]);
-        const int32_t iy = axis_index(q.y, g_l.dx[1], g_l.n[1]);
-        const int32_t iz = axis_index(q.z, g_l.dx[2], g_l.n[2]);
+        int32_t ix, iy, iz;
+        cell_axes(g_l, q.x, q.y, q.z, ix, iy, iz);
         c2 = (uint32_t)((ix * g_l.n[1] + iy) * g_l.n[2] + iz);
         const int32_t dx = ix - cx, dy = iy - cy, dz = iz - cz;
         // a move of less than a cell edge crosses at most one face per axis
