@@ -704,7 +704,7 @@ int cuba_observe(cuba_ctx *c, double *T00, double *T0x) {
   if (!c || !T00 || !T0x) return fail(CUBA_EINVAL, "NULL argument");
   const SlabOut out{T00, T0x, nullptr, nullptr, nullptr, nullptr};
   stage(c, kStageObserve, [&](const TimedLaunch *) {
-    launch_observe(c->buf[c->cur], c->d.g, c->d.vol, c->cell_sums, out, c->next_step - 1u,
+    launch_observe(c->buf[c->cur], c->d.g, c->n, c->d.vol, c->cell_sums, out, c->next_step - 1u,
                    c->stream);
   });
   return check_launch("observe launch");
@@ -715,7 +715,7 @@ int cuba_observe_moments(cuba_ctx *c, double *out) {
   const int64_t nx = c->d.g.n[0];
   const SlabOut o{out, out + nx, out + 2 * nx, out + 3 * nx, out + 4 * nx, out + 5 * nx};
   stage(c, kStageObserve, [&](const TimedLaunch *) {
-    launch_observe(c->buf[c->cur], c->d.g, c->d.vol, c->cell_sums, o, c->next_step - 1u,
+    launch_observe(c->buf[c->cur], c->d.g, c->n, c->d.vol, c->cell_sums, o, c->next_step - 1u,
                    c->stream);
   });
   return check_launch("observe launch");
@@ -726,8 +726,10 @@ int cuba_get_state(cuba_ctx *c, double *x, double *y, double *z, double *px,
   if (!c) return fail(CUBA_EINVAL, "ctx is NULL");
   if (c->n > 0 && !(x && y && z && px && py && pz))
     return fail(CUBA_EINVAL, "NULL output array");
-  launch_gather_by_id(c->buf[c->cur], c->d.n_cells, x, y, z, px, py, pz, c->next_step - 1u,
-                      c->stream);
+  // the slots' index goes to the idle buffer's ids (no slot of it is in use
+  // between steps, and it holds more than n words)
+  launch_export(c->buf[c->cur], c->d.n_cells, c->n, c->buf[c->cur ^ 1].st.id, x, y, z, px, py,
+                pz, c->next_step - 1u, c->stream);
   return check_launch("get_state launch");
 }
 

@@ -235,8 +235,9 @@ struct SlabOut {
 constexpr uint32_t kCellSums = 4;  // per cell: sum E, sum p_x, sum p_x^2 / E, count
 // cell_sums: scratch of kCellSums doubles per cell.  cur holds the binning
 // of step binning_step.
-void launch_observe(const Cells &cur, const Geometry &g, double vol, double *cell_sums,
-                    const SlabOut &out, uint32_t binning_step, hipStream_t s);
+void launch_observe(const Cells &cur, const Geometry &g, int64_t n, double vol,
+                    double *cell_sums, const SlabOut &out, uint32_t binning_step,
+                    hipStream_t s);
 // A run of k >= 1 steps of every event in the device table ev (n_events
 // live events): stream + bin, k - 1 fused steps, the last collisions, then
 // the table advance.  The work spaces: items of cells_per_item cells for the
@@ -260,8 +261,9 @@ void launch_batch_run(BatchEvent *ev, const BatchSpaces &spaces, uint32_t n_even
                       uint32_t persistent_waves, hipStream_t s, const SideStream *side,
                       void (*between)(void *, int), void *ctx,
                       const uint8_t *obs_at = nullptr);
-void launch_gather_by_id(const Cells &cur, int64_t n_cells, double *x, double *y,
-                         double *z, double *px, double *py, double *pz,
-                         uint32_t binning_step, hipStream_t s);
+// The state in id order; slot_of: scratch of n words.
+void launch_export(const Cells &cur, int64_t n_cells, int64_t n, uint32_t *slot_of, double *x,
+                   double *y, double *z, double *px, double *py, double *pz,
+                   uint32_t binning_step, hipStream_t s);
 
 }  // namespace cuba

@@ -422,10 +422,14 @@ __global__ __launch_bounds__(kBlock) void k_init_bin(
     if (!ok) atomicOr(&status->err, kErrRange);
     cell = cell_id(g, a, b, c);
   }
-  // neighbouring lanes hold unrelated cells, so each takes its own slot
-  if (active)
-    store_particle(dst, cell, atomic_add(dst.count + cell, 1u),
-                   Particle{a, b, c, qa, qb, qc, (uint32_t)i}, status);
+  // neighbouring lanes hold unrelated cells, so each takes its own slot,
+  // unless the box has so few cells that a wave's lanes meet in one (100
+  // cells: 16 us by an atomic a lane, 8 grouped)
+  const Particle q{a, b, c, qa, qb, qc, (uint32_t)i};
+  if (g.n[0] * g.n[1] * g.n[2] <= 1024)
+    append(dst, cell, active, q, status);
+  else if (active)
+    store_particle(dst, cell, atomic_add(dst.count + cell, 1u), q, status);
 }
 
 // Cells holding more than 8, 16, 32 and 64 particles, added into over[4]:
@@ -2284,50 +2288,45 @@ __global__ void k_batch_advance(BatchEvent *ev, uint32_t n_events, uint32_t k) {
 }
 
 // ---------------------------------------------------------------------------
-// Observe: per-cell sums of E and p_x (one wave per cell), then per-slab
-// sums over the slab's cells in cell order.  Slab ix is the contiguous cell
-// range [ix ny nz, (ix+1) ny nz).
+// Observe: per-cell sums of E and p_x, then per-slab sums over the slab's
+// cells in cell order.  Slab ix is the contiguous cell range
+// [ix ny nz, (ix+1) ny nz).
 // ---------------------------------------------------------------------------
+// G lanes per cell (8, 16, 32 or 64, by the mean occupancy: with a wave per
+// cell the 2.1 M cells of the 32^3 fm^3 set took 746 us, now 285).
+template <uint32_t G>
 __global__ __launch_bounds__(kBlock) void k_observe_cells(Cells cur_arg, uint32_t n_cells,
                                                           double *cell_sums,
                                                           uint32_t binning_step) {
   const GCells cur = binning(to_global(cur_arg), binning_step);
-  const uint32_t lane = lane_id();
-  const uint32_t c = blockIdx.x * kCellsPerBlock + threadIdx.x / 64;
-  if (c >= n_cells) return;
-  const uint32_t cnt = cur.count[c];
-  const uint32_t n = occupancy(cur, c);
+  const uint32_t gl = lane_id() % G;
+  const uint32_t c = (blockIdx.x * kBlock + threadIdx.x) / G;
+  const uint32_t cnt = c < n_cells ? cur.count[c] : 0u;
+  const uint32_t n = cnt < cur.cap ? cnt : cur.cap;
   const size_t base = (size_t)c * cur.cap;
   double se = 0.0, sp = 0.0, sxx = 0.0;
-  for (uint32_t j = lane; j < n; j += 64) {
+  for (uint32_t j = gl; j < n; j += G) {
     double px, py, pz;
     load_momentum(cur.st, base + j, px, py, pz);
-    const double e = norm3(px, py, pz);
-    se += e;
-    sp += px;
-    sxx += (px * px) / e;
+    obs_add(px, py, pz, se, sp, sxx);
   }
   if (cnt > cur.cap) {  // overflowing: its spilled members, in spill order
     const SpillDesc *const spl = cur.sp;
     const uint32_t ns = min(spl->hdr[2u * cur.q], spl->capacity);
-    for (uint32_t i = lane; i < ns; i += 64) {
+    for (uint32_t i = gl; i < ns; i += G) {
       if (spl->cell[i] != c) continue;
-      const size_t o = spl->base + i;
       double px, py, pz;
-      load_momentum(cur.st, o, px, py, pz);
-      const double e = norm3(px, py, pz);
-      se += e;
-      sp += px;
-      sxx += (px * px) / e;
+      load_momentum(cur.st, spl->base + i, px, py, pz);
+      obs_add(px, py, pz, se, sp, sxx);
     }
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    se += __shfl_down(se, o);
-    sp += __shfl_down(sp, o);
-    sxx += __shfl_down(sxx, o);
+  for (int o = G / 2; o > 0; o >>= 1) {
+    se += __shfl_xor(se, o);
+    sp += __shfl_xor(sp, o);
+    sxx += __shfl_xor(sxx, o);
   }
-  if (lane == 0) {
+  if (gl == 0 && c < n_cells) {
     double *const out = cell_sums + kCellSums * (size_t)c;
     out[0] = se;
     out[1] = sp;
@@ -2416,6 +2415,8 @@ __global__ __launch_bounds__(kBlock) void k_batch_observe(const BatchEvent *__re
   slab_moments(E->obs_sums, (uint32_t)(E->g.n[1] * E->g.n[2]), E->obs_vol, blockIdx.x, o);
 }
 
+// State export in one launch, one wave per cell (small states, whose outputs
+// stay in the caches).
 __global__ __launch_bounds__(kBlock) void k_gather_by_id(Cells cur_arg, uint32_t n_cells,
                                                          double *x, double *y, double *z,
                                                          double *px, double *py,
@@ -2424,34 +2425,90 @@ __global__ __launch_bounds__(kBlock) void k_gather_by_id(Cells cur_arg, uint32_t
   const uint32_t lane = lane_id();
   const uint32_t c = blockIdx.x * kCellsPerBlock + threadIdx.x / 64;
   if (c >= n_cells) return;
-  const uint32_t n = occupancy(cur, c);
-  const size_t base = (size_t)c * cur.cap;
-  for (uint32_t j = lane; j < n; j += 64) {
-    const Particle q = load_particle(cur.st, base + j);
+  const auto put = [&](size_t o) {
+    const Particle q = load_particle(cur.st, o);
     x[q.id] = q.x;
     y[q.id] = q.y;
     z[q.id] = q.z;
     px[q.id] = q.px;
     py[q.id] = q.py;
     pz[q.id] = q.pz;
-  }
+  };
+  const uint32_t n = occupancy(cur, c);
+  const size_t base = (size_t)c * cur.cap;
+  for (uint32_t j = lane; j < n; j += 64) put(base + j);
   if (cur.count[c] > cur.cap) {  // overflowing: its spilled members
     const SpillDesc *const spl = cur.sp;
     const uint32_t ns = min(spl->hdr[2u * cur.q], spl->capacity);
-    for (uint32_t i = lane; i < ns; i += 64) {
-      if (spl->cell[i] != c) continue;
-      const Particle q = load_particle(cur.st, spl->base + i);
-      x[q.id] = q.x;
-      y[q.id] = q.y;
-      z[q.id] = q.z;
-      px[q.id] = q.px;
-      py[q.id] = q.py;
-      pz[q.id] = q.pz;
-    }
+    for (uint32_t i = lane; i < ns; i += 64)
+      if (spl->cell[i] == c) put(spl->base + i);
   }
 }
 
+// State export of larger states, first of two launches: slot_of[id] for
+// every particle, G lanes per cell; the second reads the records in id
+// order.  What is scattered is then 4 bytes written and one record read a
+// particle, not six 8-byte writes (each a partial line): 16.3 M particles
+// 3.42 -> 0.96 ms, 24.9 M in 2.1 M cells 5.99 -> 1.46 ms, 0.33 M 46 -> 20
+// us; below some 10^5 particles the second launch costs more than it saves
+// (10 000: 6 us in one launch, 8 in two).
+constexpr int64_t kIndexedExportMin = 1 << 17;
+template <uint32_t G>
+__global__ __launch_bounds__(kBlock) void k_index_by_id(Cells cur_arg, uint32_t n_cells,
+                                                        uint32_t *slot_of,
+                                                        uint32_t binning_step) {
+  const GCells cur = binning(to_global(cur_arg), binning_step);
+  const uint32_t gl = lane_id() % G;
+  const uint32_t c = (blockIdx.x * kBlock + threadIdx.x) / G;
+  if (c >= n_cells) return;
+  const uint32_t cnt = cur.count[c];
+  const uint32_t n = cnt < cur.cap ? cnt : cur.cap;
+  const size_t base = (size_t)c * cur.cap;
+  for (uint32_t j = gl; j < n; j += G) slot_of[cur.st.id[base + j]] = (uint32_t)(base + j);
+  if (cnt > cur.cap) {  // overflowing: its spilled members
+    const SpillDesc *const spl = cur.sp;
+    const uint32_t ns = min(spl->hdr[2u * cur.q], spl->capacity);
+    for (uint32_t i = gl; i < ns; i += G)
+      if (spl->cell[i] == c)
+        slot_of[cur.st.id[spl->base + i]] = (uint32_t)(spl->base + i);
+  }
+}
+
+// Second launch: the records in id order.
+__global__ __launch_bounds__(kBlock) void k_export_by_id(Cells cur_arg, int64_t n,
+                                                         const uint32_t *slot_of, double *x,
+                                                         double *y, double *z, double *px,
+                                                         double *py, double *pz) {
+  const GCells cur = to_global(cur_arg);
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  const gptr<Double2> r = record(cur.st, slot_of[i]);
+  const Double2 a = r[0], b = r[1], c = r[2];
+  px[i] = a.x;
+  py[i] = a.y;
+  pz[i] = b.x;
+  x[i] = b.y;
+  y[i] = c.x;
+  z[i] = c.y;
+}
+
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
+// Lanes per cell of the kernels that walk the cells of a state of n
+// particles: the mean occupancy, rounded up to a power of two within 8 .. 64.
+inline uint32_t walk_lanes(int64_t n, int64_t n_cells) {
+  uint32_t g = 8;
+  while (g < 64 && (int64_t)g * n_cells < n) g *= 2;
+  return g;
+}
+template <typename F>
+void with_walk_lanes(uint32_t g, F &&f) {
+  switch (g) {
+    case 8: f(std::integral_constant<uint32_t, 8>{}); break;
+    case 16: f(std::integral_constant<uint32_t, 16>{}); break;
+    case 32: f(std::integral_constant<uint32_t, 32>{}); break;
+    default: f(std::integral_constant<uint32_t, 64>{});
+  }
+}
 inline unsigned cell_blocks(int64_t n_cells) {
   return (unsigned)((n_cells + kCellsPerBlock - 1) / kCellsPerBlock);
 }
@@ -2689,7 +2746,13 @@ __global__ __launch_bounds__(kBlock) void k_max_u32(const uint32_t *__restrict__
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
     m = max(m, v[i]);
   m = wave_max(m);
-  if (lane_id() == 0) atomicMax(out, m);
+  __shared__ uint32_t part[kBlock / 64];
+  if (lane_id() == 0) part[threadIdx.x / 64] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (uint32_t w = 1; w < kBlock / 64; ++w) m = max(m, part[w]);
+    atomicMax(out, m);
+  }
 }
 
 }  // namespace
@@ -2703,7 +2766,9 @@ void launch_count_cells(const double *x, const double *y, const double *z, int64
     const unsigned grid = grid_for(n) < 4096u ? grid_for(n) : 4096u;
     hipLaunchKernelGGL(k_count_cells, dim3(grid), dim3(kBlock), 0, s, x, y, z, n, g, count);
   }
-  const unsigned grid = grid_for(n_cells) < 1024u ? grid_for(n_cells) : 1024u;
+  // few blocks, one atomic each: atomics on the one word run one after the
+  // other (160 000 cells: 31 us with 2 500 of them)
+  const unsigned grid = grid_for(n_cells) < 256u ? grid_for(n_cells) : 256u;
   hipLaunchKernelGGL(k_max_u32, dim3(grid), dim3(kBlock), 0, s, (const uint32_t *)count,
                      n_cells, max_count);
 }
@@ -2716,11 +2781,15 @@ void launch_occupancy_over(const Cells &cur, int64_t n_cells, DevStatus *status,
                      (uint32_t)n_cells, status->over);
 }
 
-void launch_observe(const Cells &cur, const Geometry &g, double vol, double *cell_sums,
-                    const SlabOut &out, uint32_t binning_step, hipStream_t s) {
+void launch_observe(const Cells &cur, const Geometry &g, int64_t n, double vol,
+                    double *cell_sums, const SlabOut &out, uint32_t binning_step,
+                    hipStream_t s) {
   const int64_t n_cells = (int64_t)g.n[0] * g.n[1] * g.n[2];
-  hipLaunchKernelGGL(k_observe_cells, dim3(cell_blocks(n_cells)), dim3(kBlock), 0, s, cur,
-                     (uint32_t)n_cells, cell_sums, binning_step);
+  const uint32_t G = walk_lanes(n, n_cells);
+  with_walk_lanes(G, [&](auto lanes) {
+    hipLaunchKernelGGL((k_observe_cells<lanes.value>), dim3(grid_for(n_cells * G)),
+                       dim3(kBlock), 0, s, cur, (uint32_t)n_cells, cell_sums, binning_step);
+  });
   hipLaunchKernelGGL(k_observe_slabs, dim3((unsigned)g.n[0]), dim3(kBlock), 0, s,
                      (const double *)cell_sums, (uint32_t)(g.n[1] * g.n[2]), vol, out);
 }
@@ -2783,12 +2852,22 @@ void launch_batch_run(BatchEvent *ev, const BatchSpaces &sp, uint32_t n_events, 
                      n_events, (uint32_t)k);
 }
 
-void launch_gather_by_id(const Cells &cur, int64_t n_cells, double *x, double *y,
-                         double *z, double *px, double *py, double *pz,
-                         uint32_t binning_step, hipStream_t s) {
-  if (n_cells <= 0) return;
-  hipLaunchKernelGGL(k_gather_by_id, dim3(cell_blocks(n_cells)), dim3(kBlock), 0, s, cur,
-                     (uint32_t)n_cells, x, y, z, px, py, pz, binning_step);
+void launch_export(const Cells &cur, int64_t n_cells, int64_t n, uint32_t *slot_of, double *x,
+                   double *y, double *z, double *px, double *py, double *pz,
+                   uint32_t binning_step, hipStream_t s) {
+  if (n_cells <= 0 || n <= 0) return;
+  if (n < kIndexedExportMin) {
+    hipLaunchKernelGGL(k_gather_by_id, dim3(cell_blocks(n_cells)), dim3(kBlock), 0, s, cur,
+                       (uint32_t)n_cells, x, y, z, px, py, pz, binning_step);
+    return;
+  }
+  const uint32_t G = walk_lanes(n, n_cells);
+  with_walk_lanes(G, [&](auto lanes) {
+    hipLaunchKernelGGL((k_index_by_id<lanes.value>), dim3(grid_for(n_cells * G)), dim3(kBlock),
+                       0, s, cur, (uint32_t)n_cells, slot_of, binning_step);
+  });
+  hipLaunchKernelGGL(k_export_by_id, dim3(grid_for(n)), dim3(kBlock), 0, s, cur, n,
+                     (const uint32_t *)slot_of, x, y, z, px, py, pz);
 }
 
 }  // namespace cuba
