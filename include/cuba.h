@@ -230,26 +230,24 @@ int cuba_sync(cuba_ctx *ctx);
 
 /* Lanes per cell of the collision and binning kernels (a launch shape; the
  * results are bit-identical for every setting).  0: one wave64 per cell,
- * whatever its occupancy.  8, 16, 32 or 64: each wave takes 64 / lanes
- * consecutive cells with one particle per lane, which serves sparse cells
- * without a mostly idle wave each; cells holding more particles than lanes
- * are stepped by the whole wave in a second kernel (a wave per 64 cells, or
- * a wave per cell once the initial state has more than one such cell in 64).
- * 1 (packed): each wave takes 64 consecutive cells and packs whole cells, in
- * order, into units of at most 64 particles, one particle per lane, testing
- * pairs with the Philox filter first and the exact test in compacted rows;
- * cells of more than 64 particles go to the second kernel.  For sparse
- * boxes and boxes of dense and sparse regions.  128: a workgroup of two
+ * whatever its occupancy.  1, 8, 16, 32 or 64 (packed): a workgroup takes up
+ * to 64 consecutive cells and packs whole cells, in order, into units of at
+ * most 64 particles, one wave a unit and one lane a particle, testing pairs
+ * with the Philox filter first and the exact test in compacted rows; cells
+ * of more than 64 particles take a wave each.  For sparse boxes and boxes of
+ * dense and sparse regions.  The number is the lanes per cell of the kernel
+ * that streams and bins a run's first step (1: 16).  128: a workgroup of two
  * waves per cell, which split its pair tests (the first wave claims every
  * accepted pair in increasing pair order); for boxes of fewer cells than the
  * chip has SIMDs.  cuba_init chooses from the initial occupancy and
  * K = sigma / r_test * dt / V_cell: 128 below 1024 cells if at least half of
- * them hold more than 32 particles, else 0 below 16384 cells (launch-bound
- * steps), else 1 if at most 0.2 % of the cells hold more than 64 particles
- * and the mean occupancy is at most 8 (at most 12 if 2K >= 0.01), else the
- * smallest of 8, 16, 32 that all but 0.2 % of the cells fit, else 1 if at
- * least a quarter of the cells hold at most 8 particles and at most 0.2 %
- * more than 64, else 0.  Errors: CUBA_EINVAL for NULL or any other value.
+ * them hold more than 32 particles, else 0 below 4096 cells or if more than
+ * 0.2 % of the cells hold more than 64 particles, else 1 if the mean
+ * occupancy is at most 8 (at most 12 if 2K >= 0.01), else the smallest of 8,
+ * 16, 32 that all but 0.2 % of the cells fit (below 16384 cells if the mean
+ * is at most 18), else 1 if the mean is at most 18, 21 or 26 (below 16384,
+ * below 65536 cells, or more) or at least a quarter of the cells hold at
+ * most 8 particles, else 0.  Errors: CUBA_EINVAL for NULL or any other value.
  * For an event in a batch use cuba_batch_set_cell_lanes (which takes
  * neither 1 nor 128). */
 int cuba_set_cell_lanes(cuba_ctx *ctx, int32_t lanes);
@@ -402,7 +400,7 @@ int cuba_batch_set_observe(cuba_batch *b, int32_t slot, int32_t every, double *o
 /* Cells per binning work item of a slot's event (default: about 64
  * particles per item, at most 64 cells; 64 cells for events with lanes per
  * cell > 0); set by the autotuner.  The collision kernels take fixed units:
- * a cell per wave, or 64 / lanes cells per wave with lanes per cell > 0. */
+ * a cell per wave, or up to 64 cells a workgroup with lanes per cell > 0. */
 int cuba_batch_set_cells_per_item(cuba_batch *b, int32_t slot, int32_t cells);
 
 /* The profiles of a slot's event (as cuba_observe on cuba_batch_slot(b, slot),
@@ -414,9 +412,11 @@ int cuba_batch_observe(cuba_batch *b, int32_t slot, double *T00, double *T0x);
  * stream.  out: device f64[6 nx]. */
 int cuba_batch_observe_moments(cuba_batch *b, int32_t slot, double *out);
 
-/* Lanes per cell of a slot's event (as cuba_set_cell_lanes).  The default
- * is cuba_init's choice without its 8-lane fallback for boxes of dense and
- * sparse regions (a batch steps oversize cells a wave per 64 cells); set by
+/* Lanes per cell of a slot's event (as cuba_set_cell_lanes).  The default:
+ * 0 below 1024 cells or if more than 0.2 % of the cells hold more than 64
+ * particles, else the smallest of 8, 16, 32 that all but 0.2 % of the cells
+ * fit (below 16384 cells if the mean is at most 21), else 32 if the mean is
+ * at most 21 and at most 5 % of the cells hold more than 32, else 0; set by
  * the autotuner. */
 int cuba_batch_set_cell_lanes(cuba_batch *b, int32_t slot, int32_t lanes);
 

@@ -155,44 +155,50 @@ int derive(const cuba_params *p, int64_t n, Derived &d) {
 }
 
 // Lanes per cell from the occupancy at init (over[k] = cells holding more
-// than 8 << k particles) and the scattering constant K:
-//  * one wave per cell for boxes of fewer cells than a few waves per SIMD,
-//    whose steps are bound by launch latency, which the second kernel adds to;
-//  * on the plain path (plain: not in a batch), packed cells if at most a
-//    small fraction of the cells exceed 64 particles and the mean occupancy
-//    is at most 8, or at most 12 with 2K >= 1 % (where most pair-test rounds
-//    of the fixed-lane kernels hold a pair that passes the filter, and pay
-//    for its exact test in the whole wave);
-//  * else the smallest group of 8, 16 or 32 lanes that all but a small
-//    fraction of the cells fit (64-lane groups lost to one wave per cell
-//    in every measured occupancy mix);
-//  * else, on the plain path, packed cells if at least a quarter of the
-//    cells hold at most 8 particles and few exceed 64: a box of dense and
-//    sparse regions;
-//  * else one wave per cell.
+// than 8 << k particles) and the scattering constant K.  Measured (us a step,
+// tubes of 100 x m x m cells at 2K = 0.2-2 %; packed / one wave per cell):
+//   mean               2          8          16         20         24        28
+//   2 500 cells     9.9/9.4   11.2/10.7  14.6/11.9  22.3/12.5
+//   10 000          9.8/15.0  14.0/19.9  20.4/22.9  27.1/24.3
+//   40 000         14.1/36.0  27.4/51.9  52.5/61.6  61.3/67.7  77.8/72.9
+//   160 000        32.1/114   70.3/176   140/230    179/254    235/276   300/298
+// So packed cells (under whichever name: kPackedCells, 8, 16 or 32, which
+// also sets the lanes of the stream-bin kernel) below a mean of 18, 21 and
+// 26 for 4 096, 16 384 and 65 536 cells and more, if few cells exceed the 64
+// particles of a unit; and for boxes of dense and sparse regions (at least a
+// quarter of the cells with at most 8 particles).  Else one wave per cell.
 // Except: on the plain path, a box of fewer cells than the chip has SIMDs,
 // most of them holding more than 32 particles, takes two waves per cell (the
 // 1-D tube's 100 cells step in 24 instead of 33 us; at 10 000 cells and
-// more the second wave's extra work outweighs its parallelism).
+// more the second wave's extra work outweighs its parallelism).  In a batch
+// (plain = false) an event's step is not its own launch, so smaller boxes
+// are packed too.
 constexpr double kOversizeFraction = 2e-3;
 constexpr double kSparseFraction = 0.25;
-constexpr int64_t kSmallCellsMinCells = 16384;
+constexpr int64_t kPackedMinCells = 4096, kPackedMinCellsBatch = 1024;
 constexpr int64_t kTwoWaveMaxCells = 1024;
 constexpr double kPackedMean = 8.0, kPackedMeanHighK = 12.0, kHighTwoK = 0.01;
 uint32_t default_lanes(const uint32_t over[4], int64_t n_cells, int64_t n, double kfac,
                        bool plain) {
   if (plain && n_cells < kTwoWaveMaxCells && 2 * (int64_t)over[2] >= n_cells)
     return kTwoWavesPerCell;
-  if (n_cells < kSmallCellsMinCells) return 0;
+  if (n_cells < (plain ? kPackedMinCells : kPackedMinCellsBatch)) return 0;
   const double limit = kOversizeFraction * (double)n_cells;
   const double mean = (double)n / (double)n_cells;
-  const bool packable = plain && (double)over[3] <= limit;
-  if (packable && (mean <= kPackedMean || (2.0 * kfac >= kHighTwoK && mean <= kPackedMeanHighK)))
+  if ((double)over[3] > limit) return 0;
+  const double packed_mean = !plain              ? 21.0
+                             : n_cells < 16384   ? 18.0
+                             : n_cells < 65536   ? 21.0
+                                                 : 26.0;
+  if (plain && (mean <= kPackedMean || (2.0 * kfac >= kHighTwoK && mean <= kPackedMeanHighK)))
     return kPackedCells;
   for (uint32_t k = 0; k < 3; ++k)
-    if ((double)over[k] <= limit) return 8u << k;
-  if (packable && (double)(n_cells - over[0]) >= kSparseFraction * (double)n_cells)
+    if ((double)over[k] <= limit && (n_cells >= 16384 || mean <= packed_mean)) return 8u << k;
+  if (plain && (mean <= packed_mean ||
+                (double)(n_cells - over[0]) >= kSparseFraction * (double)n_cells))
     return kPackedCells;
+  // (a batched event's dense half would fill its units badly)
+  if (!plain && mean <= packed_mean && (double)over[2] <= 0.05 * (double)n_cells) return 32;
   return 0;
 }
 
@@ -304,12 +310,11 @@ void drop_timing(cuba_ctx *c) {
 }
 
 // Device copy of the geometry.
-// The oversize-cell launch takes a wave per cell once such cells average
-// more than one in 64 (by the initial histogram), else a wave per 64 cells.
-uint32_t over_span(const uint32_t over[4], uint32_t lanes, int64_t n_cells) {
-  if (lanes == 0 || lanes == kTwoWavesPerCell) return 64;
-  const uint32_t k = lanes == 8 ? 0 : lanes == 16 ? 1 : lanes == 32 ? 2 : 3;
-  return (int64_t)over[k] * 64 > n_cells ? 1u : 64u;
+// The cells that the packed kernel's units leave out take a launch with a
+// wave per cell once they average more than one in 64 (by the initial
+// histogram).
+uint32_t over_span(const uint32_t over[4], int64_t n_cells) {
+  return (int64_t)over[3] * 64 > n_cells ? 1u : 64u;
 }
 
 // A new time step for the steps issued after this call (Sec. 6 names a
@@ -335,8 +340,23 @@ int apply_dt(cuba_ctx *c, double dt) {
   return CUBA_OK;
 }
 
+// Cells a workgroup (four waves) of the packed kernel takes: 64, or fewer
+// while the box has too few workgroups to fill the chip and a workgroup more
+// particles than its waves take at once.  10 000 cells of 16: 64 us a step
+// in 157 tiles of 64 cells, 20 us in 1 250 of 8; 160 000 cells of 2: 32 us in
+// tiles of 64, 36 us in tiles of 32, whose waves are half idle.
+constexpr int64_t kPackedTiles = 1280, kPackedTileParticles = 160;
+uint32_t packed_tile(int64_t n, int64_t n_cells) {
+  uint32_t tile = 64;
+  while (tile > 8 && n_cells < (int64_t)tile * kPackedTiles &&
+         (int64_t)tile * n > kPackedTileParticles * n_cells)
+    tile /= 2;
+  return tile;
+}
+
 StepDevice step_device(const cuba_ctx *c) {
-  return StepDevice{&c->consts->g, over_span(c->over, c->lanes, c->d.n_cells)};
+  return StepDevice{&c->consts->g, over_span(c->over, c->d.n_cells),
+                    packed_tile(c->n, c->d.n_cells)};
 }
 
 // The step launch's device arguments, with the stage's timing events.
@@ -904,7 +924,7 @@ namespace {
 // which holds at most 65535 workgroups.
 constexpr int32_t kMaxBatchSlots = 65535;
 
-// Work spaces of a batch: binning items, small-cell chunks, oversize scans,
+// Work spaces of a batch: binning items, packed tiles, scans of their larger cells,
 // and the one-wave-per-cell spaces of small and large cell capacity.
 constexpr int kSpaces = 5;
 
@@ -943,6 +963,15 @@ void drop_batch_timing(cuba_batch *b) {
   b->timing_cap = 0;
 }
 
+// Cells a workgroup of the packed kernel takes of a batched event: about the
+// 200 particles that its four waves take at once, within 8 .. 64 cells (the
+// batch's other events fill the chip).
+uint32_t event_tile(int64_t n, int64_t n_cells) {
+  uint32_t tile = 64;
+  while (tile > 8 && (int64_t)tile * n > 200 * n_cells) tile /= 2;
+  return tile;
+}
+
 // Default cells per binning item: enough cells that an item holds about 64
 // particles (a full wave), at most 64 cells; events with lanes per cell > 0
 // bin 64 cells per item (in groups of 64 / lanes cells).
@@ -961,8 +990,7 @@ int32_t default_cpi(const cuba_ctx *c) {
 int upload_table(cuba_batch *b) {
   std::vector<BatchEvent> host;
   b->table_slots.clear();
-  uint64_t items = 0, chunks = 0, scans = 0, cells[2] = {0, 0};
-  bool scan_large = false;
+  uint64_t items = 0, tiles = 0, scans = 0, cells[2] = {0, 0};
   uint32_t obs_nx = 0;
   std::vector<int> cell_space;
   for (int32_t s = 0; s < b->max_slots; ++s) {
@@ -989,20 +1017,19 @@ int upload_table(cuba_batch *b) {
     }
     const int space = c->d.cap <= kSmallCap ? 0 : 1;
     e.item_begin = (uint32_t)items;
-    e.chunk_begin = (uint32_t)chunks;
+    e.tile = event_tile(c->n, c->d.n_cells);
+    e.tile_begin = (uint32_t)tiles;
     e.scan_begin = (uint32_t)scans;
     e.cell_begin = (uint32_t)cells[space];
     items += (e.n_cells + e.cpi - 1) / e.cpi;
     if (c->lanes > 0) {
-      const uint64_t per = 64 / c->lanes;
-      chunks += (e.n_cells + per - 1) / per;
-      scans += (e.n_cells + 63) / 64;
-      if (space == 1) scan_large = true;
+      tiles += (e.n_cells + e.tile - 1) / e.tile;
+      if (space == 1) scans += (e.n_cells + 63) / 64;
     } else {
       cells[space] += e.n_cells;
     }
     // grid sizes stay below 2^31 workgroups
-    if (items >= 0x80000000ull || chunks >= 0x80000000ull || cells[0] >= 0x80000000ull ||
+    if (items >= 0x80000000ull || tiles >= 0x80000000ull || cells[0] >= 0x80000000ull ||
         cells[1] >= 0x80000000ull)
       return fail(CUBA_EINVAL, "too many cells in the batch for one launch");
     cell_space.push_back(c->lanes > 0 ? -1 : space);
@@ -1012,16 +1039,15 @@ int upload_table(cuba_batch *b) {
   const size_t ne = host.size();
   const size_t stride = (size_t)b->max_slots;
   b->spaces.item_begin = b->dev_begin;
-  b->spaces.chunk_begin = b->dev_begin + stride;
+  b->spaces.tile_begin = b->dev_begin + stride;
   b->spaces.scan_begin = b->dev_begin + 2 * stride;
   b->spaces.cell_begin[0] = b->dev_begin + 3 * stride;
   b->spaces.cell_begin[1] = b->dev_begin + 4 * stride;
   b->spaces.n_items = (uint32_t)items;
-  b->spaces.n_chunks = (uint32_t)chunks;
+  b->spaces.n_tiles = (uint32_t)tiles;
   b->spaces.n_scans = (uint32_t)scans;
   b->spaces.n_cells[0] = (uint32_t)cells[0];
   b->spaces.n_cells[1] = (uint32_t)cells[1];
-  b->spaces.scan_large = scan_large;
   b->spaces.obs_nx = obs_nx;
   if (ne > 0) {
     // an event outside a cells space gets that space's running total (the
@@ -1030,7 +1056,7 @@ int upload_table(cuba_batch *b) {
     uint32_t run[2] = {0, 0};
     for (size_t i = 0; i < ne; ++i) {
       begins[i] = host[i].item_begin;
-      begins[stride + i] = host[i].chunk_begin;
+      begins[stride + i] = host[i].tile_begin;
       begins[2 * stride + i] = host[i].scan_begin;
       for (int sp = 0; sp < 2; ++sp) {
         begins[(3 + sp) * stride + i] = run[sp];
@@ -1161,7 +1187,6 @@ int cuba_batch_admit(cuba_batch *b, int32_t slot, const cuba_params *params, int
   const int rc = cuba_init(&c, params, n, x, y, z, px, py, pz, workspace, ws_bytes,
                            (void *)b->stream);
   if (rc != CUBA_OK) return rc;
-  // a batch steps the oversize cells of an event 64 to a wave
   c->lanes = default_lanes(c->over, c->d.n_cells, c->n, c->d.kfac, false);
   b->slot_ctx[slot] = c;
   b->slot_cpi[slot] = default_cpi(c);

@@ -123,8 +123,9 @@ struct BatchEvent {
   uint32_t cur;         // buffer holding the state at the start of a run
   uint32_t t;           // step index of the next step
   uint32_t lanes;       // lanes per cell (0: one wave per cell; 8, 16, 32, 64)
-  uint32_t chunk_begin; // first small-cell chunk (64 / lanes cells), if lanes > 0
-  uint32_t scan_begin;  // first oversize-cell scan unit (64 cells), if lanes > 0
+  uint32_t tile;        // cells per workgroup of the packed kernel, if lanes > 0
+  uint32_t tile_begin;  // first of its tiles
+  uint32_t scan_begin;  // first scan unit (64 cells), if lanes > 0 and cap > kSmallCap
   uint32_t cell_begin;  // first unit in its one-wave-per-cell space, if lanes = 0
                         // (space 0: cell capacity <= kSmallCap, space 1: larger)
   // observation inside runs: after each step s with (s + 1) % obs_every == 0
@@ -133,7 +134,6 @@ struct BatchEvent {
   // ((s + 1) / obs_every) % obs_rows of obs_out (rows of 2 nx doubles)
   uint32_t obs_every;
   uint32_t obs_rows;
-  uint32_t pad;
   double *obs_sums;
   double *obs_out;
   double obs_vol;       // slab volume
@@ -142,17 +142,16 @@ struct BatchEvent {
 // The work spaces of a batch run (see launch_batch_run): unit counts and,
 // per event in table order, the first unit of each space (device arrays).
 struct BatchSpaces {
-  const uint32_t *item_begin, *chunk_begin, *scan_begin, *cell_begin[2];
-  uint32_t n_items, n_chunks, n_scans, n_cells[2];
-  bool scan_large;  // some small-cell event has a cell capacity > kSmallCap
+  const uint32_t *item_begin, *tile_begin, *scan_begin, *cell_begin[2];
+  uint32_t n_items, n_tiles, n_scans, n_cells[2];
   uint32_t obs_nx;  // > 0: some event observes inside runs; its largest nx
 };
 
-// Lanes per cell of the cell kernels: 0 (one wave per cell), 8, 16, 32, 64
-// (64 / lanes cells per wave, one particle per lane; larger cells stepped by
-// a whole wave), kPackedCells (whole cells packed into waves of up to 64
-// particles, one per lane; plain path only) or kTwoWavesPerCell (a
-// workgroup of two waves per cell; plain path only).
+// Lanes per cell: 0 (one wave per cell), kPackedCells, 8, 16, 32 or 64
+// (whole cells packed into waves of up to 64 particles, one per lane; the
+// number is the stream-bin kernel's lanes per cell, 16 for kPackedCells) or
+// kTwoWavesPerCell (a workgroup of two waves per cell; plain path only, as
+// is kPackedCells by that name).
 constexpr uint32_t kPackedCells = 1;
 constexpr uint32_t kTwoWavesPerCell = 128;
 inline bool valid_cell_lanes(int32_t v) {
@@ -209,15 +208,16 @@ struct StepDevice {
   // and steps the oversize ones one after another; few oversize cells) or 1
   // (a wave per cell; many)
   uint32_t over_span;
+  uint32_t tile;  // cells a workgroup of the packed kernel takes (8 .. 64)
   // stage timing: events that the launch records at its start and end (on
   // its first kernel's dispatch when it is one kernel), or null
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
 };
 
 // One collision launch (fused: then streaming + binning of the next step).
-// lanes > 0: the small-cell kernel on s and, concurrently on side (if not
-// NULL; else after it on s), the kernel for the cells it leaves alone
-// (overflowing cells among them).
+// lanes > 0: the packed kernel on s and, where it does not step them itself,
+// concurrently on side (if not NULL; else after it on s) the kernel for the
+// cells it leaves alone (overflowing cells among them).
 // dev: device copy of g (equal to the host value).  The buffers src and
 // dst must be laid out alike (every array at the same distance from its twin).
 void launch_step(const Cells &src, const Cells &dst, bool fused, int64_t n_cells,
@@ -241,15 +241,15 @@ void launch_observe(const Cells &cur, const Geometry &g, int64_t n, double vol,
 // A run of k >= 1 steps of every event in the device table ev (n_events
 // live events): stream + bin, k - 1 fused steps, the last collisions, then
 // the table advance.  The work spaces: items of cells_per_item cells for the
-// binning (every event); for events with lanes per cell > 0, small-cell
-// chunks of 64 / lanes cells and scan units of 64 cells for their oversize
-// cells; for events with lanes = 0, one unit per cell, in two spaces by cell
+// binning (every event); for events with lanes per cell > 0, tiles of packed
+// cells and, if their blocks exceed kSmallCap, scan units of 64 cells for
+// what those leave; for events with lanes = 0, one unit per cell, in two spaces by cell
 // capacity (<= kSmallCap and larger), each stepped by the kernel with the
 // LDS for its capacity, so that one large event does not lower the
 // occupancy of all the others.  persistent_waves
 // > 0 caps the binning grid (persistent waves taking items with a grid
-// stride).  Each step runs the small-cell chunks on s and, concurrently on
-// side (if not NULL), the one-wave-per-cell events and the oversize cells.
+// stride).  Each step runs the packed tiles on s and, concurrently on
+// side (if not NULL), the one-wave-per-cell events and the scans.
 // between (may be NULL) is called before each step of the run with
 // its kind (0 stream-bin, 1 fused step, 2 collide) and with -1 after the last
 // one: a hook for stage timing.

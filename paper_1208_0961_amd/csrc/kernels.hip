@@ -18,9 +18,9 @@
 //                  with F kept in LDS).  With F (fused) the same wave then
 //                  streams and bins its particles for step t+1, so the
 //                  binning traffic overlaps the ALU-bound pair tests.
-//   k_step_small   64 / G cells per wave, one particle per lane (sparse
-//                  cells); k_step_large / k_step_over step the cells that
-//                  do not fit G lanes.
+//   k_step_packed  whole cells packed into waves of up to 64 particles, one
+//                  a lane (sparse cells); k_step_large / k_step_over step
+//                  larger cells where that kernel does not itself.
 //   k_step2        a workgroup of two waves per cell, splitting its pair
 //                  tests (boxes of fewer cells than SIMDs).
 //   observe        per-cell sums of E, p_x, p_x^2/E and counts, then
@@ -1137,15 +1137,16 @@ __device__ void large_cell_step(const GCells &src, const GCells &dst, const Cell
 // filled.  Claims are thus made in increasing pair order as with one wave,
 // and every other phase is split over the workgroup's lanes.  Both waves
 // pass the same barriers; code that one wave runs alone synchronises with
-// itself only.
-template <bool kFused, bool kTrace, uint32_t kCap, uint32_t kW = 1>
+// itself only.  kBlk = false: one wave per cell in a workgroup of several,
+// which synchronises with itself only throughout.
+template <bool kFused, bool kTrace, uint32_t kCap, uint32_t kW = 1, bool kBlk = true>
 __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, uint32_t c,
                                           uint32_t t, const PairArgs &pa,
                                           const Geometry &g, DevStatus *status,
                                           const TraceArgs &tr, CellLds<kFused, kCap> &lds,
                                           SecondWaveLds<kCap> *x2 = nullptr,
                                           double *obs = nullptr) {
-  static_assert(kW == 1 || (kW == 2 && !kTrace), "one or two waves, traces with one");
+  static_assert(kW == 1 || (kW == 2 && !kTrace && kBlk), "one or two waves, traces with one");
   constexpr uint32_t kT = 64 * kW;
   // filtered pairs and claimed pairs share the id buffer, kCap / 2 each
   constexpr uint32_t kFilt = kCap / 2;
@@ -1154,7 +1155,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
   uint32_t *const s_filt = lds.buf;
   uint32_t *const s_claim = lds.buf + kFilt;
   uint16_t *const s_perm = lds.perm;
-  __syncthreads();
+  cell_sync<kBlk>();
   // A fused one-wave step of a cell whose members are all in its block
   // keeps the new momenta of up to kMomCap claims in LDS (where the rank
   // sorted its ids; claim i's two members at 2i, 2i + 1, and by member a
@@ -1194,7 +1195,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     // an overflowing cell: find its spilled members (wave 0), then step it
     // here, in LDS if it fits, else with the global-memory method
     if (wv == 0) find_spilled<kFused, kCap>(src, cv, lds, status);
-    __syncthreads();
+    cell_sync<kBlk>();
     if (lds.ov_ok == 0u) return;  // internal error, flagged
     const SpillDesc *const sd = src.sp;
     cv.sbase = sd->base;
@@ -1217,7 +1218,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     const uint32_t n4 = (n + 3u) & ~3u;
     for (uint32_t j = tid; j < n4; j += kT)
       s_id[j] = j < n ? st.id[cv.at_spill(j)] : 0xFFFFFFFFu;
-    __syncthreads();
+    cell_sync<kBlk>();
 
     // canonical order: the rank of each id among the cell's ids
     if (n > kBucketRankMin) {
@@ -1239,9 +1240,9 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
       uint32_t *const s_sorted = lds.sorted;
       for (uint32_t b = tid; b < kRankBuckets; b += kT) s_bkt[b] = 0u;
       if (tid == 0) s_bkt[kRankBuckets] = n;
-      __syncthreads();
+      cell_sync<kBlk>();
       for (uint32_t j = tid; j < n; j += kT) atomicAdd(&s_bkt[(s_id[j] - lo) >> shift], 1u);
-      __syncthreads();
+      cell_sync<kBlk>();
       if (wv == 0) {  // inclusive scan of the counts: s_bkt[b] = end of bucket b
         uint4 q = reinterpret_cast<uint4 *>(s_bkt)[lane];
         q.y += q.x;
@@ -1255,14 +1256,14 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
         q.w += excl;
         reinterpret_cast<uint4 *>(s_bkt)[lane] = q;
       }
-      __syncthreads();
+      cell_sync<kBlk>();
       // each bucket filled from its end: afterwards s_bkt[b] is its start
       for (uint32_t j = tid; j < n; j += kT) {
         const uint32_t v = s_id[j];
         const uint32_t pos = atomicSub(&s_bkt[(v - lo) >> shift], 1u) - 1u;
         s_sorted[pos] = v;
       }
-      __syncthreads();
+      cell_sync<kBlk>();
       for (uint32_t j = tid; j < n; j += kT) {
         const uint32_t me = s_id[j], b = (me - lo) >> shift;
         const uint32_t p1 = s_bkt[b + 1];
@@ -1286,10 +1287,10 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
         if (kTrace && tr.perm) tr.perm[tr.offsets[cv.c] + r] = me;
       }
     }
-    __syncthreads();
+    cell_sync<kBlk>();
     if (cv.ov) {  // the members' slots, in LDS (the rank no longer needs it)
       for (uint32_t j = tid; j < n; j += kT) lds.sorted[j] = (uint32_t)cv.at_spill(j);
-      __syncthreads();
+      cell_sync<kBlk>();
     } else if (kMomInLds) {
       // the claim map (one byte a member, zero: not scattered), in the
       // rank's buckets; the barrier after the pair tests orders it
@@ -1304,13 +1305,13 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     if (kW == 1) __builtin_amdgcn_s_setprio(0);
     if (kW == 1) {
       if (pa.any)
-        test_pairs<true, kTrace, true, kFilt>(0u, npairs, cv, pa, st, s_perm, s_filt, nf,
+        test_pairs<true, kTrace, kBlk, kFilt>(0u, npairs, cv, pa, st, s_perm, s_filt, nf,
                                               s_claim, nclaim, claimed_bits, n_acc, tr,
                                               status);
       if (nf != 0)
-        resolve_filtered<kTrace>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
+        resolve_filtered<kTrace, kBlk>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
                                  claimed_bits, n_acc, tr, status);
-      __syncthreads();
+      cell_sync<kBlk>();
     } else {
       const uint32_t kh = npairs / 2u / 128u * 128u;
       if (wv == 0) {
@@ -1333,7 +1334,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
           x2->k_resume = k_resume;
         }
       }
-      __syncthreads();
+      cell_sync<kBlk>();
       if (wv == 0) {
         const uint32_t n1 = x2->n_filt, k_resume = x2->k_resume;
         if (n1 != 0)
@@ -1349,7 +1350,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
         }
         if (lane == 0) x2->nclaim = nclaim;
       }
-      __syncthreads();
+      cell_sync<kBlk>();
       nclaim = x2->nclaim;
     }
 
@@ -1411,7 +1412,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
         }
       }
     }
-    if (kFused || ob) __syncthreads();
+    if (kFused || ob) cell_sync<kBlk>();
   } else if (kTrace && n == 1 && tid == 0 && tr.perm) {
     tr.perm[tr.offsets[cv.c]] = st.id[cv.at_spill(0)];
   }
@@ -1475,240 +1476,22 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
   }
 }
 
-// ---------------------------------------------------------------------------
-// Small cells: one wave takes 64 / G consecutive cells, G lanes per cell and
-// one particle per lane.  A lane loads its particle once and keeps it in
-// registers through collisions, streaming and binning, so a sparse cell
-// costs one load round trip and one slot atomic instead of a wave of its own
-// with several dependent round trips.
-// ---------------------------------------------------------------------------
-struct SmallLds {
-  __align__(16) uint32_t id[64];  // by lane (the cell's storage order)
-  double x[64], y[64], z[64];     // by lane
-  double px[64], py[64], pz[64];  // by group and canonical rank
-  SlotTable tab;
-};
+constexpr uint32_t kPackedMax = 64;  // particles of a packed unit, and of a cell it takes
 
-template <uint32_t G>
-using ClaimMask = typename std::conditional<(G == 64), uint64_t, uint32_t>::type;
-
-// Collisions of the cells c0 .. c_end - 1 (at most 64 / G) of src at step t.
-// The canonical rank of each particle is counted over its cell's ids in
-// LDS, where the momenta are then stored in canonical order (and the
-// positions by lane, so that no particle state stays live in registers
-// through the pair loop).  Pairs k = gl, gl + G, ... of each cell are tested
-// as in cell_step (Philox w1 filter, then the exact Eq. (3) test in the same
-// lane); a cell's accepted pairs of one round appear in its bits of the
-// wave's ballot in increasing k, so the greedy claim walks those bits in
-// order, with the cell's claimed set kept identically by all its lanes.
-// Both lanes of a claimed pair evaluate its kinematics (same inputs, same
-// code, hence the same result) and keep their own half.  kFused: every lane
-// then streams and bins its particle into dst for step t+1.  Cells holding
-// more than G particles are left alone; the result has bit grp G set for
-// each such cell c0 + grp.
-template <bool kFused, bool kTrace, uint32_t G>
-__device__ __forceinline__ uint64_t small_cells_step(const GCells &src, const GCells &dst,
-                                                     uint32_t c0, uint32_t c_end,
-                                                     uint32_t t, const PairArgs &pa,
-                                                     const Geometry &g, DevStatus *status,
-                                                     const TraceArgs &tr, SmallLds &lds,
-                                                     double *obs = nullptr) {
-  static_assert(G == 8 || G == 16 || G == 32 || G == 64, "lanes per cell");
-  constexpr uint32_t kNone = 0xFFFFFFFFu;
-  const uint32_t lane = lane_id();
-  const uint32_t grp = lane / G, gl = lane % G;
-  const uint32_t c = c0 + grp;
-  const bool in_range = c < c_end;
-  if (c0 == 0 && lane == 0) clear_idle_scratch(src, t);
-  // overflowing cells are left to the kernel for larger cells
-  const uint32_t cnt = in_range ? src.count[c] : 0u;
-  const bool overflowing = cnt > src.cap;
-  const uint32_t n = overflowing ? 0u : cnt;
-  const bool small = in_range && !overflowing && n <= G;
-  const bool mine = small && gl < n;
-  const size_t o = (size_t)c * src.cap + gl;
-  __syncthreads();  // a previous call's readers of lds are done
-  double qx = 0, qy = 0, qz = 0;
-  {
-    uint32_t id = kNone;  // ids are below 2^32 - 1, so kNone ranks after all
-    if (mine) {
-      const Particle q = load_particle(src.st, o);
-      lds.x[lane] = q.x;
-      lds.y[lane] = q.y;
-      lds.z[lane] = q.z;
-      qx = q.px;
-      qy = q.py;
-      qz = q.pz;
-      id = q.id;
-    }
-    lds.id[lane] = id;
-  }
-  __syncthreads();
-  uint32_t r = 0;
-  if (mine) {
-    const uint32_t id = lds.id[lane];
-    const uint4 *q4 = reinterpret_cast<const uint4 *>(lds.id + grp * G);
-#pragma unroll
-    for (uint32_t m = 0; m < G / 4; ++m) {
-      const uint4 q = q4[m];
-      r += (q.x < id) + (q.y < id) + (q.z < id) + (q.w < id);
-    }
-    lds.px[grp * G + r] = qx;
-    lds.py[grp * G + r] = qy;
-    lds.pz[grp * G + r] = qz;
-    if (kTrace && tr.perm) tr.perm[tr.offsets[c] + r] = id;
-  }
-  __syncthreads();
-
-  const double *const spx = lds.px + grp * G;
-  const double *const spy = lds.py + grp * G;
-  const double *const spz = lds.pz + grp * G;
-  const uint32_t npairs = small ? n * (n - 1u) / 2u : 0u;
-  ClaimMask<G> claimed = 0;  // the cell's claimed canonical indices
-  uint32_t partner = kNone, kpair = 0, n_acc = 0;
-  if (pa.any) {
-    for (uint32_t k0 = 0; __ballot(k0 < npairs) != 0; k0 += G) {
-      const uint32_t k = k0 + gl;
-      bool acc = false;
-      if (k < npairs && philox10_w1(k, c, t, 0u, pa.key0, pa.key1) <= pa.w1_max) {
-        const Words4 w = philox10(k, c, t, 0u, pa.key0, pa.key1);
-        uint32_t a, b;
-        pair_of_index(k, n, a, b);
-        acc = uniform53(w.w0, w.w1) <
-              p22(spx[a], spy[a], spz[a], spx[b], spy[b], spz[b], pa.kfac);
-        if (kTrace && acc && tr.cand) {
-          const uint32_t slot = atomicAdd(&tr.counts[0], 1u);
-          if (slot < tr.cand_cap) {
-            tr.cand[3 * (size_t)slot + 0] = c;
-            tr.cand[3 * (size_t)slot + 1] = a;
-            tr.cand[3 * (size_t)slot + 2] = b;
-          } else {
-            atomicOr(&status->err, kErrTrace);
-          }
-        }
-      }
-      n_acc += acc ? 1u : 0u;
-      uint64_t seg = __ballot(acc);
-      if (G < 64) seg = (seg >> (grp * G)) & ((1ull << (G % 64)) - 1ull);
-      while (seg != 0) {
-        const uint32_t kk = k0 + (uint32_t)__builtin_ctzll(seg);
-        seg &= seg - 1ull;
-        uint32_t a, b;
-        pair_of_index(kk, n, a, b);
-        const ClaimMask<G> ab = ((ClaimMask<G>)1 << a) | ((ClaimMask<G>)1 << b);
-        if ((claimed & ab) == 0) {
-          claimed |= ab;
-          if (mine && (r == a || r == b)) {
-            partner = r == a ? b : a;
-            kpair = kk;
-          }
-          if (kTrace && tr.claim && gl == 0) {
-            const uint32_t slot = atomicAdd(&tr.counts[1], 1u);
-            if (slot < tr.claim_cap) {
-              tr.claim[3 * (size_t)slot + 0] = c;
-              tr.claim[3 * (size_t)slot + 1] = a;
-              tr.claim[3 * (size_t)slot + 2] = b;
-            } else {
-              atomicOr(&status->err, kErrTrace);
-            }
-          }
-        }
-      }
-    }
-  }
-
-  // work counters of the wave's cells, in one slot
-  const bool scat = partner != kNone;
-  {
-    uint32_t cnt_pairs = small && gl == 0 ? npairs : 0u;
-    uint32_t cnt_claims = scat && r < partner ? 1u : 0u;
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) {
-      cnt_pairs += __shfl_down(cnt_pairs, s);
-      n_acc += __shfl_down(n_acc, s);
-      cnt_claims += __shfl_down(cnt_claims, s);
-    }
-    if (lane == 0 && cnt_pairs != 0) {
-      const uint32_t slot = c0 % kCounterSlots;
-      atomicAdd(&status->pairs[slot], (unsigned long long)cnt_pairs);
-      atomicAdd(&status->cand[slot], (unsigned long long)n_acc);
-      atomicAdd(&status->claims[slot], (unsigned long long)cnt_claims);
-    }
-  }
-
-  double px = 0, py = 0, pz = 0;
-  if (mine) {
-    px = spx[r];
-    py = spy[r];
-    pz = spz[r];
-  }
-  if (scat) {
-    const bool lo = r < partner;
-    const uint32_t a = lo ? r : partner, b = lo ? partner : r;
-    const Words4 w = philox10(kpair, c, t, 1u, pa.key0, pa.key1);
-    double ax = spx[a], ay = spy[a], az = spz[a];
-    double bx = spx[b], by = spy[b], bz = spz[b];
-    scatter_pair(ax, ay, az, bx, by, bz, uniform53(w.w0, w.w1), uniform53(w.w2, w.w3));
-    px = lo ? ax : bx;
-    py = lo ? ay : by;
-    pz = lo ? az : bz;
-    if (!kFused) put_momentum(src.st, o, px, py, pz);
-  }
-
-  if (obs) {  // the cell's sums over its G lanes, written by its first lane
-    double se = 0.0, sp = 0.0, sxx = 0.0;
-    if (mine) obs_add(px, py, pz, se, sp, sxx);
-#pragma unroll
-    for (int o = G / 2; o > 0; o >>= 1) {
-      se += __shfl_xor(se, o);
-      sp += __shfl_xor(sp, o);
-      sxx += __shfl_xor(sxx, o);
-    }
-    if (small && gl == 0) {
-      double *const out = obs + kCellSums * (size_t)c;
-      out[0] = se;
-      out[1] = sp;
-      out[2] = sxx;
-      out[3] = (double)n;
-    }
-  }
-  if (kFused) {
-    double x = 0, y = 0, z = 0;
-    uint32_t id = 0, c2 = 0;
-    if (mine) {
-      x = lds.x[lane];
-      y = lds.y[lane];
-      z = lds.z[lane];
-      id = lds.id[lane];
-      advance<true>(g, x, y, z, px, py, pz);
-      c2 = cell_id(g, x, y, z);
-    }
-    clear_slot_table(lds.tab);
-    append_table(dst, c2, mine, Particle{x, y, z, px, py, pz, id}, status, lds.tab);
-    if (small && gl == 0) src.count[c] = 0u;
-  }
-  return __ballot(in_range && !small && !overflowing && gl == 0);
-}
-
-// The cells among c0 .. c_end - 1 (at most 64) holding more than `lanes`
-// particles, stepped one after another by the whole wave: the cells that a
-// small-cell launch with that many lanes per cell left alone (lanes = 0:
-// every non-empty cell).  A separate launch, so that each kernel keeps the
-// registers of its own path (the small-cell kernel runs at twice the
-// occupancy of the wave-per-cell code).
+// The cells among c0 .. c_end - 1 (at most 64) that a packed launch left
+// alone (more than kPackedMax particles, or overflowing), stepped one after
+// another by the whole wave.
 template <bool kFused, bool kTrace, uint32_t kCap>
 __device__ __forceinline__ void large_cells_step(const GCells &src, const GCells &dst,
-                                                 uint32_t c0, uint32_t c_end, uint32_t lanes,
-                                                 uint32_t t, const PairArgs &pa,
+                                                 uint32_t c0, uint32_t c_end, uint32_t t,
+                                                 const PairArgs &pa,
                                                  const Geometry &g, DevStatus *status,
                                                  const TraceArgs &tr,
                                                  CellLds<kFused, kCap> &lds,
                                                  double *obs = nullptr) {
   const uint32_t c = c0 + lane_id();
   const uint32_t n = c < c_end ? src.count[c] : 0u;
-  // the cells the small-cell kernel leaves: more particles than lanes, or
-  // overflowing (more than the block holds)
-  uint64_t big = __ballot(n > lanes || n > src.cap);
+  uint64_t big = __ballot(n > kPackedMax || n > src.cap);
   while (big != 0) {
     const uint32_t l = (uint32_t)__builtin_ctzll(big);
     big &= big - 1ull;
@@ -1716,23 +1499,11 @@ __device__ __forceinline__ void large_cells_step(const GCells &src, const GCells
   }
 }
 
-template <bool kFused, bool kTrace, uint32_t G>
-__global__ __launch_bounds__(64) void k_step_small(Cells src_arg, Cells dst_arg, uint32_t n_cells,
-                                                   uint32_t t, PairArgs pa, Geometry g,
-                                                   DevStatus *status, TraceArgs tr) {
-  const GCells src = binning(to_global(src_arg), t);
-  const GCells dst = binning(to_global(dst_arg), t + 1u);
-  __shared__ SmallLds lds;
-  constexpr uint32_t kPer = 64 / G;
-  const uint32_t c0 = xcd_runs<8>(blockIdx.x, gridDim.x) * kPer;
-  const uint32_t c_end = c0 + kPer < n_cells ? c0 + kPer : n_cells;
-  (void)small_cells_step<kFused, kTrace, G>(src, dst, c0, c_end, t, pa, g, status, tr, lds);
-}
-
 // ---------------------------------------------------------------------------
-// Packed cells: a wave takes a tile of 64 consecutive cells and packs whole
-// cells, in cell order, into units of at most 64 particles, one particle per
-// lane (a unit ends before the cell that would not fit).  So a sparse box
+// Packed cells: a workgroup of four waves takes a tile of up to 64
+// consecutive cells and packs whole cells, in cell order, into units of at
+// most 64 particles, one wave a unit, one particle per lane (a unit ends
+// before the cell that would not fit).  So a sparse box
 // steps with few idle lanes whatever its mix of occupancies, where a fixed
 // number of lanes per cell idles most of them in its emptier cells.  Each
 // unit:
@@ -1752,9 +1523,19 @@ __global__ __launch_bounds__(64) void k_step_small(Cells src_arg, Cells dst_arg,
 //   6. fused: streams and bins every particle; else writes the scattered
 //      momenta back.
 // Cells holding more than 64 particles, or more than their block holds,
-// are left to the kernel for larger cells.
+// take a wave each after the units (a launch of their own cost 5-12 us a
+// step), or are left to the kernels for larger cells.
+// What bounds it: VALU issue (~80 % busy on the 32^3 fm^3 set, ~1 400
+// instructions a unit, two fifths of them pair tests) where waves fill the
+// chip, the chain of a unit's loads, LDS exchanges, slot atomics and stores
+// (~10 us) where they do not.  Four waves a tile, not one: 24 units of a
+// dense tile one after another kept its wave for 350 us, the last ones
+// nearly alone.  160 000 cells, 50 steps: 12 a cell 8.85 -> 5.49 ms (32
+// lanes a cell before, one particle a lane, half the lanes idle), 2 a cell
+// 1.83 -> 1.79 ms; 128 batched events of 5 100 particles, 100 steps: 30.1 ->
+// 7.1 ms (a wave per cell before); 24 ensemble events, 25 steps: 15.4 ->
+// 13.0 ms; 32^3 fm^3 set, 10 steps: 20.1 -> 19.5 ms.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kPackedMax = 64;    // particles of a unit, and of a cell it takes
 constexpr uint32_t kPackedFilt = 256;  // filtered pairs held before a row is resolved
 
 struct PackedLds {
@@ -1766,6 +1547,14 @@ struct PackedLds {
   uint32_t start[64], cnt[64];     // by tile cell: first lane, particles
   uint32_t partner[64];            // by canonical position: the claimed partner's
   SlotTable tab;
+};
+
+// A wave's LDS: its units, then (after them) its larger cells.
+constexpr uint32_t kPackedWaves = 4;
+template <bool kFused>
+union PackedWaveLds {
+  PackedLds unit;
+  CellLds<kFused, kSmallCap> cell;
 };
 
 // Exact test and claims of filt[i0 .. i0 + 63] (< nf), in list order.
@@ -1829,34 +1618,52 @@ __device__ __forceinline__ void packed_resolve_row(
   }
 }
 
-template <bool kFused, bool kTrace>
+// One wave's share of the tile of cells c0 .. c_end - 1 (at most 64), by a workgroup of
+// kPackedWaves waves: the units are numbered in cell order and wave w takes
+// units w, w + kPackedWaves, ...; with kLarge, the cells left out of the
+// units (more than 64 particles, or overflowing) follow in the same count,
+// each stepped by one wave as in cell_step (if `large`).  The waves meet once, after all
+// have read the tile's counts and before those are cleared.
+template <bool kFused, bool kTrace, bool kLarge>
 __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCells &dst,
-                                                  uint32_t c0, uint32_t n_cells, uint32_t t,
+                                                  uint32_t c0, uint32_t c_end, uint32_t t,
                                                   const PairArgs &pa, const Geometry &g,
                                                   DevStatus *status, const TraceArgs &tr,
-                                                  PackedLds &lds) {
+                                                  PackedWaveLds<kFused> &wlds, uint32_t wave,
+                                                  bool large, double *obs = nullptr) {
   // wave priority as in cell_step: the filter loop at the base priority,
   // the latency-bound rest of a unit above it
   __builtin_amdgcn_s_setprio(1);
+  PackedLds &lds = wlds.unit;
   constexpr uint32_t kNone = 0xFFFFFFFFu;
   const uint32_t lane = lane_id();
   const uint64_t below = (1ull << lane) - 1ull;
-  if (c0 == 0 && lane == 0) clear_idle_scratch(src, t);
+  if (c0 == 0 && wave == 0 && lane == 0) clear_idle_scratch(src, t);
   // the tile's cells, one a lane; overflowing and larger cells are left out
   const uint32_t cc = c0 + lane;
-  const uint32_t ccnt = cc < n_cells ? src.count[cc] : 0u;
-  const bool packed = cc < n_cells && ccnt <= kPackedMax && ccnt <= src.cap;
+  const uint32_t ccnt = cc < c_end ? src.count[cc] : 0u;
+  const bool packed = cc < c_end && ccnt <= kPackedMax && ccnt <= src.cap;
+  __syncthreads();
+  if (kFused && wave == 0 && packed) src.count[cc] = 0u;  // for the buffer's next use
+  if (obs && wave == 0 && packed && ccnt == 0u) {
+    double *const out = obs + kCellSums * (size_t)cc;
+    out[0] = out[1] = out[2] = out[3] = 0.0;
+  }
   const uint32_t nl = packed ? ccnt : 0u;
   const uint32_t incl = wave_inclusive_sum(nl);  // inclusive prefix of the packed counts
   const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
   if (kFused) clear_slot_table(lds.tab);
-  uint32_t cnt_pairs = 0, n_acc = 0, n_claims = 0;
+  uint32_t cnt_pairs = 0, n_acc = 0, n_claims = 0, unit = 0;
   for (uint32_t base = 0; base < total;) {
     // the unit: the cells whose particles end within base + 64 (a prefix of
     // the tile's lanes beyond the previous unit; each cell fits alone)
     const uint64_t fit = __ballot(incl <= base + kPackedMax);
     const uint32_t e = 63u - (uint32_t)__builtin_clzll(fit);
     const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)e);
+    if (unit++ % kPackedWaves != wave) {
+      base = end;
+      continue;
+    }
     const uint32_t p = end - base;  // particles of the unit
     const bool in_unit = nl > 0 && incl - nl >= base && lane <= e;
     wave_lds_sync();  // the previous unit's readers of lds are done
@@ -1969,6 +1776,33 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
         put_momentum(src.st, (size_t)c * src.cap + gl, px, py, pz);
       }
     }
+    if (obs) {
+      // the cells' sums (kCellSums), one cell a lane, from the terms of its
+      // particles, which take the momenta's place in LDS
+      wave_lds_sync();
+      if (mine) {
+        double se = 0.0, sp = 0.0, sxx = 0.0;
+        obs_add(px, py, pz, se, sp, sxx);
+        lds.px[lane] = se;
+        lds.py[lane] = sp;
+        lds.pz[lane] = sxx;
+      }
+      wave_lds_sync();
+      if (in_unit) {
+        double se = 0.0, sp = 0.0, sxx = 0.0;
+        const uint32_t first = incl - nl - base;
+        for (uint32_t j = first; j < first + nl; ++j) {
+          se += lds.px[j];
+          sp += lds.py[j];
+          sxx += lds.pz[j];
+        }
+        double *const out = obs + kCellSums * (size_t)cc;
+        out[0] = se;
+        out[1] = sp;
+        out[2] = sxx;
+        out[3] = (double)nl;
+      }
+    }
     if (kFused) {
       double x = 0, y = 0, z = 0;
       uint32_t c2 = 0, id = 0;
@@ -1985,8 +1819,7 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
     }
     base = end;
   }
-  // work counters of the tile, in one slot; the packed cells' counts
-  // cleared for the buffer's next use
+  // work counters of the wave's units, in one slot
 #pragma unroll
   for (int s = 32; s > 0; s >>= 1) {
     cnt_pairs += __shfl_down(cnt_pairs, s);
@@ -1998,7 +1831,14 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
     atomicAdd(&status->cand[slot], (unsigned long long)n_acc);
     atomicAdd(&status->claims[slot], (unsigned long long)n_claims);
   }
-  if (kFused && packed) src.count[cc] = 0u;
+  if (kLarge && large) {
+    for (uint64_t big = __ballot(ccnt > kPackedMax || ccnt > src.cap); big != 0;
+         big &= big - 1ull)
+      if (unit++ % kPackedWaves == wave)
+        cell_step<kFused, kTrace, kSmallCap, 1, false>(src, dst,
+                                                       c0 + (uint32_t)__builtin_ctzll(big), t, pa,
+                                                       g, status, tr, wlds.cell, nullptr, obs);
+  }
 }
 
 // dst is src shifted by dst_shift bytes and g is read from device memory
@@ -2006,23 +1846,24 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
 // loops).  Five waves per SIMD: the compiler's choice (4, 101-104 VGPRs)
 // made the 32^3 fm^3 set's fused step 5 % slower, six (80 VGPRs, 12
 // spilled) 4 %.
-template <bool kFused, bool kTrace>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_step_packed(
-    Cells src_arg, int64_t dst_shift, uint32_t n_cells, uint32_t t, PairArgs pa,
+template <bool kFused, bool kTrace, bool kLarge>
+__global__ __launch_bounds__(64 * kPackedWaves) __attribute__((amdgpu_waves_per_eu(5))) void k_step_packed(
+    Cells src_arg, int64_t dst_shift, uint32_t n_cells, uint32_t tile, uint32_t t, PairArgs pa,
     const Geometry *__restrict__ gp, DevStatus *status, TraceArgs tr) {
   const GCells src = binning(to_global(src_arg), t);
-  __shared__ PackedLds lds;
-  const uint32_t c0 = xcd_runs<8>(blockIdx.x, gridDim.x) * 64u;
-  packed_cells_step<kFused, kTrace>(src, dst_of(src, dst_shift, t), c0, n_cells, t, pa, *gp,
-                                    status, tr, lds);
+  __shared__ PackedWaveLds<kFused> lds[kPackedWaves];
+  const uint32_t c0 = xcd_runs<8>(blockIdx.x, gridDim.x) * tile;
+  const uint32_t c_end = min(c0 + tile, n_cells);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
+  packed_cells_step<kFused, kTrace, kLarge>(src, dst_of(src, dst_shift, t), c0, c_end, t, pa,
+                                            *gp, status, tr, lds[wave], wave, true);
 }
 
-// One wave per 64 consecutive cells: the cells holding more than `lanes`
-// particles.
+// One wave per 64 consecutive cells: the cells that the packed launch left.
 template <bool kFused, bool kTrace, uint32_t kCap>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_step_large(
     Cells src_arg, Cells dst_arg, uint32_t n_cells,
-                                                   uint32_t lanes, uint32_t t, PairArgs pa,
+                                                   uint32_t t, PairArgs pa,
                                                    Geometry g, DevStatus *status,
                                                    TraceArgs tr) {
   const GCells src = binning(to_global(src_arg), t);
@@ -2030,24 +1871,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   __shared__ CellLds<kFused, kCap> lds;
   const uint32_t c0 = blockIdx.x * 64u;
   const uint32_t c_end = c0 + 64u < n_cells ? c0 + 64u : n_cells;
-  large_cells_step<kFused, kTrace, kCap>(src, dst, c0, c_end, lanes, t, pa, g, status, tr,
-                                         lds);
+  large_cells_step<kFused, kTrace, kCap>(src, dst, c0, c_end, t, pa, g, status, tr, lds);
 }
 
-// One wave per cell, for the cells holding more than `lanes` particles: the
-// oversize-cell launch when such cells are common (a wave that scans 64 of
-// them would step them one after another).
+// One wave per cell, for the cells that the packed launch left when they are
+// common (a wave that scans 64 of them would step them one after another).
 template <bool kFused, bool kTrace, uint32_t kCap>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<kCap>()))) void k_step_over(
     Cells src_arg, int64_t dst_shift,
-                                                  uint32_t lanes, uint32_t t, PairArgs pa,
+                                                  uint32_t t, PairArgs pa,
                                                   const Geometry *__restrict__ gp,
                                                   DevStatus *status, TraceArgs tr) {
   const GCells src = binning(to_global(src_arg), t);
   __shared__ CellLds<kFused, kCap> lds;
   const uint32_t c = xcd_runs<8>(blockIdx.x, gridDim.x);
   const uint32_t cnt = src.count[c];
-  if (cnt <= lanes && cnt <= src.cap) return;
+  if (cnt <= kPackedMax && cnt <= src.cap) return;
   cell_step<kFused, kTrace, kCap>(src, dst_of(src, dst_shift, t), c, t, pa, *gp, status, tr,
                                   lds);
 }
@@ -2094,10 +1933,10 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(cell_waves<
 //   items   cpi consecutive cells, for the binning (every event); a wave
 //           takes items with a grid stride, so a grid smaller than the item
 //           count is a persistent launch;
-//   chunks  64 / lanes cells, one wave each, for the small cells of events
-//           with lanes per cell > 0;
-//   scans   64 cells, one wave each, stepping the cells of those events that
-//           hold more particles than the event's lanes per cell;
+//   tiles   `tile` cells, a workgroup each, for the events with lanes per
+//           cell > 0, which are stepped in packed units;
+//   scans   64 cells, one wave each, stepping the cells that the units leave
+//           out, for those of these events whose blocks exceed the small LDS;
 //   cells   one cell per wave, for events stepped one wave per cell.
 // The step kernels have no loop over units: a loop keeps the descriptor and
 // lane constants live across iterations, which costs registers and with
@@ -2131,7 +1970,7 @@ struct EventView {
   Geometry g;
   PairArgs pa;
   DevStatus *status;
-  uint32_t t, lanes, n_cells;
+  uint32_t t, n_cells;
 };
 
 __device__ __forceinline__ EventView event_view(const BatchEvent *__restrict__ E, uint32_t j) {
@@ -2149,7 +1988,6 @@ __device__ __forceinline__ EventView event_view(const BatchEvent *__restrict__ E
   v.t = E->t + j - 1u;
   v.src = binning(v.src, v.t);
   v.dst = binning(v.dst, v.t + 1u);
-  v.lanes = E->lanes;
   v.n_cells = E->n_cells;
   return v;
 }
@@ -2202,54 +2040,43 @@ __global__ __launch_bounds__(kBlock) void k_batch_bin(const BatchEvent *__restri
   }
 }
 
-// Small cells: one wave per chunk of 64 / lanes cells.
+// Packed cells: a workgroup per tile of the event's `tile` cells.  The cells
+// that the units leave out are stepped here too where their blocks fit the
+// small LDS, else by k_batch_step_scan.
 template <bool kFused>
-__global__ __launch_bounds__(64) void k_batch_step_small(const BatchEvent *__restrict__ ev,
-                                                         const uint32_t *__restrict__ chunk_begin,
-                                                         uint32_t n_events, uint32_t j) {
-  __shared__ SmallLds lds;
-  const uint32_t chunk = xcd_runs<8>(blockIdx.x, gridDim.x);
-  const BatchEvent *__restrict__ E = ev + find_event(chunk_begin, n_events, chunk);
-  const EventView v = event_view(E, j);
-  const uint32_t per = 64u / v.lanes;
-  const uint32_t c0 = (chunk - E->chunk_begin) * per;
-  const uint32_t c1 = c0 + per < v.n_cells ? c0 + per : v.n_cells;
-  const TraceArgs none{};
-  double *const obs = obs_target(E, j);
-  switch (v.lanes) {
-    case 8:
-      small_cells_step<kFused, false, 8>(v.src, v.dst, c0, c1, v.t, v.pa, v.g, v.status, none, lds,
-                                         obs);
-      break;
-    case 16:
-      small_cells_step<kFused, false, 16>(v.src, v.dst, c0, c1, v.t, v.pa, v.g, v.status, none,
-                                          lds, obs);
-      break;
-    case 32:
-      small_cells_step<kFused, false, 32>(v.src, v.dst, c0, c1, v.t, v.pa, v.g, v.status, none,
-                                          lds, obs);
-      break;
-    default:
-      small_cells_step<kFused, false, 64>(v.src, v.dst, c0, c1, v.t, v.pa, v.g, v.status, none,
-                                          lds, obs);
-  }
+__global__ __launch_bounds__(64 * kPackedWaves) __attribute__((amdgpu_waves_per_eu(5))) void k_batch_step_packed(
+    const BatchEvent *__restrict__ ev, const uint32_t *__restrict__ tile_begin,
+    uint32_t n_events, uint32_t j) {
+  __shared__ PackedWaveLds<kFused> lds[kPackedWaves];
+  const uint32_t unit = xcd_runs<8>(blockIdx.x, gridDim.x);
+  const BatchEvent *__restrict__ E = ev + find_event(tile_begin, n_events, unit);
+  const uint32_t s = (E->cur ^ (j & 1u)) & 1u;
+  const uint32_t t = E->t + j - 1u;
+  const GCells src = binning(to_global(E->buf[s]), t);
+  const int64_t shift = (const char *)E->buf[s ^ 1u].st.rec - (const char *)E->buf[s].st.rec;
+  const PairArgs pa = E->pa;
+  const uint32_t c0 = (unit - E->tile_begin) * E->tile;
+  const uint32_t c_end = min(c0 + E->tile, E->n_cells);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
+  packed_cells_step<kFused, false, true>(src, dst_of(src, shift, t), c0, c_end, t, pa, E->g,
+                                         E->status, TraceArgs{}, lds[wave], wave,
+                                         src.cap <= kSmallCap, obs_target(E, j));
 }
 
-// The cells of 64 consecutive cells of a small-cell event holding more than
-// its lanes per cell (rare), by the whole wave.
-template <bool kFused, uint32_t kCap>
+// The cells of 64 consecutive cells of a packed event with blocks of more
+// than kSmallCap slots that its units left out, by the whole wave.
+template <bool kFused>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_batch_step_scan(
-    const BatchEvent *__restrict__ ev,
-                                                        const uint32_t *__restrict__ scan_begin,
-                                                        uint32_t n_events, uint32_t j) {
-  __shared__ CellLds<kFused, kCap> lds;
+    const BatchEvent *__restrict__ ev, const uint32_t *__restrict__ scan_begin,
+    uint32_t n_events, uint32_t j) {
+  __shared__ CellLds<kFused, kCellCap> lds;
   const uint32_t unit = blockIdx.x;
   const BatchEvent *__restrict__ E = ev + find_event(scan_begin, n_events, unit);
   const EventView v = event_view(E, j);
   const uint32_t c0 = (unit - E->scan_begin) * 64u;
   const uint32_t c1 = c0 + 64u < v.n_cells ? c0 + 64u : v.n_cells;
-  large_cells_step<kFused, false, kCap>(v.src, v.dst, c0, c1, v.lanes, v.t, v.pa, v.g,
-                                        v.status, TraceArgs{}, lds, obs_target(E, j));
+  large_cells_step<kFused, false, kCellCap>(v.src, v.dst, c0, c1, v.t, v.pa, v.g, v.status,
+                                            TraceArgs{}, lds, obs_target(E, j));
 }
 
 // One wave per cell of the events stepped one wave per cell.  Held to the
@@ -2646,45 +2473,30 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
                  dev.ev_stop, src, shift, t, pa, dev.g, status, tr);
     return;
   }
-  // the small cells and, concurrently, the cells the small-cell kernel
+  const dim3 grid((n_cells + dev.tile - 1) / dev.tile), wide(64 * kPackedWaves);
+  // few larger cells, in blocks that the small LDS holds: the packed kernel
+  // steps them itself
+  if constexpr (!kTrace && kCap == kSmallCap) {
+    if (dev.over_span != 1) {
+      launch_timed(k_step_packed<kFused, kTrace, true>, grid, wide, s, dev.ev_start, dev.ev_stop,
+                   src, shift, n_cells, dev.tile, t, pa, dev.g, status, tr);
+      return;
+    }
+  }
+  // the packed cells and, concurrently, the cells that the packed kernel
   // leaves alone (disjoint cells; both append to dst through atomics); timed
   // by events recorded around the whole launch
   if (dev.ev_start) (void)hipEventRecord(dev.ev_start, s);
   fork(s, side);
-  const uint32_t per = lanes == kPackedCells ? 64u : 64u / lanes;  // cells per wave
-  const dim3 grid((n_cells + per - 1) / per);
-  // the particles above which a cell goes to the second kernel
-  const uint32_t thr = lanes == kPackedCells ? kPackedMax : lanes;
-  switch (lanes) {
-    case kPackedCells:
-      hipLaunchKernelGGL((k_step_packed<kFused, kTrace>), grid, block, 0, s, src,
-                         (int64_t)((const char *)dst.st.rec - (const char *)src.st.rec), n_cells, t,
-                         pa, dev.g, status, tr);
-      break;
-    case 8:
-      hipLaunchKernelGGL((k_step_small<kFused, kTrace, 8>), grid, block, 0, s, src, dst,
-                         n_cells, t, pa, g, status, tr);
-      break;
-    case 16:
-      hipLaunchKernelGGL((k_step_small<kFused, kTrace, 16>), grid, block, 0, s, src, dst,
-                         n_cells, t, pa, g, status, tr);
-      break;
-    case 32:
-      hipLaunchKernelGGL((k_step_small<kFused, kTrace, 32>), grid, block, 0, s, src, dst,
-                         n_cells, t, pa, g, status, tr);
-      break;
-    default:
-      hipLaunchKernelGGL((k_step_small<kFused, kTrace, 64>), grid, block, 0, s, src, dst,
-                         n_cells, t, pa, g, status, tr);
-  }
+  hipLaunchKernelGGL((k_step_packed<kFused, kTrace, false>), grid, wide, 0, s, src, shift,
+                     n_cells, dev.tile, t, pa, dev.g, status, tr);
   hipStream_t so = side ? side->stream : s;
   if (dev.over_span == 1)
     hipLaunchKernelGGL((k_step_over<kFused, kTrace, kCap>), dim3(n_cells), block, 0, so, src,
-                       (int64_t)((const char *)dst.st.rec - (const char *)src.st.rec), thr, t,
-                       pa, dev.g, status, tr);
+                       shift, t, pa, dev.g, status, tr);
   else
     hipLaunchKernelGGL((k_step_large<kFused, kTrace, kCap>), dim3((n_cells + 63) / 64), block,
-                       0, so, src, dst, n_cells, thr, t, pa, g, status, tr);
+                       0, so, src, dst, n_cells, t, pa, g, status, tr);
   join(s, side);
   if (dev.ev_stop) (void)hipEventRecord(dev.ev_stop, s);
 }
@@ -2806,33 +2618,29 @@ void launch_batch_run(BatchEvent *ev, const BatchSpaces &sp, uint32_t n_events, 
   if (between) between(ctx, 0);
   hipLaunchKernelGGL(k_batch_bin, dim3(bin_grid), dim3(kBlock), 0, s, cev, sp.item_begin,
                      n_events, sp.n_items);
-  // launch j: the small cells on s; concurrently on the side stream the
-  // cells of events stepped one wave per cell, then the oversize cells of
-  // small-cell events (all disjoint cells; appends go through atomics)
+  // launch j: the packed events on s; concurrently on the side stream the
+  // cells of events stepped one wave per cell, then the larger cells of
+  // packed events with large blocks (all disjoint cells; appends go through
+  // atomics)
   auto step = [&](auto fused, uint32_t j) {
     constexpr bool kF = decltype(fused)::value;
     const bool both =
-        sp.n_chunks > 0 && (sp.n_cells[0] > 0 || sp.n_cells[1] > 0 || sp.n_scans > 0);
+        sp.n_tiles > 0 && (sp.n_cells[0] > 0 || sp.n_cells[1] > 0 || sp.n_scans > 0);
     const SideStream *sd = both ? side : nullptr;
     const hipStream_t s2 = sd ? sd->stream : s;
     fork(s, sd);
-    if (sp.n_chunks > 0)
-      hipLaunchKernelGGL((k_batch_step_small<kF>), dim3(sp.n_chunks), wave, 0, s, cev,
-                         sp.chunk_begin, n_events, j);
+    if (sp.n_tiles > 0)
+      hipLaunchKernelGGL((k_batch_step_packed<kF>), dim3(sp.n_tiles), dim3(64 * kPackedWaves), 0,
+                         s, cev, sp.tile_begin, n_events, j);
     if (sp.n_cells[0] > 0)
       hipLaunchKernelGGL((k_batch_step_cells<kF, kSmallCap>), dim3(sp.n_cells[0]), wave, 0, s2,
                          cev, sp.cell_begin[0], n_events, j);
     if (sp.n_cells[1] > 0)
       hipLaunchKernelGGL((k_batch_step_cells<kF, kCellCap>), dim3(sp.n_cells[1]), wave, 0, s2,
                          cev, sp.cell_begin[1], n_events, j);
-    if (sp.n_scans > 0) {
-      if (sp.scan_large)
-        hipLaunchKernelGGL((k_batch_step_scan<kF, kCellCap>), dim3(sp.n_scans), wave, 0, s2,
-                           cev, sp.scan_begin, n_events, j);
-      else
-        hipLaunchKernelGGL((k_batch_step_scan<kF, kSmallCap>), dim3(sp.n_scans), wave, 0, s2,
-                           cev, sp.scan_begin, n_events, j);
-    }
+    if (sp.n_scans > 0)
+      hipLaunchKernelGGL((k_batch_step_scan<kF>), dim3(sp.n_scans), wave, 0, s2, cev,
+                         sp.scan_begin, n_events, j);
     join(s, sd);
     // the events due for an observation after this launch
     if (sp.obs_nx > 0 && (!obs_at || obs_at[j]))

@@ -81,6 +81,17 @@ def footprint(req: Request) -> int:
                                   "cell_capacity": W.capacity_for(req.work)}, req.work.n)
 
 
+def lanes_for(work: W.Workload) -> int:
+    """Lanes per cell of a request's event, which is admitted without reading
+    its occupancy back: the library's rule for batched events, from the
+    expected occupancies (packed cells where the mean is at most 21 and the
+    dense side's cells fit a packed unit of 64 particles)."""
+    hot = W.max_mean_occupancy(work)
+    if work.n_cells < 1024 or work.n > 21 * work.n_cells or hot + 4.0 * math.sqrt(hot) > 64.0:
+        return 0
+    return next((g for g in (8, 16) if hot + 3.0 * math.sqrt(hot) <= g), 32)
+
+
 def collect_ready(pending: deque, results: list, now, block: bool = False):
     """Moves every queued result whose copy to the host has completed from
     `pending` (entries (done event, result fields, host T00, host T0x)) to
@@ -199,7 +210,8 @@ class Server:
         with torch.cuda.stream(lane.B.stream):
             state = W.riemann_state_torch(req.work, req.state_seed, device=self.device)
         lane.B.admit_async(slot, {**req.work.params(),
-                                  "cell_capacity": W.capacity_for(req.work)}, state)
+                                  "cell_capacity": W.capacity_for(req.work)}, state,
+                           lanes=lanes_for(req.work))
         if self.observe_in_runs:
             w = req.work
             lane.B.set_observe(slot, w.observe_every, rows=max(1, w.steps // w.observe_every))
