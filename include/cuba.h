@@ -236,12 +236,13 @@ int cuba_sync(cuba_ctx *ctx);
  * with the Philox filter first and the exact test in compacted rows; cells
  * of more than 64 particles take a wave each.  For sparse boxes and boxes of
  * dense and sparse regions.  The number is the lanes per cell of the kernel
- * that streams and bins a run's first step (1: 16).  128: a workgroup of two
- * waves per cell, which split its pair tests (the first wave claims every
- * accepted pair in increasing pair order); for boxes of fewer cells than the
- * chip has SIMDs.  cuba_init chooses from the initial occupancy and
+ * that streams and bins a run's first step (1: 16).  128: a workgroup of 4, 8
+ * or 16 waves per cell, which split its pair tests (the first wave claims
+ * every accepted pair in increasing pair order); for boxes of few dense
+ * cells.  cuba_init chooses from the initial occupancy and
  * K = sigma / r_test * dt / V_cell: 128 below 1024 cells if at least half of
- * them hold more than 32 particles, else 0 below 4096 cells or if more than
+ * them hold more than 32 particles and below 4096 cells if the mean
+ * occupancy is at least cells / 20, else 0 below 4096 cells or if more than
  * 0.2 % of the cells hold more than 64 particles, else 1 if the mean
  * occupancy is at most 8 (at most 12 if 2K >= 0.01), else the smallest of 8,
  * 16, 32 that all but 0.2 % of the cells fit (below 16384 cells if the mean

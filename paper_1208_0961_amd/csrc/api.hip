@@ -167,21 +167,25 @@ int derive(const cuba_params *p, int64_t n, Derived &d) {
 // 26 for 4 096, 16 384 and 65 536 cells and more, if few cells exceed the 64
 // particles of a unit; and for boxes of dense and sparse regions (at least a
 // quarter of the cells with at most 8 particles).  Else one wave per cell.
-// Except: on the plain path, a box of fewer cells than the chip has SIMDs,
-// most of them holding more than 32 particles, takes two waves per cell (the
-// 1-D tube's 100 cells step in 24 instead of 33 us; at 10 000 cells and
-// more the second wave's extra work outweighs its parallelism).  In a batch
+// Except: on the plain path, a box of few dense cells takes several waves per
+// cell: fewer cells than the chip has SIMDs, most of them holding more than
+// 32 particles (100 cells of 100: 17 against 31 us a step, 900 of 33: 11
+// against 14), or up to 4 096 cells whose mean is a twentieth of their number
+// or more (1 600 cells of 65 / 100: 24 / 32 against 23 / 37 us, 2 500 of 100 /
+// 200: 44 / 87 against 45 / 115, 3 600 of 200 / 400: 116 / 338 against 123 /
+// 404), as each wave per cell then leaves SIMDs idle.  In a batch
 // (plain = false) an event's step is not its own launch, so smaller boxes
 // are packed too.
 constexpr double kOversizeFraction = 2e-3;
 constexpr double kSparseFraction = 0.25;
 constexpr int64_t kPackedMinCells = 4096, kPackedMinCellsBatch = 1024;
-constexpr int64_t kTwoWaveMaxCells = 1024;
+constexpr int64_t kWideMaxCells = 1024, kWideMaxCellsDense = 4096;
 constexpr double kPackedMean = 8.0, kPackedMeanHighK = 12.0, kHighTwoK = 0.01;
 uint32_t default_lanes(const uint32_t over[4], int64_t n_cells, int64_t n, double kfac,
                        bool plain) {
-  if (plain && n_cells < kTwoWaveMaxCells && 2 * (int64_t)over[2] >= n_cells)
-    return kTwoWavesPerCell;
+  if (plain && ((n_cells < kWideMaxCells && 2 * (int64_t)over[2] >= n_cells) ||
+                (n_cells < kWideMaxCellsDense && 20 * n >= n_cells * n_cells)))
+    return kWideCells;
   if (n_cells < (plain ? kPackedMinCells : kPackedMinCellsBatch)) return 0;
   const double limit = kOversizeFraction * (double)n_cells;
   const double mean = (double)n / (double)n_cells;
@@ -354,9 +358,19 @@ uint32_t packed_tile(int64_t n, int64_t n_cells) {
   return tile;
 }
 
+// Waves per cell of the wide kernel (us a step with 4 / 8 / 16 waves): 100
+// cells of 65: 12.4 / 12.8 / 12.9, of 200: 31.4 / 26.1 / 27.7, of 400: 85.0 /
+// 64.3 / 60.7; 400 cells of 200: 33.3 / 28.7 / 40.7; 900 cells of 100: 21.5 /
+// 28.4 / 28.3, of 400: 123 / 118 / 154 (a workgroup of 16 waves has a CU to
+// itself).
+uint32_t wide_waves(int64_t n, int64_t n_cells) {
+  if (n_cells >= 512 || n < 80 * n_cells) return 4;
+  return n_cells <= 256 && n > 300 * n_cells ? 16u : 8u;
+}
+
 StepDevice step_device(const cuba_ctx *c) {
   return StepDevice{&c->consts->g, over_span(c->over, c->d.n_cells),
-                    packed_tile(c->n, c->d.n_cells)};
+                    packed_tile(c->n, c->d.n_cells), wide_waves(c->n, c->d.n_cells)};
 }
 
 // The step launch's device arguments, with the stage's timing events.

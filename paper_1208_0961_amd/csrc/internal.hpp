@@ -150,15 +150,15 @@ struct BatchSpaces {
 // Lanes per cell: 0 (one wave per cell), kPackedCells, 8, 16, 32 or 64
 // (whole cells packed into waves of up to 64 particles, one per lane; the
 // number is the stream-bin kernel's lanes per cell, 16 for kPackedCells) or
-// kTwoWavesPerCell (a workgroup of two waves per cell; plain path only, as
-// is kPackedCells by that name).
+// kWideCells (a workgroup of several waves per cell; plain path only, as is
+// kPackedCells by that name).
 constexpr uint32_t kPackedCells = 1;
-constexpr uint32_t kTwoWavesPerCell = 128;
+constexpr uint32_t kWideCells = 128;
 inline bool valid_cell_lanes(int32_t v) {
   return v == 0 || v == 8 || v == 16 || v == 32 || v == 64;
 }
 inline bool valid_plain_cell_lanes(int32_t v) {
-  return valid_cell_lanes(v) || v == (int32_t)kTwoWavesPerCell ||
+  return valid_cell_lanes(v) || v == (int32_t)kWideCells ||
          v == (int32_t)kPackedCells;
 }
 
@@ -208,7 +208,8 @@ struct StepDevice {
   // and steps the oversize ones one after another; few oversize cells) or 1
   // (a wave per cell; many)
   uint32_t over_span;
-  uint32_t tile;  // cells a workgroup of the packed kernel takes (8 .. 64)
+  uint32_t tile;   // cells a workgroup of the packed kernel takes (8 .. 64)
+  uint32_t waves;  // waves per cell of the wide kernel: 4, 8 or 16
   // stage timing: events that the launch records at its start and end (on
   // its first kernel's dispatch when it is one kernel), or null
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;

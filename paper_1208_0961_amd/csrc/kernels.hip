@@ -21,8 +21,8 @@
 //   k_step_packed  whole cells packed into waves of up to 64 particles, one
 //                  a lane (sparse cells); k_step_large / k_step_over step
 //                  larger cells where that kernel does not itself.
-//   k_step2        a workgroup of two waves per cell, splitting its pair
-//                  tests (boxes of fewer cells than SIMDs).
+//   k_step_wide    a workgroup of 4, 8 or 16 waves per cell (boxes of few
+//                  dense cells).
 //   observe        per-cell sums of E, p_x, p_x^2/E and counts, then
 //                  fixed-order slab sums.
 //   gather         state export by id.
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_carry(uint32_t *offsets,
 }
 
 // ---------------------------------------------------------------------------
-// Collisions: one wave64 (one workgroup) per cell, or two (k_step2).
+// Collisions: one wave64 (one workgroup) per cell (several: k_step_wide).
 // ---------------------------------------------------------------------------
 // A cell being stepped: member j is slot base + j of the buffer's arrays,
 // or, in an overflowing cell (ov), for j >= cap spill slot sbase + sidx[j -
@@ -877,15 +877,6 @@ struct CellLds {
   __align__(16) uint32_t bkt[kRankBuckets + 4];  // bucket ends, then starts
   __align__(16) uint32_t sorted[kCap];           // ids in bucket order
   uint32_t ov_pool_lo, ov_pool_hi, ov_ok, pad;   // an overflowing cell's scratch
-};
-
-// LDS of the second wave of a cell stepped by two: its filtered pairs, and
-// what it hands to the first wave (count, first pair it did not test), and
-// the first wave's claim count for the kinematics.
-template <uint32_t kCap>
-struct SecondWaveLds {
-  uint32_t filt[kCap / 2];
-  uint32_t n_filt, k_resume, nclaim, pad;
 };
 
 // The launch of step t clears the scratch that no launch uses now: src's
@@ -1126,28 +1117,17 @@ __device__ void large_cell_step(const GCells &src, const GCells &dst, const Cell
   if (obs) obs_write_wave(obs, cv.c, n, se, sp, sxx);
 }
 
-// Collisions of cell c of src at step t by a workgroup of kW waves (1 or
-// 2).  kFused: afterwards stream and bin the cell's particles into dst for
-// step t+1 and clear src's count.  Starts with a barrier, so a wave may call
-// it for several cells.  With two waves (x2: the second wave's LDS) the
-// pair range is split: the first wave tests the pairs below kh, resolving
-// and claiming as it goes, while the second filters the pairs from kh on
-// into its own buffer; the first wave then resolves those in order (they
-// all follow its own) and tests any pairs the second left once its buffer
-// filled.  Claims are thus made in increasing pair order as with one wave,
-// and every other phase is split over the workgroup's lanes.  Both waves
-// pass the same barriers; code that one wave runs alone synchronises with
-// itself only.  kBlk = false: one wave per cell in a workgroup of several,
-// which synchronises with itself only throughout.
-template <bool kFused, bool kTrace, uint32_t kCap, uint32_t kW = 1, bool kBlk = true>
+// Collisions of cell c of src at step t by one wave.  kFused: afterwards
+// stream and bin the cell's particles into dst for step t+1 and clear src's
+// count.  Starts with a barrier, so a wave may call it for several cells.
+// kBlk: the workgroup is this one wave; else the wave shares it with others
+// and synchronises with itself only.
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk = true>
 __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, uint32_t c,
                                           uint32_t t, const PairArgs &pa,
                                           const Geometry &g, DevStatus *status,
                                           const TraceArgs &tr, CellLds<kFused, kCap> &lds,
-                                          SecondWaveLds<kCap> *x2 = nullptr,
                                           double *obs = nullptr) {
-  static_assert(kW == 1 || (kW == 2 && !kTrace && kBlk), "one or two waves, traces with one");
-  constexpr uint32_t kT = 64 * kW;
   // filtered pairs and claimed pairs share the id buffer, kCap / 2 each
   constexpr uint32_t kFilt = kCap / 2;
   static_assert(kCap <= kCellCap && kFilt >= 256, "cell capacity");
@@ -1156,13 +1136,13 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
   uint32_t *const s_claim = lds.buf + kFilt;
   uint16_t *const s_perm = lds.perm;
   cell_sync<kBlk>();
-  // A fused one-wave step of a cell whose members are all in its block
+  // A fused step of a cell whose members are all in its block
   // keeps the new momenta of up to kMomCap claims in LDS (where the rank
   // sorted its ids; claim i's two members at 2i, 2i + 1, and by member a
   // byte map to them, in the rank's buckets) for its binning, instead of
   // writing them back to the source block, whose lines would then be
   // written to memory once more though no one reads them again.
-  constexpr bool kMomInLds = kFused && kW == 1;
+  constexpr bool kMomInLds = kFused;
   constexpr uint32_t kMomCap = kCap / 12u;  // 6 doubles a claim in sorted[]
   static_assert(6u * kMomCap * sizeof(double) <= kCap * sizeof(uint32_t), "claim momenta");
   static_assert(2u * kMomCap + 2u <= 255u && kCap <= 4u * (kRankBuckets + 4u), "claim map");
@@ -1173,8 +1153,6 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
   bool mom_lds = false;
 
   const uint32_t lane = lane_id();
-  const uint32_t tid = kW == 1 ? lane : (uint32_t)threadIdx.x;
-  const uint32_t wv = tid / 64;  // this wave within the cell's workgroup
   CellView cv;
   cv.c = c;
   cv.t = t;
@@ -1185,38 +1163,35 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
   cv.sbase = 0;
   cv.sidx = nullptr;
   cv.slots = lds.sorted;
-  if (cv.c == 0 && tid == 0) clear_idle_scratch(src, t);
+  if (cv.c == 0 && lane == 0) clear_idle_scratch(src, t);
   // Wave priority: the phases that are chains of dependent loads, LDS
   // atomics and barriers (ids and rank; claims, kinematics and binning)
   // issue ahead of the other waves' pair-test loops, which keep the VALU
   // busy meanwhile; the pair tests run at the base priority.
-  if (kW == 1) __builtin_amdgcn_s_setprio(1);
+  __builtin_amdgcn_s_setprio(1);
   if (cv.ov) {
-    // an overflowing cell: find its spilled members (wave 0), then step it
+    // an overflowing cell: find its spilled members, then step it
     // here, in LDS if it fits, else with the global-memory method
-    if (wv == 0) find_spilled<kFused, kCap>(src, cv, lds, status);
+    find_spilled<kFused, kCap>(src, cv, lds, status);
     cell_sync<kBlk>();
     if (lds.ov_ok == 0u) return;  // internal error, flagged
     const SpillDesc *const sd = src.sp;
     cv.sbase = sd->base;
     cv.sidx = sd->pool->buf + (((uint64_t)lds.ov_pool_hi << 32) | lds.ov_pool_lo);
     if (cv.n > kCap) {
-      if (wv == 0)
-        large_cell_step<kFused, kTrace, kCap>(src, dst, cv, pa, g, status, tr, lds,
-                                              kW == 1 ? obs : nullptr);
+      large_cell_step<kFused, kTrace, kCap>(src, dst, cv, pa, g, status, tr, lds, obs);
       return;
     }
   }
   const uint32_t n = cv.n;
   const GState &st = src.st;
-  // observation sums only for one wave per cell (the batch's shape)
-  double *const ob = kW == 1 ? obs : nullptr;
+  double *const ob = obs;
 
   uint32_t nclaim = 0;
   if (n >= 2) {
     // ids to LDS, padded to a multiple of 4 with an id no particle has
     const uint32_t n4 = (n + 3u) & ~3u;
-    for (uint32_t j = tid; j < n4; j += kT)
+    for (uint32_t j = lane; j < n4; j += 64u)
       s_id[j] = j < n ? st.id[cv.at_spill(j)] : 0xFFFFFFFFu;
     cell_sync<kBlk>();
 
@@ -1238,12 +1213,12 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
       const uint32_t shift = bits > 8u ? bits - 8u : 0u;
       uint32_t *const s_bkt = lds.bkt;
       uint32_t *const s_sorted = lds.sorted;
-      for (uint32_t b = tid; b < kRankBuckets; b += kT) s_bkt[b] = 0u;
-      if (tid == 0) s_bkt[kRankBuckets] = n;
+      for (uint32_t b = lane; b < kRankBuckets; b += 64u) s_bkt[b] = 0u;
+      if (lane == 0) s_bkt[kRankBuckets] = n;
       cell_sync<kBlk>();
-      for (uint32_t j = tid; j < n; j += kT) atomicAdd(&s_bkt[(s_id[j] - lo) >> shift], 1u);
+      for (uint32_t j = lane; j < n; j += 64u) atomicAdd(&s_bkt[(s_id[j] - lo) >> shift], 1u);
       cell_sync<kBlk>();
-      if (wv == 0) {  // inclusive scan of the counts: s_bkt[b] = end of bucket b
+      {  // inclusive scan of the counts: s_bkt[b] = end of bucket b
         uint4 q = reinterpret_cast<uint4 *>(s_bkt)[lane];
         q.y += q.x;
         q.z += q.y;
@@ -1258,13 +1233,13 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
       }
       cell_sync<kBlk>();
       // each bucket filled from its end: afterwards s_bkt[b] is its start
-      for (uint32_t j = tid; j < n; j += kT) {
+      for (uint32_t j = lane; j < n; j += 64u) {
         const uint32_t v = s_id[j];
         const uint32_t pos = atomicSub(&s_bkt[(v - lo) >> shift], 1u) - 1u;
         s_sorted[pos] = v;
       }
       cell_sync<kBlk>();
-      for (uint32_t j = tid; j < n; j += kT) {
+      for (uint32_t j = lane; j < n; j += 64u) {
         const uint32_t me = s_id[j], b = (me - lo) >> shift;
         const uint32_t p1 = s_bkt[b + 1];
         uint32_t r = s_bkt[b];
@@ -1276,7 +1251,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
       // at most kBucketRankMin < 64 particles: one per lane, counting all ids
       const uint4 *s_id4 = reinterpret_cast<const uint4 *>(s_id);
       static_assert(kBucketRankMin < 64, "one particle per lane");
-      if (tid < n) {
+      if (lane < n) {
         const uint32_t me = s_id[lane];
         uint32_t r = 0;
         for (uint32_t m = 0; m < n4 / 4; ++m) {
@@ -1289,7 +1264,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     }
     cell_sync<kBlk>();
     if (cv.ov) {  // the members' slots, in LDS (the rank no longer needs it)
-      for (uint32_t j = tid; j < n; j += kT) lds.sorted[j] = (uint32_t)cv.at_spill(j);
+      for (uint32_t j = lane; j < n; j += 64u) lds.sorted[j] = (uint32_t)cv.at_spill(j);
       cell_sync<kBlk>();
     } else if (kMomInLds) {
       // the claim map (one byte a member, zero: not scattered), in the
@@ -1302,63 +1277,20 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     // and the claims of the filtered ones in increasing k
     const uint32_t npairs = n * (n - 1u) / 2u;
     uint32_t nf = 0, claimed_bits = 0, n_acc = 0;
-    if (kW == 1) __builtin_amdgcn_s_setprio(0);
-    if (kW == 1) {
-      if (pa.any)
-        test_pairs<true, kTrace, kBlk, kFilt>(0u, npairs, cv, pa, st, s_perm, s_filt, nf,
-                                              s_claim, nclaim, claimed_bits, n_acc, tr,
-                                              status);
-      if (nf != 0)
-        resolve_filtered<kTrace, kBlk>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
-                                 claimed_bits, n_acc, tr, status);
-      cell_sync<kBlk>();
-    } else {
-      const uint32_t kh = npairs / 2u / 128u * 128u;
-      if (wv == 0) {
-        if (pa.any)
-          test_pairs<true, false, false, kFilt>(0u, kh, cv, pa, st, s_perm, s_filt, nf,
-                                                s_claim, nclaim, claimed_bits, n_acc, tr,
-                                                status);
-        if (nf != 0)
-          resolve_filtered<false, false>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
-                                         claimed_bits, n_acc, tr, status);
-        nf = 0;
-      } else {
-        uint32_t n1 = 0, k_resume = npairs;
-        if (pa.any)
-          k_resume = test_pairs<false, false, false, kCap / 2>(
-              kh, npairs, cv, pa, st, s_perm, x2->filt, n1, s_claim, nclaim, claimed_bits,
-              n_acc, tr, status);
-        if (lane == 0) {
-          x2->n_filt = n1;
-          x2->k_resume = k_resume;
-        }
-      }
-      cell_sync<kBlk>();
-      if (wv == 0) {
-        const uint32_t n1 = x2->n_filt, k_resume = x2->k_resume;
-        if (n1 != 0)
-          resolve_filtered<false, false>(n1, cv, pa, st, s_perm, x2->filt, s_claim, nclaim,
-                                         claimed_bits, n_acc, tr, status);
-        if (k_resume < npairs) {
-          test_pairs<true, false, false, kFilt>(k_resume, npairs, cv, pa, st, s_perm, s_filt,
-                                                nf, s_claim, nclaim, claimed_bits, n_acc, tr,
-                                                status);
-          if (nf != 0)
-            resolve_filtered<false, false>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
-                                           claimed_bits, n_acc, tr, status);
-        }
-        if (lane == 0) x2->nclaim = nclaim;
-      }
-      cell_sync<kBlk>();
-      nclaim = x2->nclaim;
-    }
+    __builtin_amdgcn_s_setprio(0);
+    if (pa.any)
+      test_pairs<true, kTrace, kBlk, kFilt>(0u, npairs, cv, pa, st, s_perm, s_filt, nf, s_claim,
+                                            nclaim, claimed_bits, n_acc, tr, status);
+    if (nf != 0)
+      resolve_filtered<kTrace, kBlk>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
+                                     claimed_bits, n_acc, tr, status);
+    cell_sync<kBlk>();
 
-    if (kW == 1) __builtin_amdgcn_s_setprio(1);
+    __builtin_amdgcn_s_setprio(1);
     // work counters (spread over slots by cell against contention)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) n_acc += __shfl_down(n_acc, o);
-    if (tid == 0) {
+    if (lane == 0) {
       const uint32_t slot = cv.c % kCounterSlots;
       atomicAdd(&status->pairs[slot], (unsigned long long)npairs);
       atomicAdd(&status->cand[slot], (unsigned long long)n_acc);
@@ -1369,7 +1301,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     // written back in place, or for the binning below into LDS; a fused
     // step then bins every particle
     mom_lds = kMomInLds && !cv.ov && nclaim <= kMomCap;
-    for (uint32_t i0 = wv * 64u; i0 < nclaim; i0 += kT) {
+    for (uint32_t i0 = 0; i0 < nclaim; i0 += 64u) {
       const uint32_t i = i0 + lane;
       const bool active = i < nclaim;
       double ax = 0, ay = 0, az = 0, bx = 0, by = 0, bz = 0;
@@ -1413,7 +1345,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
       }
     }
     if (kFused || ob) cell_sync<kBlk>();
-  } else if (kTrace && n == 1 && tid == 0 && tr.perm) {
+  } else if (kTrace && n == 1 && lane == 0 && tr.perm) {
     tr.perm[tr.offsets[cv.c]] = st.id[cv.at_spill(0)];
   }
 
@@ -1428,8 +1360,8 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     const uint32_t sy = (uint32_t)g_l.n[2], sx = (uint32_t)g_l.n[1] * sy;
     const int32_t cx = (int32_t)(cv.c / sx), cy = (int32_t)(cv.c % sx / sy),
                   cz = (int32_t)(cv.c % sy);
-    uint32_t *const s_dir = lds.buf + (kW == 1 ? 0u : 64u * wv);  // the ids' dead buffer
-    for (uint32_t j0 = wv * 64u; j0 < n; j0 += kT) {
+    uint32_t *const s_dir = lds.buf;  // the ids' dead buffer
+    for (uint32_t j0 = 0; j0 < n; j0 += 64u) {
       const uint32_t j = j0 + lane;
       const bool active = j < n;
       Particle q{};
@@ -1462,7 +1394,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
         append(dst, c2, active, q, status);
       }
     }
-    if (tid == 0) src.count[cv.c] = 0u;
+    if (lane == 0) src.count[cv.c] = 0u;
     if (ob) obs_write_wave(ob, cv.c, n, se, sp, sxx);
   } else if (ob) {
     double se = 0.0, sp = 0.0, sxx = 0.0;
@@ -1495,7 +1427,7 @@ __device__ __forceinline__ void large_cells_step(const GCells &src, const GCells
   while (big != 0) {
     const uint32_t l = (uint32_t)__builtin_ctzll(big);
     big &= big - 1ull;
-    cell_step<kFused, kTrace, kCap>(src, dst, c0 + l, t, pa, g, status, tr, lds, nullptr, obs);
+    cell_step<kFused, kTrace, kCap>(src, dst, c0 + l, t, pa, g, status, tr, lds, obs);
   }
 }
 
@@ -1835,9 +1767,9 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
     for (uint64_t big = __ballot(ccnt > kPackedMax || ccnt > src.cap); big != 0;
          big &= big - 1ull)
       if (unit++ % kPackedWaves == wave)
-        cell_step<kFused, kTrace, kSmallCap, 1, false>(src, dst,
+        cell_step<kFused, kTrace, kSmallCap, false>(src, dst,
                                                        c0 + (uint32_t)__builtin_ctzll(big), t, pa,
-                                                       g, status, tr, wlds.cell, nullptr, obs);
+                                                       g, status, tr, wlds.cell, obs);
   }
 }
 
@@ -1909,22 +1841,381 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<k
                                   lds);
 }
 
-// Two waves per cell (a workgroup of 128): half the pair tests each, so a
-// box of few cells has twice as many, shorter waves to spread over the
-// SIMDs (the tail of a launch whose waves are long and few is idle time).
-template <bool kFused, uint32_t kCap>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(cell_waves<kCap>()))) void k_step2(
-    Cells src_arg, int64_t dst_shift, uint32_t t,
-                                               PairArgs pa, const Geometry *__restrict__ gp,
-                                               DevStatus *status) {
-  const GCells src = binning(to_global(src_arg), t);
-  __shared__ CellLds<kFused, kCap> lds;
-  __shared__ SecondWaveLds<kCap> x2;
-  cell_step<kFused, false, kCap, 2>(src, dst_of(src, dst_shift, t),
-                                    xcd_runs<8>(blockIdx.x, gridDim.x), t, pa, *gp, status,
-                                    TraceArgs{}, lds, &x2);
+// ---------------------------------------------------------------------------
+// Several waves per cell, for boxes of few dense cells, where one wave per
+// cell leaves most SIMDs idle and the step is one cell's chain of phases.
+// A workgroup of kW waves:
+//   1. loads every particle into registers (kCap / 64 kW per thread; the
+//      slots' loads do not wait for the count), ids into LDS;
+//   2. ranks the ids and stores the momenta in canonical order in LDS, where
+//      the later phases read them: no further global load;
+//   3. tests the pairs in rounds: wave w filters the w-th of kW consecutive
+//      ranges (Philox w1) into its own list and keeps in it those that the
+//      exact test accepts; then the first wave claims from the lists in
+//      order, so that the claims run in increasing pair order as with one
+//      wave.  A range is half as long as fills its list on average; should a
+//      list fill all the same, the first wave tests the rest of that range
+//      itself;
+//   4. with each row of claims the first wave computes their kinematics, in
+//      the lanes that hold them, in place (a member is claimed once, but a
+//      later round still tests with its momentum from before: so where there
+//      are several rounds, or a list filled, the claims are listed and the
+//      kinematics follow the last one);
+//   5. fused: streams and bins each particle from its registers; else writes
+//      the scattered momenta back.
+// Cells whose members are not all in their block go to the one-wave path.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kWideFilt = 256;  // filtered pairs of a wave's list
+template <bool kFused, uint32_t kCap, uint32_t kW>
+struct WideLds {
+  CellLds<kFused, kCap> cell;  // ids, rank scratch, claims (and the one-wave path)
+  double px[kCap], py[kCap], pz[kCap];  // by canonical position
+  uint32_t filt[kW][kWideFilt];
+  uint32_t n_filt[kW], k_resume[kW];
+  uint32_t claimed[kCap / 32];  // flags by canonical position
+  uint32_t dir[54];
+  uint32_t n_claim;
+};
+
+// Exact test of the nf pairs in filt (one wave): the accepted ones, as
+// a << 10 | b, move to its front in order; returns their number.
+template <typename Lds>
+__device__ __forceinline__ uint32_t wide_exact(uint32_t nf, uint32_t *filt, const Lds &lds,
+                                               uint32_t c, uint32_t n, uint32_t t,
+                                               const PairArgs &pa) {
+  uint32_t kept = 0;
+  for (uint32_t i0 = 0; i0 < nf; i0 += 64u) {
+    const uint32_t i = i0 + lane_id();
+    bool acc = false;
+    uint32_t a = 0, b = 0;
+    if (i < nf) {
+      const uint32_t k = filt[i];
+      const Words4 w = philox10(k, c, t, 0u, pa.key0, pa.key1);
+      pair_of_index(k, n, a, b);
+      acc = uniform53(w.w0, w.w1) < p22(lds.px[a], lds.py[a], lds.pz[a], lds.px[b], lds.py[b],
+                                        lds.pz[b], pa.kfac);
+    }
+    wave_lds_sync();
+    const uint64_t m = __ballot(acc);
+    if (acc) filt[kept + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull))] = a << 10 | b;
+    kept += (uint32_t)__popcll(m);
+  }
+  wave_lds_sync();
+  return kept;
 }
 
+// New momenta of the pair (a, b) of cell c, in place.
+template <typename Lds>
+__device__ __forceinline__ void wide_scatter(uint32_t a, uint32_t b, Lds &lds, uint32_t c,
+                                             uint32_t n, uint32_t t, const PairArgs &pa) {
+  const Words4 w = philox10(row_start(a, n) + (b - a - 1u), c, t, 1u, pa.key0, pa.key1);
+  double ax = lds.px[a], ay = lds.py[a], az = lds.pz[a];
+  double bx = lds.px[b], by = lds.py[b], bz = lds.pz[b];
+  scatter_pair(ax, ay, az, bx, by, bz, uniform53(w.w0, w.w1), uniform53(w.w2, w.w3));
+  lds.px[a] = ax;
+  lds.py[a] = ay;
+  lds.pz[a] = az;
+  lds.px[b] = bx;
+  lds.py[b] = by;
+  lds.pz[b] = bz;
+}
+
+// Claims of a row of accepted pairs, one a lane (a << 10 | b; `have`: the
+// lane holds one), in lane order, by one wave: of those whose members are
+// free the first is taken and its members' others dropped, until none is
+// left.  Returns the lanes that won.
+template <typename Lds>
+__device__ __forceinline__ uint64_t wide_claim_row(uint32_t v, bool have, Lds &lds) {
+  const uint32_t a = v >> 10, b = v & 1023u;
+  bool open = have && ((lds.claimed[a >> 5] >> (a & 31u)) & 1u) == 0u &&
+              ((lds.claimed[b >> 5] >> (b & 31u)) & 1u) == 0u;
+  uint64_t won = 0;
+  for (uint64_t m = __ballot(open); m != 0; m = __ballot(open)) {
+    const uint32_t l = (uint32_t)__builtin_ctzll(m);
+    const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
+    const uint32_t la = vl >> 10, lb = vl & 1023u;
+    won |= 1ull << l;
+    open = open && a != la && a != lb && b != la && b != lb;
+  }
+  if ((won >> lane_id()) & 1ull) {
+    atomicOr(&lds.claimed[a >> 5], 1u << (a & 31u));
+    atomicOr(&lds.claimed[b >> 5], 1u << (b & 31u));
+  }
+  wave_lds_sync();
+  return won;
+}
+
+// Claims of a whole list, appended to claims.
+template <typename Lds>
+__device__ __forceinline__ void wide_claim(uint32_t na, const uint32_t *list, Lds &lds,
+                                           uint32_t *claims, uint32_t &nclaim) {
+  const uint32_t lane = lane_id();
+  for (uint32_t i0 = 0; i0 < na; i0 += 64u) {
+    const uint32_t v = i0 + lane < na ? list[i0 + lane] : 0u;
+    const uint64_t won = wide_claim_row(v, i0 + lane < na, lds);
+    if ((won >> lane) & 1ull)
+      claims[nclaim + (uint32_t)__popcll(won & ((1ull << lane) - 1ull))] = v;
+    nclaim += (uint32_t)__popcll(won);
+  }
+}
+
+template <bool kFused, uint32_t kCap, uint32_t kW>
+__device__ __forceinline__ void wide_cell_step(const GCells &src, const GCells &dst, uint32_t c,
+                                               uint32_t t, const PairArgs &pa, const Geometry &g,
+                                               DevStatus *status, WideLds<kFused, kCap, kW> &lds) {
+  constexpr uint32_t kT = 64u * kW, kPer = kCap / kT;
+  static_assert(kPer * kT == kCap && kCap <= kCellCap, "whole particles per thread");
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / 64u));
+  const size_t base = (size_t)c * src.cap;
+  Particle q[kPer];
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    q[i] = Particle{};
+    if (tid + i * kT < src.cap) q[i] = load_particle(src.st, base + tid + i * kT);
+  }
+  const uint32_t n = src.count[c];
+  if (n > src.cap) {
+    if (wv == 0)
+      cell_step<kFused, false, kCap, false>(src, dst, c, t, pa, g, status, TraceArgs{}, lds.cell);
+    return;
+  }
+  if (c == 0 && tid == 0) clear_idle_scratch(src, t);
+
+  // ids to LDS, padded to a multiple of 4 with an id no particle has
+  uint32_t *const s_id = lds.cell.buf;
+  const uint32_t n4 = (n + 3u) & ~3u;
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    const uint32_t j = tid + i * kT;
+    if (j < n4) s_id[j] = j < n ? q[i].id : 0xFFFFFFFFu;
+  }
+  for (uint32_t w = tid; w < kCap / 32u; w += kT) lds.claimed[w] = 0u;
+  if (tid < 27u) lds.dir[tid] = 0u;
+  __syncthreads();
+  // canonical position: every thread counts the smaller ids (up to kCountMax
+  // members), else by buckets of the id as in cell_step
+  constexpr uint32_t kCountMax = 256;
+  uint32_t rank[kPer];
+  if (n <= kCountMax) {
+    const uint4 *const s_id4 = reinterpret_cast<const uint4 *>(s_id);
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      const uint32_t me = q[i].id;
+      uint32_t r = 0;
+      if (tid + i * kT < n)
+#pragma unroll 4
+        for (uint32_t m = 0; m < n4 / 4u; ++m) {
+          const uint4 v = s_id4[m];
+          r += (v.x < me) + (v.y < me) + (v.z < me) + (v.w < me);
+        }
+      rank[i] = r;
+    }
+  } else {
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    for (uint32_t j = lane; j < n; j += 64u) {
+      lo = min(lo, s_id[j]);
+      hi = max(hi, s_id[j]);
+    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    const uint32_t bits = 32u - (uint32_t)__builtin_clz(hi - lo);
+    const uint32_t shift = bits > 8u ? bits - 8u : 0u;
+    uint32_t *const s_bkt = lds.cell.bkt;
+    for (uint32_t b = tid; b < kRankBuckets; b += kT) s_bkt[b] = 0u;
+    if (tid == 0) s_bkt[kRankBuckets] = n;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i)
+      if (tid + i * kT < n) atomicAdd(&s_bkt[(q[i].id - lo) >> shift], 1u);
+    __syncthreads();
+    if (wv == 0) {  // ends of the buckets
+      uint4 v = reinterpret_cast<uint4 *>(s_bkt)[lane];
+      v.y += v.x;
+      v.z += v.y;
+      v.w += v.z;
+      const uint32_t excl = wave_inclusive_sum(v.w) - v.w;
+      v.x += excl;
+      v.y += excl;
+      v.z += excl;
+      v.w += excl;
+      reinterpret_cast<uint4 *>(s_bkt)[lane] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i)
+      if (tid + i * kT < n)
+        lds.cell.sorted[atomicSub(&s_bkt[(q[i].id - lo) >> shift], 1u) - 1u] = q[i].id;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      rank[i] = 0;
+      if (tid + i * kT < n) {
+        const uint32_t b = (q[i].id - lo) >> shift, p1 = s_bkt[b + 1u];
+        uint32_t r = s_bkt[b];
+        for (uint32_t p = r; p < p1; ++p) r += lds.cell.sorted[p] < q[i].id ? 1u : 0u;
+        rank[i] = r;
+      }
+    }
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i)
+    if (tid + i * kT < n) {
+      lds.px[rank[i]] = q[i].px;
+      lds.py[rank[i]] = q[i].py;
+      lds.pz[rank[i]] = q[i].pz;
+    }
+  __syncthreads();
+
+  uint32_t *const claims = lds.cell.buf;  // the ids' buffer; at most n / 2 claims
+  const uint32_t npairs = n > 1u ? n * (n - 1u) / 2u : 0u;
+  uint32_t nclaim = 0, n_acc = 0, listed = 0;
+  if (pa.any && npairs != 0u) {
+    CellView cv{};
+    cv.c = c;
+    cv.n = n;
+    cv.t = t;
+    // pairs of a wave's range: an equal share, at most what fills half its
+    // list on average, whole rows of two
+    const float full = 0.5f * (float)kWideFilt * 0x1p32f / ((float)pa.w1_max + 1.0f);
+    const uint32_t room = max(128u, (uint32_t)min(full, 1e6f) & ~127u);
+    const uint32_t range = min(room, (npairs + 128u * kW - 1u) / (128u * kW) * 128u);
+    for (uint32_t k0 = 0; k0 < npairs; k0 += kW * range) {
+      const uint32_t kb = min(k0 + wv * range, npairs), ke = min(kb + range, npairs);
+      uint32_t nf = 0, none = 0, no_bits = 0, unused = 0;
+      const uint32_t stop = test_pairs<false, false, false, kWideFilt>(
+          kb, ke, cv, pa, src.st, nullptr, lds.filt[wv], nf, nullptr, none, no_bits, unused,
+          TraceArgs{}, status);
+      wave_lds_sync();
+      const uint32_t na = wide_exact(nf, lds.filt[wv], lds, c, n, t, pa);
+      n_acc += na;
+      if (lane == 0) {
+        lds.n_filt[wv] = na;
+        lds.k_resume[wv] = stop;
+      }
+      __syncthreads();
+      if (wv == 0) {
+        const uint32_t cnt = lane < kW ? lds.n_filt[lane] : 0u;
+        const uint32_t end = min(k0 + (lane + 1u) * range, npairs);
+        const bool whole = __ballot(lane < kW && lds.k_resume[lane] < end) == 0ull;
+        if (whole && npairs <= kW * range) {
+          // the only round: rows of 64 over all the lists
+          const uint32_t incl = wave_inclusive_sum(cnt);
+          const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+          for (uint32_t i0 = 0; i0 < total; i0 += 64u) {
+            const uint32_t i = i0 + lane;
+            uint32_t w = 0, first = 0;  // the list holding entry i, its first entry
+#pragma unroll
+            for (uint32_t u = 0; u + 1u < kW; ++u) {
+              const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)u);
+              if (i >= e) {
+                w = u + 1u;
+                first = e;
+              }
+            }
+            const uint32_t v = i < total ? lds.filt[w][i - first] : 0u;
+            const uint64_t won = wide_claim_row(v, i < total, lds);
+            nclaim += (uint32_t)__popcll(won);
+            if ((won >> lane) & 1ull) wide_scatter(v >> 10, v & 1023u, lds, c, n, t, pa);
+          }
+        } else {
+          for (uint32_t w = 0; w < kW; ++w) {
+            wide_claim(lds.n_filt[w], lds.filt[w], lds, claims, listed);
+            // a list that filled: the rest of its range
+            const uint32_t to = min(k0 + (w + 1u) * range, npairs);
+            for (uint32_t k = lds.k_resume[w]; k < to;) {
+              uint32_t more = 0;
+              k = test_pairs<false, false, false, kWideFilt>(k, to, cv, pa, src.st, nullptr,
+                                                             lds.filt[w], more, nullptr, none,
+                                                             no_bits, unused, TraceArgs{}, status);
+              wave_lds_sync();
+              more = wide_exact(more, lds.filt[w], lds, c, n, t, pa);
+              n_acc += more;
+              wide_claim(more, lds.filt[w], lds, claims, listed);
+            }
+          }
+        }
+        if (lane == 0) lds.n_claim = listed;
+      }
+      __syncthreads();
+    }
+    listed = lds.n_claim;
+  }
+  if (lane == 0) {
+    const uint32_t slot = c % kCounterSlots;
+    if (n_acc != 0u) atomicAdd(&status->cand[slot], (unsigned long long)n_acc);
+    if (wv == 0) {
+      atomicAdd(&status->pairs[slot], (unsigned long long)npairs);
+      atomicAdd(&status->claims[slot], (unsigned long long)(nclaim + listed));
+    }
+  }
+  if (listed != 0u) {
+    for (uint32_t i = tid; i < listed; i += kT)
+      wide_scatter(claims[i] >> 10, claims[i] & 1023u, lds, c, n, t, pa);
+    __syncthreads();
+  }
+  if (!kFused) {
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      const uint32_t r = rank[i];
+      if (tid + i * kT < n && ((lds.claimed[r >> 5] >> (r & 31u)) & 1u))
+        put_momentum(src.st, base + tid + i * kT, lds.px[r], lds.py[r], lds.pz[r]);
+    }
+    return;
+  }
+  // streaming and binning: slots by direction of move, numbered over the
+  // whole workgroup (as neighbour_fetch_add does for a wave)
+  const uint32_t sy = (uint32_t)g.n[2], sx = (uint32_t)g.n[1] * sy;
+  const int32_t cx = (int32_t)(c / sx), cy = (int32_t)(c % sx / sy), cz = (int32_t)(c % sy);
+  uint32_t c2[kPer], dir[kPer], order[kPer];
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    dir[i] = 27u;  // none
+    c2[i] = order[i] = 0u;
+    if (tid + i * kT < n) {
+      const uint32_t r = rank[i];
+      q[i].px = lds.px[r];
+      q[i].py = lds.py[r];
+      q[i].pz = lds.pz[r];
+      advance<true>(g, q[i].x, q[i].y, q[i].z, q[i].px, q[i].py, q[i].pz);
+      int32_t ix, iy, iz;
+      cell_axes(g, q[i].x, q[i].y, q[i].z, ix, iy, iz);
+      c2[i] = (uint32_t)((ix * g.n[1] + iy) * g.n[2] + iz);
+      const int32_t dx = ix - cx, dy = iy - cy, dz = iz - cz;
+      dir[i] = 28u;  // not a neighbour
+      if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1) {
+        dir[i] = (uint32_t)(9 * (dx + 1) + 3 * (dy + 1) + (dz + 1));
+        order[i] = atomicAdd(&lds.dir[dir[i]], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < 27u && lds.dir[tid] != 0u) {
+    const int32_t dx = (int32_t)(tid / 9u) - 1, dy = (int32_t)(tid / 3u % 3u) - 1,
+                  dz = (int32_t)(tid % 3u) - 1;
+    const uint32_t key = (uint32_t)((int32_t)c + dx * (int32_t)sx + dy * (int32_t)sy + dz);
+    lds.dir[27u + tid] = atomic_add(dst.count + key, lds.dir[tid]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    if (dir[i] < 27u) store_particle(dst, c2[i], lds.dir[27u + dir[i]] + order[i], q[i], status);
+    if (__ballot(dir[i] == 28u) != 0ull) append(dst, c2[i], dir[i] == 28u, q[i], status);
+  }
+  if (tid == 0) src.count[c] = 0u;
+}
+
+template <bool kFused, uint32_t kCap, uint32_t kW>
+__global__ __launch_bounds__(64 * kW) void k_step_wide(Cells src_arg, int64_t dst_shift,
+                                                       uint32_t t, PairArgs pa,
+                                                       const Geometry *__restrict__ gp,
+                                                       DevStatus *status) {
+  const GCells src = binning(to_global(src_arg), t);
+  __shared__ WideLds<kFused, kCap, kW> lds;
+  const Geometry g = *gp;
+  wide_cell_step<kFused, kCap, kW>(src, dst_of(src, dst_shift, t),
+                                   xcd_runs<8>(blockIdx.x, gridDim.x), t, pa, g, status, lds);
+}
 
 // ---------------------------------------------------------------------------
 // Batched steps: all live events of a batch advance together.  Each kernel
@@ -2099,8 +2390,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<k
   const int64_t shift = (const char *)E->buf[s ^ 1u].st.rec - (const char *)E->buf[s].st.rec;
   const PairArgs pa = E->pa;
   cell_step<kFused, false, kCap>(src, dst_of(src, shift, t), unit - E->cell_begin, t,
-                                 pa, E->g, E->status, TraceArgs{}, lds, nullptr,
-                                 obs_target(E, j));
+                                 pa, E->g, E->status, TraceArgs{}, lds, obs_target(E, j));
 }
 
 
@@ -2404,7 +2694,7 @@ void launch_stream_bin(const Cells &src, const Cells &dst, int64_t n_cells, uint
   // (packed cells: 16 lanes a cell; a stream-bin that packs 64 particles
   // a round whatever their cells measured the same on the 32^3 fm^3 set,
   // whose sparse cells' cost is their partly used cache lines)
-  const uint32_t G = lanes == 0 || lanes == kTwoWavesPerCell ? 64u
+  const uint32_t G = lanes == 0 || lanes == kWideCells ? 64u
                      : lanes == kPackedCells                 ? 16u
                                                              : lanes;
   const int64_t waves = (n_cells + 64 / G - 1) / (64 / G);
@@ -2463,12 +2753,21 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
   const int64_t shift = (int64_t)((const char *)dst.st.rec - (const char *)src.st.rec);
   // one kernel: timing events ride on its dispatch (no packets of their own
   // between launches)
-  if (lanes == kTwoWavesPerCell && !kTrace) {
-    launch_timed(k_step2<kFused, kCap>, dim3(n_cells), dim3(128), s, dev.ev_start, dev.ev_stop,
-                 src, shift, t, pa, dev.g, status);
+  if (lanes == kWideCells && !kTrace) {
+    const auto wide = [&](auto waves) {
+      constexpr uint32_t kW = decltype(waves)::value;
+      launch_timed(k_step_wide<kFused, kCap, kW>, dim3(n_cells), dim3(64 * kW), s, dev.ev_start,
+                   dev.ev_stop, src, shift, t, pa, dev.g, status);
+    };
+    if (dev.waves == 4)
+      wide(std::integral_constant<uint32_t, 4>{});
+    else if (dev.waves == 8)
+      wide(std::integral_constant<uint32_t, 8>{});
+    else
+      wide(std::integral_constant<uint32_t, kCap == kSmallCap ? 8 : 16>{});
     return;
   }
-  if (lanes == 0 || lanes == kTwoWavesPerCell) {
+  if (lanes == 0 || lanes == kWideCells) {
     launch_timed(k_step<kFused, kTrace, kCap>, dim3(n_cells), block, s, dev.ev_start,
                  dev.ev_stop, src, shift, t, pa, dev.g, status, tr);
     return;
