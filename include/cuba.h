@@ -246,9 +246,10 @@ int cuba_sync(cuba_ctx *ctx);
  * 0.2 % of the cells hold more than 64 particles, else 1 if the mean
  * occupancy is at most 8 (at most 12 if 2K >= 0.01), else the smallest of 8,
  * 16, 32 that all but 0.2 % of the cells fit (below 16384 cells if the mean
- * is at most 18), else 1 if the mean is at most 18, 21 or 26 (below 16384,
- * below 65536 cells, or more) or at least a quarter of the cells hold at
- * most 8 particles, else 0.  Errors: CUBA_EINVAL for NULL or any other value.
+ * is at most M), else 1 if the mean is at most M and few cells hold more
+ * than 32 (M = 10, 18, 21, 26 below 8192, 16384, 65536 cells and above) or,
+ * from 16384 cells, at least a quarter of the cells hold at most 8
+ * particles, else 0.  Errors: CUBA_EINVAL for NULL or any other value.
  * For an event in a batch use cuba_batch_set_cell_lanes (which takes
  * neither 1 nor 128). */
 int cuba_set_cell_lanes(cuba_ctx *ctx, int32_t lanes);

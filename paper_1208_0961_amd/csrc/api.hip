@@ -162,11 +162,15 @@ int derive(const cuba_params *p, int64_t n, Derived &d) {
 //   10 000          9.8/15.0  14.0/19.9  20.4/22.9  27.1/24.3
 //   40 000         14.1/36.0  27.4/51.9  52.5/61.6  61.3/67.7  77.8/72.9
 //   160 000        32.1/114   70.3/176   140/230    179/254    235/276   300/298
-// So packed cells (under whichever name: kPackedCells, 8, 16 or 32, which
-// also sets the lanes of the stream-bin kernel) below a mean of 18, 21 and
-// 26 for 4 096, 16 384 and 65 536 cells and more, if few cells exceed the 64
-// particles of a unit; and for boxes of dense and sparse regions (at least a
-// quarter of the cells with at most 8 particles).  Else one wave per cell.
+// (halves at one density ratio of 2; at a ratio of 8 the dense half decides:
+// 10 000 cells, mean 12 19.8/19.5, mean 16 27.8/21.5; 25 600, mean 12
+// 30.4/37.3, mean 16 42.3/40.7.)  So packed cells (under whichever name:
+// kPackedCells, 8, 16 or 32, which also sets the lanes of the stream-bin
+// kernel) below a mean of 10, 18, 21 and 26 for 4 096, 8 192, 16 384 and
+// 65 536 cells and more, if few cells exceed the 64 particles of a unit, and
+// in the smaller boxes few 32; and for boxes of dense and sparse regions (at
+// least a quarter of the cells with at most 8 particles).  Else one wave per
+// cell.
 // Except: on the plain path, a box of few dense cells takes several waves per
 // cell: fewer cells than the chip has SIMDs, most of them holding more than
 // 32 particles (100 cells of 100: 17 against 31 us a step, 900 of 33: 11
@@ -190,19 +194,21 @@ uint32_t default_lanes(const uint32_t over[4], int64_t n_cells, int64_t n, doubl
   const double limit = kOversizeFraction * (double)n_cells;
   const double mean = (double)n / (double)n_cells;
   if ((double)over[3] > limit) return 0;
-  const double packed_mean = !plain              ? 21.0
-                             : n_cells < 16384   ? 18.0
-                             : n_cells < 65536   ? 21.0
-                                                 : 26.0;
+  const double packed_mean = !plain            ? 21.0
+                             : n_cells < 8192  ? 10.0
+                             : n_cells < 16384 ? 18.0
+                             : n_cells < 65536 ? 21.0
+                                               : 26.0;
+  const double over32 = (double)over[2] / (double)n_cells;
+  const bool few32 = over32 <= (!plain ? 0.05 : n_cells < 16384 ? 0.03 : n_cells < 65536 ? 0.08 : 1.0);
   if (plain && (mean <= kPackedMean || (2.0 * kfac >= kHighTwoK && mean <= kPackedMeanHighK)))
     return kPackedCells;
   for (uint32_t k = 0; k < 3; ++k)
     if ((double)over[k] <= limit && (n_cells >= 16384 || mean <= packed_mean)) return 8u << k;
-  if (plain && (mean <= packed_mean ||
-                (double)(n_cells - over[0]) >= kSparseFraction * (double)n_cells))
+  if (mean <= packed_mean && few32) return plain ? kPackedCells : 32u;
+  if (plain && n_cells >= 16384 &&
+      (double)(n_cells - over[0]) >= kSparseFraction * (double)n_cells)
     return kPackedCells;
-  // (a batched event's dense half would fill its units badly)
-  if (!plain && mean <= packed_mean && (double)over[2] <= 0.05 * (double)n_cells) return 32;
   return 0;
 }
 
@@ -345,15 +351,25 @@ int apply_dt(cuba_ctx *c, double dt) {
 }
 
 // Cells a workgroup (four waves) of the packed kernel takes: 64, or fewer
-// while the box has too few workgroups to fill the chip and a workgroup more
-// particles than its waves take at once.  10 000 cells of 16: 64 us a step
-// in 157 tiles of 64 cells, 20 us in 1 250 of 8; 160 000 cells of 2: 32 us in
-// tiles of 64, 36 us in tiles of 32, whose waves are half idle.
-constexpr int64_t kPackedTiles = 1280, kPackedTileParticles = 160;
-uint32_t packed_tile(int64_t n, int64_t n_cells) {
+// while the box has too few workgroups to fill the chip and a workgroup of
+// its dense cells more particles than four units hold.  10 000 cells of 16:
+// 64 us a step in 157 tiles of 64 cells, 20 us in 1 250 of 8; 160 000 cells of
+// 2: 32 us in tiles of 64, 36 us in tiles of 32, whose waves are half idle.
+// The dense cells' occupancy: 7/4 of the mean, or a value of the densest class
+// of the initial histogram that holds an eighth of the cells (halves of 17
+// and 2 a cell on 6 848 cells: 21 us a step with tiles by the mean, 15 us with
+// tiles by the dense half, 17 us with one wave per cell).
+constexpr int64_t kPackedTiles = 1280, kPackedTileParticles = 224;
+uint32_t packed_tile(const uint32_t over[4], int64_t n, int64_t n_cells) {
+  int64_t dense = 7 * n / (4 * n_cells) + 1;
+  for (int k = 2; k >= 0; --k)
+    if (8 * (int64_t)over[k] >= n_cells) {
+      dense = 14 << k < dense ? dense : 14 << k;
+      break;
+    }
   uint32_t tile = 64;
-  while (tile > 8 && n_cells < (int64_t)tile * kPackedTiles &&
-         (int64_t)tile * n > kPackedTileParticles * n_cells)
+  while (tile > 4 && n_cells < (int64_t)tile * kPackedTiles &&
+         (int64_t)tile * dense > kPackedTileParticles)
     tile /= 2;
   return tile;
 }
@@ -370,7 +386,7 @@ uint32_t wide_waves(int64_t n, int64_t n_cells) {
 
 StepDevice step_device(const cuba_ctx *c) {
   return StepDevice{&c->consts->g, over_span(c->over, c->d.n_cells),
-                    packed_tile(c->n, c->d.n_cells), wide_waves(c->n, c->d.n_cells)};
+                    packed_tile(c->over, c->n, c->d.n_cells), wide_waves(c->n, c->d.n_cells)};
 }
 
 // The step launch's device arguments, with the stage's timing events.

@@ -208,7 +208,7 @@ struct StepDevice {
   // and steps the oversize ones one after another; few oversize cells) or 1
   // (a wave per cell; many)
   uint32_t over_span;
-  uint32_t tile;   // cells a workgroup of the packed kernel takes (8 .. 64)
+  uint32_t tile;   // cells a workgroup of the packed kernel takes (4 .. 64)
   uint32_t waves;  // waves per cell of the wide kernel: 4, 8 or 16
   // stage timing: events that the launch records at its start and end (on
   // its first kernel's dispatch when it is one kernel), or null
