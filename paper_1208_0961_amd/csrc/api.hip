@@ -252,7 +252,8 @@ struct cuba_ctx {
   int64_t n;
   uint32_t next_step;
   uint32_t lanes;  // lanes per cell of the cell kernels (valid_cell_lanes)
-  uint32_t over[4];  // cells of the initial state holding > 8, 16, 32, 64 particles
+  // cells of the initial state holding > 8, 16, 32, 64, kFitsSmall particles
+  uint32_t over[kOverClasses];
   hipStream_t stream;
   DevStatus *status;
   Cells buf[2];
@@ -374,6 +375,21 @@ uint32_t packed_tile(const uint32_t over[4], int64_t n, int64_t n_cells) {
   return tile;
 }
 
+// Whether the waves of four cells share their pairs (one wave per cell else):
+// the mean occupancy at least 50, 60 from 16 384 cells, and K mean^2, which is
+// half the filtered pairs of a mean cell or a quarter of a dense one's, at
+// most 10.5 (beyond, their exact tests and claims by few waves cost more than
+// the shared filter saves).  Speed-up over one wave per cell by the mean on
+// 11 323 / 40 000 cells at K mean^2 = 0.08 mean: 45 1.01 / 0.99, 57 1.04 /
+// 1.01, 70 1.05 / 1.02, 85 1.07 / 1.07, 105 1.10 / 1.09, 125 1.12 / 1.12; at
+// 0.16 mean: 57 1.03 / 1.01, 70 1.00 / 1.01, 85 0.99 / 1.00, 105 0.87 / 0.96;
+// 3 600 cells of 85: 0.97.
+constexpr int64_t kGroupMinCells = 6000;
+bool shares_pairs(int64_t n, int64_t n_cells, double kfac) {
+  const double mean = (double)n / (double)n_cells;
+  return mean >= (n_cells < 16384 ? 50.0 : 60.0) && kfac * mean * mean <= 10.5;
+}
+
 // Waves per cell of the wide kernel (us a step with 4 / 8 / 16 waves): 100
 // cells of 65: 12.4 / 12.8 / 12.9, of 200: 31.4 / 26.1 / 27.7, of 400: 85.0 /
 // 64.3 / 60.7; 400 cells of 200: 33.3 / 28.7 / 40.7; 900 cells of 100: 21.5 /
@@ -386,7 +402,9 @@ uint32_t wide_waves(int64_t n, int64_t n_cells) {
 
 StepDevice step_device(const cuba_ctx *c) {
   return StepDevice{&c->consts->g, over_span(c->over, c->d.n_cells),
-                    packed_tile(c->over, c->n, c->d.n_cells), wide_waves(c->n, c->d.n_cells)};
+                    packed_tile(c->over, c->n, c->d.n_cells), wide_waves(c->n, c->d.n_cells),
+                    c->d.n_cells >= kGroupMinCells && shares_pairs(c->n, c->d.n_cells, c->d.kfac),
+                    c->over[4] == 0};
 }
 
 // The step launch's device arguments, with the stage's timing events.
@@ -592,7 +610,7 @@ int init_context(cuba_ctx *c, const Derived &d, const cuba_params *params, int64
     return CUBA_OK;
   }
   hipError_t e = hipSuccess;
-  uint32_t head[5] = {0, 0, 0, 0, 0};  // err, over[4]
+  uint32_t head[1 + kOverClasses] = {};  // err, over
   static_assert(offsetof(DevStatus, over) == sizeof(uint32_t), "status layout");
   SpillDesc back[2];
   e = hipMemcpyAsync(head, &c->status->err, sizeof(head), hipMemcpyDeviceToHost, c->stream);
@@ -605,7 +623,7 @@ int init_context(cuba_ctx *c, const Derived &d, const cuba_params *params, int64
     if (std::memcmp(&back[b], &hsd[b], sizeof(SpillDesc)) != 0)
       return fail(CUBA_EDEVICE, "internal: spill descriptor not in place");
   const uint32_t err = head[0];
-  for (int k = 0; k < 4; ++k) c->over[k] = head[1 + k];
+  for (uint32_t k = 0; k < kOverClasses; ++k) c->over[k] = head[1 + k];
   c->lanes = default_lanes(c->over, d.n_cells, n, d.kfac, true);
   if (err & kErrRange)
     return fail(CUBA_ERANGE, "a particle is outside [0, L], non-finite, or has |p| = 0");
@@ -955,8 +973,8 @@ namespace {
 constexpr int32_t kMaxBatchSlots = 65535;
 
 // Work spaces of a batch: binning items, packed tiles, scans of their larger cells,
-// and the one-wave-per-cell spaces of small and large cell capacity.
-constexpr int kSpaces = 5;
+// the one-wave-per-cell spaces of small and large cell capacity, and groups.
+constexpr int kSpaces = 6;
 
 // Graphs of the old table: set aside (a launch of them may still be in
 // flight) and destroyed once the stream has been synchronized.
@@ -1020,7 +1038,16 @@ int32_t default_cpi(const cuba_ctx *c) {
 int upload_table(cuba_batch *b) {
   std::vector<BatchEvent> host;
   b->table_slots.clear();
-  uint64_t items = 0, tiles = 0, scans = 0, cells[2] = {0, 0};
+  uint64_t items = 0, tiles = 0, scans = 0, cells[3] = {0, 0, 0};
+  // the events whose waves share their cells' pairs, if they fill the chip
+  const auto shares = [&](int32_t s) {
+    const cuba_ctx *c = b->slot_ctx[s];
+    return c && b->slot_active[s] && c->lanes == 0 && c->d.n_cells > 0 &&
+           c->d.cap <= kSmallCap && shares_pairs(c->n, c->d.n_cells, c->d.kfac);
+  };
+  int64_t shared_cells = 0;
+  for (int32_t s = 0; s < b->max_slots; ++s)
+    if (shares(s)) shared_cells += b->slot_ctx[s]->d.n_cells;
   uint32_t obs_nx = 0;
   std::vector<int> cell_space;
   for (int32_t s = 0; s < b->max_slots; ++s) {
@@ -1045,7 +1072,9 @@ int upload_table(cuba_batch *b) {
       e.obs_vol = c->d.vol;
       if ((uint32_t)c->d.g.n[0] > obs_nx) obs_nx = (uint32_t)c->d.g.n[0];
     }
-    const int space = c->d.cap <= kSmallCap ? 0 : 1;
+    const int space = c->d.cap > kSmallCap                               ? 1
+                      : shared_cells >= kGroupMinCells && shares(s) ? 2
+                                                                    : 0;
     e.item_begin = (uint32_t)items;
     e.tile = event_tile(c->n, c->d.n_cells);
     e.tile_begin = (uint32_t)tiles;
@@ -1056,7 +1085,7 @@ int upload_table(cuba_batch *b) {
       tiles += (e.n_cells + e.tile - 1) / e.tile;
       if (space == 1) scans += (e.n_cells + 63) / 64;
     } else {
-      cells[space] += e.n_cells;
+      cells[space] += space == 2 ? (e.n_cells + kGroup - 1) / kGroup : e.n_cells;
     }
     // grid sizes stay below 2^31 workgroups
     if (items >= 0x80000000ull || tiles >= 0x80000000ull || cells[0] >= 0x80000000ull ||
@@ -1073,24 +1102,27 @@ int upload_table(cuba_batch *b) {
   b->spaces.scan_begin = b->dev_begin + 2 * stride;
   b->spaces.cell_begin[0] = b->dev_begin + 3 * stride;
   b->spaces.cell_begin[1] = b->dev_begin + 4 * stride;
+  b->spaces.group_begin = b->dev_begin + 5 * stride;
   b->spaces.n_items = (uint32_t)items;
   b->spaces.n_tiles = (uint32_t)tiles;
   b->spaces.n_scans = (uint32_t)scans;
   b->spaces.n_cells[0] = (uint32_t)cells[0];
   b->spaces.n_cells[1] = (uint32_t)cells[1];
+  b->spaces.n_groups = (uint32_t)cells[2];
   b->spaces.obs_nx = obs_nx;
   if (ne > 0) {
     // an event outside a cells space gets that space's running total (the
     // next event's begin), so the lookup never lands on it
     std::vector<uint32_t> begins(kSpaces * stride, 0u);
-    uint32_t run[2] = {0, 0};
+    uint32_t run[3] = {0, 0, 0};
     for (size_t i = 0; i < ne; ++i) {
       begins[i] = host[i].item_begin;
       begins[stride + i] = host[i].tile_begin;
       begins[2 * stride + i] = host[i].scan_begin;
-      for (int sp = 0; sp < 2; ++sp) {
+      for (int sp = 0; sp < 3; ++sp) {
         begins[(3 + sp) * stride + i] = run[sp];
-        if (cell_space[i] == sp) run[sp] += host[i].n_cells;
+        if (cell_space[i] == sp)
+          run[sp] += sp == 2 ? (host[i].n_cells + kGroup - 1) / kGroup : host[i].n_cells;
       }
     }
     // through pinned staging, in stream order, without waiting for the

@@ -58,11 +58,12 @@ __device__ __forceinline__ Words4 philox10(uint32_t x0, uint32_t x1, uint32_t x2
 // in full; then round 7 needs hi(A) and B, round 8 lo(A) and hi(B), round 9
 // hi(A), round 10 lo(B).  16 vector multiplies instead of 20 (fewer when
 // the counter's cell, step and purpose words are wave-uniform).
-__device__ __forceinline__ uint32_t philox10_w1(uint32_t x0, uint32_t x1, uint32_t x2,
-                                                uint32_t x3, uint32_t key0,
-                                                uint32_t key1) {
+// philox_w1_from: the same after the first kDone rounds.
+template <uint32_t kDone>
+__device__ __forceinline__ uint32_t philox_w1_from(uint32_t x0, uint32_t x1, uint32_t x2,
+                                                   uint32_t x3, uint32_t key0, uint32_t key1) {
 #pragma unroll
-  for (uint32_t r = 0; r < 6; ++r)
+  for (uint32_t r = kDone; r < 6; ++r)
     philox_round(x0, x1, x2, x3, key0 + r * kWeylA, key1 + r * kWeylB);
   {  // round 7
     const uint32_t ha = __umulhi(x0, kMulA);
@@ -83,6 +84,11 @@ __device__ __forceinline__ uint32_t philox10_w1(uint32_t x0, uint32_t x1, uint32
   return x2 * kMulB;
 }
 
+__device__ __forceinline__ uint32_t philox10_w1(uint32_t x0, uint32_t x1, uint32_t x2,
+                                                uint32_t x3, uint32_t key0,
+                                                uint32_t key1) {
+  return philox_w1_from<0>(x0, x1, x2, x3, key0, key1);
+}
 // 53-bit uniform in [0, 1) from two words (hi:lo).
 __device__ __forceinline__ double uniform53(uint32_t lo, uint32_t hi) {
   const uint64_t bits = ((((uint64_t)hi) << 32) | lo) >> 11;

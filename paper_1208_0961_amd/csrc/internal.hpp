@@ -12,6 +12,8 @@ namespace cuba {
 
 constexpr uint32_t kCellCap = 1024;  // = CUBA_MAX_CELL_OCCUPANCY
 constexpr uint32_t kSmallCap = 512;  // cell kernels with half the LDS
+constexpr uint32_t kFitsSmall = 384;  // a box whose cells hold at most this at init
+                                      // rarely exceeds kSmallCap later
 constexpr uint32_t kScanTile = 2048; // counts per scan tile
 
 // Device-side error bits, accumulated until the next cuba_sync.
@@ -84,10 +86,12 @@ struct OverflowPool {
 // counters are spread over kCounterSlots slots (by cell) so that the
 // per-cell atomics of the collision kernel do not contend on one address.
 constexpr uint32_t kCounterSlots = 256;
+constexpr uint32_t kOverClasses = 5;
 struct DevStatus {
   uint32_t err;
-  uint32_t over[4];  // cells holding more than 8, 16, 32, 64 particles (filled at init)
-  uint32_t pad[59];
+  uint32_t over[kOverClasses];  // cells holding more than 8, 16, 32, 64, kFitsSmall
+                                // particles (filled at init)
+  uint32_t pad[63 - kOverClasses];
   unsigned long long pairs[kCounterSlots];   // pair tests
   unsigned long long cand[kCounterSlots];    // pairs with u < P22
   unsigned long long claims[kCounterSlots];  // scatterings
@@ -127,7 +131,8 @@ struct BatchEvent {
   uint32_t tile_begin;  // first of its tiles
   uint32_t scan_begin;  // first scan unit (64 cells), if lanes > 0 and cap > kSmallCap
   uint32_t cell_begin;  // first unit in its one-wave-per-cell space, if lanes = 0
-                        // (space 0: cell capacity <= kSmallCap, space 1: larger)
+                        // (space 0: cell capacity <= kSmallCap, space 1: larger,
+                        // space 2: groups)
   // observation inside runs: after each step s with (s + 1) % obs_every == 0
   // (obs_every > 0), the collision launch writes the per-cell sums into
   // obs_sums and a slab launch writes T00 and T0x into row
@@ -142,8 +147,8 @@ struct BatchEvent {
 // The work spaces of a batch run (see launch_batch_run): unit counts and,
 // per event in table order, the first unit of each space (device arrays).
 struct BatchSpaces {
-  const uint32_t *item_begin, *tile_begin, *scan_begin, *cell_begin[2];
-  uint32_t n_items, n_tiles, n_scans, n_cells[2];
+  const uint32_t *item_begin, *tile_begin, *scan_begin, *cell_begin[2], *group_begin;
+  uint32_t n_items, n_tiles, n_scans, n_cells[2], n_groups;
   uint32_t obs_nx;  // > 0: some event observes inside runs; its largest nx
 };
 
@@ -152,6 +157,7 @@ struct BatchSpaces {
 // number is the stream-bin kernel's lanes per cell, 16 for kPackedCells) or
 // kWideCells (a workgroup of several waves per cell; plain path only, as is
 // kPackedCells by that name).
+constexpr uint32_t kGroup = 4;  // cells whose waves may share their pairs
 constexpr uint32_t kPackedCells = 1;
 constexpr uint32_t kWideCells = 128;
 inline bool valid_cell_lanes(int32_t v) {
@@ -210,6 +216,8 @@ struct StepDevice {
   uint32_t over_span;
   uint32_t tile;   // cells a workgroup of the packed kernel takes (4 .. 64)
   uint32_t waves;  // waves per cell of the wide kernel: 4, 8 or 16
+  bool group;      // waves of four cells share their pairs (lanes = 0, small LDS)
+  bool fits_small; // the cells hold at most kFitsSmall particles at init
   // stage timing: events that the launch records at its start and end (on
   // its first kernel's dispatch when it is one kernel), or null
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
@@ -225,8 +233,8 @@ void launch_step(const Cells &src, const Cells &dst, bool fused, int64_t n_cells
                  uint32_t lanes, uint32_t t, const PairArgs &pa, const Geometry &g, DevStatus *status,
                  const TraceArgs *trace, hipStream_t s, const SideStream *side,
                  const StepDevice &dev);
-// Counts the cells of cur holding more than 8, 16, 32 and 64 particles into
-// status->over (which must be zero).
+// Counts the cells of cur holding more than 8, 16, 32, 64 and kFitsSmall
+// particles into status->over (which must be zero).
 void launch_occupancy_over(const Cells &cur, int64_t n_cells, DevStatus *status, hipStream_t s);
 // Per-slab outputs of an observation (each may be NULL): T00, T0x, Txx
 // [GeV/fm^3], density n [fm^-3], rest-frame e [GeV/fm^3] and v.

@@ -432,26 +432,27 @@ __global__ __launch_bounds__(kBlock) void k_init_bin(
     store_particle(dst, cell, atomic_add(dst.count + cell, 1u), q, status);
 }
 
-// Cells holding more than 8, 16, 32 and 64 particles, added into over[4]:
-// a grid stride over the cells, counts kept per wave, summed per block in
-// LDS, then four atomics per block (one atomic per wave and counter
-// serialised on the four addresses at 2 M cells).
+// Cells holding more than 8, 16, 32, 64 and kFitsSmall particles, added into
+// over[5]: a grid stride over the cells, counts kept per wave, summed per
+// block in LDS, then an atomic per class and block (one atomic per wave and
+// counter serialised on the addresses at 2 M cells).
 __global__ __launch_bounds__(kBlock) void k_occupancy_over(Cells cur_arg, uint32_t n_cells,
                                                            uint32_t *over) {
   const GCells cur = to_global(cur_arg);
-  __shared__ uint32_t part[kBlock / 64][4];
-  uint32_t acc[4] = {0u, 0u, 0u, 0u};
+  __shared__ uint32_t part[kBlock / 64][kOverClasses];
+  uint32_t acc[kOverClasses] = {};
   for (uint32_t c0 = blockIdx.x * kBlock; c0 < n_cells; c0 += gridDim.x * kBlock) {
     const uint32_t c = c0 + threadIdx.x;
     const uint32_t n = c < n_cells ? cur.count[c] : 0u;
 #pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) acc[k] += (uint32_t)__popcll(__ballot(n > (8u << k)));
+    for (uint32_t k = 0; k < kOverClasses; ++k)
+      acc[k] += (uint32_t)__popcll(__ballot(n > (k < 4u ? 8u << k : kFitsSmall)));
   }
   const uint32_t w = threadIdx.x / 64;
   if (lane_id() == 0)
-    for (uint32_t k = 0; k < 4; ++k) part[w][k] = acc[k];
+    for (uint32_t k = 0; k < kOverClasses; ++k) part[w][k] = acc[k];
   __syncthreads();
-  if (threadIdx.x < 4) {
+  if (threadIdx.x < kOverClasses) {
     uint32_t sum = 0;
     for (uint32_t i = 0; i < kBlock / 64; ++i) sum += part[i][threadIdx.x];
     if (sum != 0) atomicAdd(&over[threadIdx.x], sum);
@@ -927,7 +928,7 @@ __device__ void find_spilled(const GCells &src, const CellView &cv, CellLds<kFus
   const uint64_t below = (1ull << lane) - 1ull;
   const SpillDesc *const sd = src.sp;
   OverflowPool *const pool = sd->pool;
-  const uint32_t n = cv.n, nsp = n - cv.cap;
+  const uint32_t n = cv.n, nsp = cv.ov ? n - cv.cap : 0u;
   const uint32_t ns = min(sd->hdr[2u * src.q], sd->capacity);
   uint64_t need = nsp;
   if (n > kCap) need += (uint64_t)n + n / 2u + 1u + (n + 31u) / 32u;
@@ -944,7 +945,7 @@ __device__ void find_spilled(const GCells &src, const CellView &cv, CellLds<kFus
   if (ok) {
     uint32_t *const mem = pool->buf + b;
     uint32_t found = 0;
-    for (uint32_t i0 = 0; i0 < ns; i0 += 64u) {
+    for (uint32_t i0 = 0; nsp != 0u && i0 < ns; i0 += 64u) {
       const uint32_t i = i0 + lane;
       const bool hit = i < ns && sd->cell[i] == cv.c;
       const uint64_t mk = __ballot(hit);
@@ -964,7 +965,7 @@ __device__ void find_spilled(const GCells &src, const CellView &cv, CellLds<kFus
   }
 }
 
-// The collisions of an overflowing cell larger than the LDS holds (then,
+// The collisions of a cell larger than the LDS holds (then,
 // kFused, the binning of its members), by one wave with its canonical
 // order, claimed flags and claims in global scratch: ranks by counting
 // smaller ids against chunks staged in LDS, pair tests 64 at a time in
@@ -978,7 +979,7 @@ __device__ void large_cell_step(const GCells &src, const GCells &dst, const Cell
                                 double *obs) {
   const uint32_t lane = lane_id();
   const uint32_t n = cv.n;
-  uint32_t *const perm = const_cast<uint32_t *>(cv.sidx) + (n - cv.cap);
+  uint32_t *const perm = const_cast<uint32_t *>(cv.sidx) + (cv.ov ? n - cv.cap : 0u);
   uint32_t *const claims = perm + n;
   uint32_t *const bits = claims + n / 2u + 1u;
   const GState &st = src.st;
@@ -1117,43 +1118,73 @@ __device__ void large_cell_step(const GCells &src, const GCells &dst, const Cell
   if (obs) obs_write_wave(obs, cv.c, n, se, sp, sxx);
 }
 
-// Collisions of cell c of src at step t by one wave.  kFused: afterwards
-// stream and bin the cell's particles into dst for step t+1 and clear src's
-// count.  Starts with a barrier, so a wave may call it for several cells.
+// A fused step of a cell whose members are all in its block keeps the new
+// momenta of up to kMax claims in LDS (where the rank sorted its ids; claim
+// i's two members at 2i, 2i + 1, and by member a byte map to them, in the
+// rank's buckets) for its binning, instead of writing them back to the
+// source block, whose lines would then be written to memory once more though
+// no one reads them again.
+template <uint32_t kCap>
+struct ClaimLds {
+  static constexpr uint32_t kMax = kCap / 12u;  // 6 doubles a claim in sorted[]
+  static_assert(6u * kMax * sizeof(double) <= kCap * sizeof(uint32_t), "claim momenta");
+  static_assert(2u * kMax + 2u <= 255u && kCap <= 4u * (kRankBuckets + 4u), "claim map");
+  double *mx, *my, *mz;
+  uint8_t *map;
+  template <bool kFused>
+  __device__ __forceinline__ explicit ClaimLds(CellLds<kFused, kCap> &lds)
+      : mx(reinterpret_cast<double *>(lds.sorted)), my(mx + 2u * kMax), mz(my + 2u * kMax),
+        map(reinterpret_cast<uint8_t *>(lds.bkt)) {}
+  // claim i's new momenta, of members ja and jb
+  __device__ __forceinline__ void put(uint32_t i, uint32_t ja, uint32_t jb, double ax, double ay,
+                                      double az, double bx, double by, double bz) const {
+    mx[2u * i] = ax;
+    my[2u * i] = ay;
+    mz[2u * i] = az;
+    mx[2u * i + 1u] = bx;
+    my[2u * i + 1u] = by;
+    mz[2u * i + 1u] = bz;
+    map[ja] = (uint8_t)(2u * i + 1u);
+    map[jb] = (uint8_t)(2u * i + 2u);
+  }
+  // member j's new momentum, if it has one
+  __device__ __forceinline__ void take(uint32_t j, Particle &q) const {
+    const uint32_t m = map[j];
+    if (m != 0u) {
+      q.px = mx[m - 1u];
+      q.py = my[m - 1u];
+      q.pz = mz[m - 1u];
+    }
+  }
+};
+
+// A cell's step by one wave runs in three parts: cell_open (canonical order),
+// cell_pairs (pair tests, claims, kinematics) and cell_close (observation
+// sums, streaming and binning).
+struct CellWork {
+  CellView cv;
+  bool live;     // the later parts are still to do
+  bool mom_lds;  // new momenta are in LDS, not written back
+};
+
+// Part 1: the cell's view, and its canonical order in lds.perm.  A cell
+// larger than the LDS holds is stepped here altogether.  Starts with a
+// barrier, so a wave may call it for several cells.
 // kBlk: the workgroup is this one wave; else the wave shares it with others
 // and synchronises with itself only.
-template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk = true>
-__device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, uint32_t c,
-                                          uint32_t t, const PairArgs &pa,
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk>
+__device__ __forceinline__ void cell_open(CellWork &w, const GCells &src, const GCells &dst,
+                                          uint32_t c, uint32_t t, const PairArgs &pa,
                                           const Geometry &g, DevStatus *status,
                                           const TraceArgs &tr, CellLds<kFused, kCap> &lds,
-                                          double *obs = nullptr) {
-  // filtered pairs and claimed pairs share the id buffer, kCap / 2 each
-  constexpr uint32_t kFilt = kCap / 2;
-  static_assert(kCap <= kCellCap && kFilt >= 256, "cell capacity");
+                                          double *obs) {
+  w.live = false;
+  w.mom_lds = false;
   uint32_t *const s_id = lds.buf;
-  uint32_t *const s_filt = lds.buf;
-  uint32_t *const s_claim = lds.buf + kFilt;
   uint16_t *const s_perm = lds.perm;
   cell_sync<kBlk>();
-  // A fused step of a cell whose members are all in its block
-  // keeps the new momenta of up to kMomCap claims in LDS (where the rank
-  // sorted its ids; claim i's two members at 2i, 2i + 1, and by member a
-  // byte map to them, in the rank's buckets) for its binning, instead of
-  // writing them back to the source block, whose lines would then be
-  // written to memory once more though no one reads them again.
-  constexpr bool kMomInLds = kFused;
-  constexpr uint32_t kMomCap = kCap / 12u;  // 6 doubles a claim in sorted[]
-  static_assert(6u * kMomCap * sizeof(double) <= kCap * sizeof(uint32_t), "claim momenta");
-  static_assert(2u * kMomCap + 2u <= 255u && kCap <= 4u * (kRankBuckets + 4u), "claim map");
-  double *const s_mx = reinterpret_cast<double *>(lds.sorted);
-  double *const s_my = s_mx + 2u * kMomCap;
-  double *const s_mz = s_my + 2u * kMomCap;
-  uint8_t *const s_cmap = reinterpret_cast<uint8_t *>(lds.bkt);
-  bool mom_lds = false;
-
   const uint32_t lane = lane_id();
-  CellView cv;
+  CellView &cv = w.cv;
   cv.c = c;
   cv.t = t;
   cv.base = (size_t)cv.c * src.cap;
@@ -1169,9 +1200,10 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
   // issue ahead of the other waves' pair-test loops, which keep the VALU
   // busy meanwhile; the pair tests run at the base priority.
   __builtin_amdgcn_s_setprio(1);
-  if (cv.ov) {
-    // an overflowing cell: find its spilled members, then step it
-    // here, in LDS if it fits, else with the global-memory method
+  if (cv.ov || cv.n > kCap) {
+    // an overflowing cell: find its spilled members, then step it here, in
+    // LDS if it fits, else (as any cell larger than the LDS) with the
+    // global-memory method
     find_spilled<kFused, kCap>(src, cv, lds, status);
     cell_sync<kBlk>();
     if (lds.ov_ok == 0u) return;  // internal error, flagged
@@ -1185,9 +1217,7 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
   }
   const uint32_t n = cv.n;
   const GState &st = src.st;
-  double *const ob = obs;
-
-  uint32_t nclaim = 0;
+  w.live = true;
   if (n >= 2) {
     // ids to LDS, padded to a multiple of 4 with an id no particle has
     const uint32_t n4 = (n + 3u) & ~3u;
@@ -1266,89 +1296,109 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
     if (cv.ov) {  // the members' slots, in LDS (the rank no longer needs it)
       for (uint32_t j = lane; j < n; j += 64u) lds.sorted[j] = (uint32_t)cv.at_spill(j);
       cell_sync<kBlk>();
-    } else if (kMomInLds) {
+    } else if (!kTrace) {
       // the claim map (one byte a member, zero: not scattered), in the
       // rank's buckets; the barrier after the pair tests orders it
       for (uint32_t j = lane * 4u; j < n; j += 256u)
-        *reinterpret_cast<uint32_t *>(s_cmap + j) = 0u;
+        *reinterpret_cast<uint32_t *>(ClaimLds<kCap>(lds).map + j) = 0u;
     }
-
-    // every pair k = 0 .. n(n-1)/2 - 1 (test_pairs), then the exact test
-    // and the claims of the filtered ones in increasing k
-    const uint32_t npairs = n * (n - 1u) / 2u;
-    uint32_t nf = 0, claimed_bits = 0, n_acc = 0;
-    __builtin_amdgcn_s_setprio(0);
-    if (pa.any)
-      test_pairs<true, kTrace, kBlk, kFilt>(0u, npairs, cv, pa, st, s_perm, s_filt, nf, s_claim,
-                                            nclaim, claimed_bits, n_acc, tr, status);
-    if (nf != 0)
-      resolve_filtered<kTrace, kBlk>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
-                                     claimed_bits, n_acc, tr, status);
-    cell_sync<kBlk>();
-
-    __builtin_amdgcn_s_setprio(1);
-    // work counters (spread over slots by cell against contention)
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) n_acc += __shfl_down(n_acc, o);
-    if (lane == 0) {
-      const uint32_t slot = cv.c % kCounterSlots;
-      atomicAdd(&status->pairs[slot], (unsigned long long)npairs);
-      atomicAdd(&status->cand[slot], (unsigned long long)n_acc);
-      atomicAdd(&status->claims[slot], (unsigned long long)nclaim);
-    }
-
-    // kinematics of the claimed pairs (disjoint: one writer per particle),
-    // written back in place, or for the binning below into LDS; a fused
-    // step then bins every particle
-    mom_lds = kMomInLds && !cv.ov && nclaim <= kMomCap;
-    for (uint32_t i0 = 0; i0 < nclaim; i0 += 64u) {
-      const uint32_t i = i0 + lane;
-      const bool active = i < nclaim;
-      double ax = 0, ay = 0, az = 0, bx = 0, by = 0, bz = 0;
-      uint32_t ja = 0, jb = 0;
-      if (active) {
-        const uint32_t v = s_claim[i];
-        const uint32_t a = (v >> 10) & 1023u, b = v & 1023u;
-        const uint32_t k = row_start(a, n) + (b - a - 1u);
-        const Words4 w = philox10(k, cv.c, t, 1u, pa.key0, pa.key1);
-        const double uc = uniform53(w.w0, w.w1);
-        const double uphi = uniform53(w.w2, w.w3);
-        ja = s_perm[a];
-        jb = s_perm[b];
-        const size_t ia = cv.at(ja), ib = cv.at(jb);
-        load_momentum(st, ia, ax, ay, az);
-        load_momentum(st, ib, bx, by, bz);
-        scatter_pair(ax, ay, az, bx, by, bz, uc, uphi);
-        if (mom_lds) {
-          s_mx[2u * i] = ax;
-          s_my[2u * i] = ay;
-          s_mz[2u * i] = az;
-          s_mx[2u * i + 1u] = bx;
-          s_my[2u * i + 1u] = by;
-          s_mz[2u * i + 1u] = bz;
-          s_cmap[ja] = (uint8_t)(2u * i + 1u);
-          s_cmap[jb] = (uint8_t)(2u * i + 2u);
-        } else {
-          put_momentum(st, ia, ax, ay, az);
-          put_momentum(st, ib, bx, by, bz);
-        }
-        if (kTrace && tr.claim) {
-          const uint32_t slot = atomicAdd(&tr.counts[1], 1u);
-          if (slot < tr.claim_cap) {
-            tr.claim[3 * (size_t)slot + 0] = cv.c;
-            tr.claim[3 * (size_t)slot + 1] = a;
-            tr.claim[3 * (size_t)slot + 2] = b;
-          } else {
-            atomicOr(&status->err, kErrTrace);
-          }
-        }
-      }
-    }
-    if (kFused || ob) cell_sync<kBlk>();
   } else if (kTrace && n == 1 && lane == 0 && tr.perm) {
     tr.perm[tr.offsets[cv.c]] = st.id[cv.at_spill(0)];
   }
+}
 
+// Part 2.
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk>
+__device__ __forceinline__ void cell_pairs(CellWork &w, const GCells &src, const PairArgs &pa,
+                                           DevStatus *status, const TraceArgs &tr,
+                                           CellLds<kFused, kCap> &lds, const double *obs) {
+  const CellView &cv = w.cv;
+  const uint32_t lane = lane_id(), n = cv.n;
+  const GState &st = src.st;
+  if (n < 2u) return;
+  // filtered pairs and claimed pairs share the id buffer, kCap / 2 each
+  constexpr uint32_t kFilt = kCap / 2, kMomCap = ClaimLds<kCap>::kMax;
+  static_assert(kCap <= kCellCap && kFilt >= 256, "cell capacity");
+  uint32_t *const s_filt = lds.buf;
+  uint32_t *const s_claim = lds.buf + kFilt;
+  const uint16_t *const s_perm = lds.perm;
+  const ClaimLds<kCap> cl(lds);
+  uint32_t nclaim = 0;
+      // every pair k = 0 .. n(n-1)/2 - 1 (test_pairs), then the exact test
+      // and the claims of the filtered ones in increasing k
+      const uint32_t npairs = n * (n - 1u) / 2u;
+      uint32_t nf = 0, claimed_bits = 0, n_acc = 0;
+      __builtin_amdgcn_s_setprio(0);
+      if (pa.any)
+        test_pairs<true, kTrace, kBlk, kFilt>(0u, npairs, cv, pa, st, s_perm, s_filt, nf, s_claim,
+                                              nclaim, claimed_bits, n_acc, tr, status);
+      if (nf != 0)
+        resolve_filtered<kTrace, kBlk>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
+                                       claimed_bits, n_acc, tr, status);
+      cell_sync<kBlk>();
+
+      __builtin_amdgcn_s_setprio(1);
+      // work counters (spread over slots by cell against contention)
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) n_acc += __shfl_down(n_acc, o);
+      if (lane == 0) {
+        const uint32_t slot = cv.c % kCounterSlots;
+        atomicAdd(&status->pairs[slot], (unsigned long long)npairs);
+        atomicAdd(&status->cand[slot], (unsigned long long)n_acc);
+        atomicAdd(&status->claims[slot], (unsigned long long)nclaim);
+      }
+
+      // kinematics of the claimed pairs (disjoint: one writer per particle),
+      // written back in place, or for the binning below into LDS; a fused
+      // step then bins every particle
+      w.mom_lds = kFused && !cv.ov && nclaim <= kMomCap;
+      for (uint32_t i0 = 0; i0 < nclaim; i0 += 64u) {
+        const uint32_t i = i0 + lane;
+        const bool active = i < nclaim;
+        double ax = 0, ay = 0, az = 0, bx = 0, by = 0, bz = 0;
+        uint32_t ja = 0, jb = 0;
+        if (active) {
+          const uint32_t v = s_claim[i];
+          const uint32_t a = (v >> 10) & 1023u, b = v & 1023u;
+          const uint32_t k = row_start(a, n) + (b - a - 1u);
+          const Words4 u = philox10(k, cv.c, cv.t, 1u, pa.key0, pa.key1);
+          ja = s_perm[a];
+          jb = s_perm[b];
+          const size_t ia = cv.at(ja), ib = cv.at(jb);
+          load_momentum(st, ia, ax, ay, az);
+          load_momentum(st, ib, bx, by, bz);
+          scatter_pair(ax, ay, az, bx, by, bz, uniform53(u.w0, u.w1), uniform53(u.w2, u.w3));
+          if (w.mom_lds) {
+            cl.put(i, ja, jb, ax, ay, az, bx, by, bz);
+          } else {
+            put_momentum(st, ia, ax, ay, az);
+            put_momentum(st, ib, bx, by, bz);
+          }
+          if (kTrace && tr.claim) {
+            const uint32_t slot = atomicAdd(&tr.counts[1], 1u);
+            if (slot < tr.claim_cap) {
+              tr.claim[3 * (size_t)slot + 0] = cv.c;
+              tr.claim[3 * (size_t)slot + 1] = a;
+              tr.claim[3 * (size_t)slot + 2] = b;
+            } else {
+              atomicOr(&status->err, kErrTrace);
+            }
+          }
+        }
+      }
+      if (kFused || obs) cell_sync<kBlk>();
+}
+
+// Part 3 (with kFused clears src's count).
+template <bool kFused, uint32_t kCap>
+__device__ __forceinline__ void cell_close(const CellWork &w, const GCells &src,
+                                           const GCells &dst, const Geometry &g,
+                                           DevStatus *status, CellLds<kFused, kCap> &lds,
+                                           double *obs) {
+  const CellView &cv = w.cv;
+  const uint32_t lane = lane_id(), n = cv.n;
+  const GState &st = src.st;
+  const ClaimLds<kCap> cl(lds);
   if (kFused) {
     // stream and bin every particle (scattered momenta are in LDS or were
     // written back in place; the barrier above makes them visible to all
@@ -1369,15 +1419,10 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
       bool near = true;
       if (active) {
         q = load_particle(st, cv.at(j));
-        if (mom_lds) {
-          const uint32_t m = s_cmap[j];
-          if (m != 0u) {
-            q.px = s_mx[m - 1u];
-            q.py = s_my[m - 1u];
-            q.pz = s_mz[m - 1u];
-          }
+        if (w.mom_lds) {
+          cl.take(j, q);
         }
-        if (ob) obs_add(q.px, q.py, q.pz, se, sp, sxx);
+        if (obs) obs_add(q.px, q.py, q.pz, se, sp, sxx);
         advance<true>(g_l, q.x, q.y, q.z, q.px, q.py, q.pz);
         int32_t ix, iy, iz;
         cell_axes(g_l, q.x, q.y, q.z, ix, iy, iz);
@@ -1395,8 +1440,8 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
       }
     }
     if (lane == 0) src.count[cv.c] = 0u;
-    if (ob) obs_write_wave(ob, cv.c, n, se, sp, sxx);
-  } else if (ob) {
+    if (obs) obs_write_wave(obs, cv.c, n, se, sp, sxx);
+  } else if (obs) {
     double se = 0.0, sp = 0.0, sxx = 0.0;
     for (uint32_t j = lane; j < n; j += 64u) {
       const size_t o = cv.at(j);
@@ -1404,8 +1449,294 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
       load_momentum(st, o, px, py, pz);
       obs_add(px, py, pz, se, sp, sxx);
     }
-    obs_write_wave(ob, cv.c, n, se, sp, sxx);
+    obs_write_wave(obs, cv.c, n, se, sp, sxx);
   }
+}
+
+// Collisions of cell c of src at step t by one wave.  kFused: afterwards
+// stream and bin the cell's particles into dst for step t+1 and clear src's
+// count.
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk = true>
+__device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, uint32_t c,
+                                          uint32_t t, const PairArgs &pa,
+                                          const Geometry &g, DevStatus *status,
+                                          const TraceArgs &tr, CellLds<kFused, kCap> &lds,
+                                          double *obs = nullptr) {
+  CellWork w;
+  cell_open<kFused, kTrace, kCap, kBlk>(w, src, dst, c, t, pa, g, status, tr, lds, obs);
+  if (!w.live) return;
+  cell_pairs<kFused, kTrace, kCap, kBlk>(w, src, pa, status, tr, lds, obs);
+  cell_close<kFused, kCap>(w, src, dst, g, status, lds, obs);
+}
+
+// ---------------------------------------------------------------------------
+// Four cells by a workgroup of four waves (boxes of many dense cells).  Wave
+// w opens and closes cell c0 + w as above; in between the waves share the
+// four cells' pairs:
+//   filter      the waves take the rows of 64 pair indices in turn, each
+//               testing its indices in all four cells: what rounds 1 to 3 of
+//               Philox owe to the index alone (three of a test's 16
+//               multiplies, two of its 15 XORs) is computed once for the
+//               four.  Passing pairs go to their cell's list in any order;
+//   the rest    one wave sorts the ~40 filtered pairs by cell and index, tests
+//               them exactly, claims, and computes the kinematics, a pair a
+//               lane in one row, where each cell alone fills a few lanes of a
+//               row in each of these.
+// A cell whose list would exceed kListMax (or that overflows its block, or
+// that holds no pair) is left out and taken by its own wave alone.
+// Bound by VALU issue on the full tube (a wave per cell: 98 % busy).  Against
+// one wave per cell: 684 -> 577 M VALU instructions a launch there, 1.23 ->
+// 1.12 ms; 3-D tube's 50 steps 4.82 -> 4.33 ms (96 -> 87 us a step).  Two
+// cells to a workgroup gained half of that, and one LDS atomic a row for all
+// four lists, instead of one a list, less than four.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kListMax = 40;  // <= ClaimLds::kMax: every claim's momenta fit
+template <uint32_t kG>
+struct GroupLds {
+  uint32_t n[kG];    // members of the cells that share their pairs, else 0
+  uint32_t cnt[kG];  // filtered pairs
+  __align__(16) uint32_t list[kG][kListMax];  // unused entries all ones
+  uint32_t sorted[kG * kListMax];  // the exact test's results, by cell and index
+};
+
+// Filter rows wv, wv + kG, ... of the cells c0 .. c0 + 3 (np pairs each).
+template <uint32_t kG>
+__device__ __forceinline__ void group_filter(uint32_t c0, uint32_t t, const uint32_t *np,
+                                             const PairArgs &pa, GroupLds<kG> &q, uint32_t wv) {
+  const uint32_t lane = lane_id(), lim = pa.w1_max;
+  const uint64_t tb = (uint64_t)t * kMulB;
+  uint32_t s2[kG], s3[kG];  // what the cell adds to word 2 in rounds 2 and 3
+#pragma unroll
+  for (uint32_t i = 0; i < kG; ++i) {
+    const uint64_t ca = (uint64_t)((uint32_t)(tb >> 32) ^ (c0 + i) ^ pa.key0) * kMulA;
+    s2[i] = (uint32_t)(ca >> 32) ^ (pa.key1 + kWeylB);
+    s3[i] = (uint32_t)ca ^ (pa.key1 + 2u * kWeylB);
+  }
+  const uint32_t e2 = (uint32_t)tb ^ (pa.key0 + kWeylA), e3 = pa.key0 + 2u * kWeylA;
+  const auto uniform = [](uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+  };
+  uint32_t most = np[0], least = np[0];
+#pragma unroll
+  for (uint32_t i = 1; i < kG; ++i) {
+    most = max(most, np[i]);
+    least = min(least, np[i]);
+  }
+  most = uniform(most);
+  least = uniform(least);
+  // word w1 of index k in cell i, from the shared products
+  const auto word = [&](uint32_t i, uint64_t ka, uint64_t kb, uint64_t kc) {
+    const uint64_t kd = (uint64_t)((uint32_t)ka ^ s2[i]) * kMulB;  // round 3
+    return philox_w1_from<3>(xor3((uint32_t)(kd >> 32), (uint32_t)kb, e3), (uint32_t)kd,
+                             (uint32_t)(kc >> 32) ^ s3[i], (uint32_t)kc, pa.key0, pa.key1);
+  };
+  const auto put = [&](uint32_t i, uint32_t k, bool pass) {
+    if (__ballot(pass) != 0ull && pass) {
+      const uint32_t at = atomicAdd(&q.cnt[i], 1u);
+      if (at < kListMax) q.list[i][at] = k;
+    }
+  };
+  uint32_t k0 = wv * 64u;
+  for (; k0 + 64u <= least; k0 += 64u * kG) {  // whole rows of every cell
+    const uint32_t k = k0 + lane;
+    const uint64_t ka = (uint64_t)k * kMulA;                                 // round 1
+    const uint64_t kb = (uint64_t)((uint32_t)(ka >> 32) ^ pa.key1) * kMulB;  // round 2
+    const uint64_t kc = (uint64_t)((uint32_t)(kb >> 32) ^ e2) * kMulA;       // round 3
+    uint32_t w[kG], low = 0xFFFFFFFFu;
+#pragma unroll
+    for (uint32_t i = 0; i < kG; ++i) {
+      w[i] = word(i, ka, kb, kc);
+      low = min(low, w[i]);
+    }
+    if (__ballot(low <= lim) != 0ull) {
+#pragma unroll
+      for (uint32_t i = 0; i < kG; ++i) put(i, k, w[i] <= lim);
+    }
+  }
+  for (; k0 < most; k0 += 64u * kG) {
+    const uint32_t k = k0 + lane;
+    const uint64_t ka = (uint64_t)k * kMulA;
+    const uint64_t kb = (uint64_t)((uint32_t)(ka >> 32) ^ pa.key1) * kMulB;
+    const uint64_t kc = (uint64_t)((uint32_t)(kb >> 32) ^ e2) * kMulA;
+#pragma unroll
+    for (uint32_t i = 0; i < kG; ++i)
+      if (k0 < np[i]) put(i, k, word(i, ka, kb, kc) <= lim && k < np[i]);
+  }
+}
+
+// The cells' parts of GroupLds::sorted: off[i] is the first entry of cell i;
+// a cell that its own wave takes has none.
+template <uint32_t kG>
+__device__ __forceinline__ void group_offsets(const GroupLds<kG> &q, uint32_t *off) {
+  off[0] = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kG; ++i) {
+    const uint32_t f = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.cnt[i]);
+    off[i + 1] = off[i] + (f <= kListMax ? f : 0u);
+  }
+}
+
+// Exact tests of the filtered pairs, wave wv the rows wv, wv + kG, ... of 64:
+// each pair ranks its index in its cell's list and leaves flag | cell << 20 |
+// a << 10 | b at its place.
+template <bool kFused, uint32_t kCap, uint32_t kG>
+__device__ __forceinline__ void group_exact(uint32_t c0, uint32_t t, const uint32_t *n,
+                                            const PairArgs &pa, const GCells &src,
+                                            GroupLds<kG> &q, const CellLds<kFused, kCap> *lds,
+                                            uint32_t wv) {
+  uint32_t off[kG + 1];
+  group_offsets<kG>(q, off);
+  for (uint32_t e = wv * 64u + lane_id(); e < off[kG]; e += 64u * kG) {
+    uint32_t i = 0, first = 0, f = off[1], nn = n[0];
+#pragma unroll
+    for (uint32_t u = 1; u < kG; ++u)
+      if (e >= off[u]) {
+        i = u;
+        first = off[u];
+        f = off[u + 1] - off[u];
+        nn = n[u];
+      }
+    const uint32_t k = q.list[i][e - first];
+    const uint4 *const list = reinterpret_cast<const uint4 *>(q.list[i]);
+    uint32_t r = first;
+#pragma unroll 2
+    for (uint32_t m = 0; 4u * m < f; ++m) {
+      const uint4 v = list[m];
+      r += (v.x < k) + (v.y < k) + (v.z < k) + (v.w < k);
+    }
+    const Words4 w = philox10(k, c0 + i, t, 0u, pa.key0, pa.key1);
+    uint32_t a, b;
+    pair_of_index(k, nn, a, b);
+    const size_t base = (size_t)(c0 + i) * src.cap;
+    double ax, ay, az, bx, by, bz;
+    load_momentum(src.st, base + lds[i].perm[a], ax, ay, az);
+    load_momentum(src.st, base + lds[i].perm[b], bx, by, bz);
+    const bool acc = uniform53(w.w0, w.w1) < p22(ax, ay, az, bx, by, bz, pa.kfac);
+    q.sorted[r] = (acc ? 0x80000000u : 0u) | i << 20 | a << 10 | b;
+  }
+}
+
+// Claims and kinematics (one wave): the accepted pairs move together, in
+// order; each row of 64 is claimed in order and its claims scattered, a pair
+// a lane.
+template <bool kFused, uint32_t kCap, uint32_t kG>
+__device__ __forceinline__ void group_claim(uint32_t c0, uint32_t t, const uint32_t *n,
+                                            const PairArgs &pa, const GCells &src,
+                                            DevStatus *status, GroupLds<kG> &q,
+                                            CellLds<kFused, kCap> *lds) {
+  static_assert(kListMax <= ClaimLds<kCap>::kMax, "claim momenta");
+  const uint32_t lane = lane_id();
+  const uint64_t below = (1ull << lane) - 1ull;
+  uint32_t off[kG + 1], pairs = 0;
+  group_offsets<kG>(q, off);
+#pragma unroll
+  for (uint32_t i = 0; i < kG; ++i)
+    if (n[i] > 1u && (uint32_t)__builtin_amdgcn_readfirstlane((int)q.cnt[i]) <= kListMax)
+      pairs += n[i] * (n[i] - 1u) / 2u;
+  uint32_t total = 0;  // accepted pairs
+  for (uint32_t e0 = 0; e0 < off[kG]; e0 += 64u) {
+    const uint32_t v = e0 + lane < off[kG] ? q.sorted[e0 + lane] : 0u;
+    wave_lds_sync();
+    const uint64_t m = __ballot((v & 0x80000000u) != 0u);
+    if (v & 0x80000000u) q.sorted[total + (uint32_t)__popcll(m & below)] = v & 0x7FFFFFFFu;
+    total += (uint32_t)__popcll(m);
+  }
+  wave_lds_sync();
+  uint32_t got[kG] = {}, n_claims = 0;  // claims of each cell, and of all
+  for (uint32_t e0 = 0; e0 < total; e0 += 64u) {
+    const bool have = e0 + lane < total;
+    const uint32_t v = have ? q.sorted[e0 + lane] : 0u;
+    const uint32_t i = v >> 20, a = (v >> 10) & 1023u, b = v & 1023u;
+    const uint32_t ma = i << 10 | a, mb = i << 10 | b;
+    const uint32_t ja = lds[i].perm[a], jb = lds[i].perm[b];
+    const ClaimLds<kCap> cl(lds[i]);
+    // free of an earlier row's claims
+    bool open = have && cl.map[ja] == 0 && cl.map[jb] == 0;
+    uint64_t won = 0;
+    for (uint64_t m = __ballot(open); m != 0; m = __ballot(open)) {
+      const uint32_t l = (uint32_t)__builtin_ctzll(m);
+      const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
+      const uint32_t li = vl >> 10 & ~1023u, la = li | (vl >> 10 & 1023u), lb = li | (vl & 1023u);
+      won |= 1ull << l;
+      open = open && ma != la && ma != lb && mb != la && mb != lb;
+    }
+    const bool mine = ((won >> lane) & 1ull) != 0ull;
+    uint32_t at = 0, nn = n[0];  // the claim's number in its cell; members
+#pragma unroll
+    for (uint32_t u = 0; u < kG; ++u) {
+      const uint64_t m = __ballot(mine && i == u);
+      if (i == u) {
+        at = got[u] + (uint32_t)__popcll(m & below);
+        nn = n[u];
+      }
+      got[u] += (uint32_t)__popcll(m);
+    }
+    n_claims += (uint32_t)__popcll(won);
+    if (mine) {
+      const Words4 w = philox10(row_start(a, nn) + (b - a - 1u), c0 + i, t, 1u, pa.key0, pa.key1);
+      const size_t base = (size_t)(c0 + i) * src.cap;
+      double ax, ay, az, bx, by, bz;
+      load_momentum(src.st, base + ja, ax, ay, az);
+      load_momentum(src.st, base + jb, bx, by, bz);
+      scatter_pair(ax, ay, az, bx, by, bz, uniform53(w.w0, w.w1), uniform53(w.w2, w.w3));
+      cl.put(at, ja, jb, ax, ay, az, bx, by, bz);
+      if (!kFused) {
+        put_momentum(src.st, base + ja, ax, ay, az);
+        put_momentum(src.st, base + jb, bx, by, bz);
+      }
+    }
+    wave_lds_sync();
+  }
+  if (lane == 0) {
+    const uint32_t slot = c0 % kCounterSlots;
+    atomicAdd(&status->pairs[slot], (unsigned long long)pairs);
+    atomicAdd(&status->cand[slot], (unsigned long long)total);
+    atomicAdd(&status->claims[slot], (unsigned long long)n_claims);
+  }
+}
+
+// Cells c0 .. c0 + 3 (those below n_cells) by a workgroup of four waves.
+template <bool kFused, uint32_t kCap, uint32_t kG>
+__device__ __forceinline__ void group_cells_step(const GCells &src, const GCells &dst, uint32_t c0,
+                                                uint32_t n_cells, uint32_t t, const PairArgs &pa,
+                                                const Geometry &g, DevStatus *status,
+                                                GroupLds<kG> &q, CellLds<kFused, kCap> *lds,
+                                                double *obs) {
+  const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
+  const TraceArgs none{};
+  CellWork w;
+  w.live = false;
+  w.cv.n = 0u;
+  if (c0 + wv < n_cells)
+    cell_open<kFused, false, kCap, false>(w, src, dst, c0 + wv, t, pa, g, status, none, lds[wv],
+                                          obs);
+  if (lane_id() == 0) {
+    q.n[wv] = w.live && !w.cv.ov && w.cv.n > 1u ? w.cv.n : 0u;
+    q.cnt[wv] = 0u;
+  }
+  if (lane_id() < kListMax / 4u)
+    reinterpret_cast<uint4 *>(q.list[wv])[lane_id()] =
+        uint4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+  __syncthreads();
+  uint32_t n[kG], np[kG];
+#pragma unroll
+  for (uint32_t i = 0; i < kG; ++i) {
+    n[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.n[i]);
+    np[i] = n[i] > 1u ? n[i] * (n[i] - 1u) / 2u : 0u;
+  }
+  __builtin_amdgcn_s_setprio(0);
+  if (pa.any) group_filter<kG>(c0, t, np, pa, q, wv);
+  __builtin_amdgcn_s_setprio(1);
+  __syncthreads();
+  const bool alone = q.n[wv] == 0u || q.cnt[wv] > kListMax;
+  group_exact<kFused, kCap, kG>(c0, t, n, pa, src, q, lds, wv);
+  __syncthreads();
+  if (wv == 0) group_claim<kFused, kCap, kG>(c0, t, n, pa, src, status, q, lds);
+  __syncthreads();
+  if (!alone) w.mom_lds = kFused;
+  if (!w.live) return;
+  if (alone) cell_pairs<kFused, false, kCap, false>(w, src, pa, status, none, lds[wv], obs);
+  cell_close<kFused, kCap>(w, src, dst, g, status, lds[wv], obs);
 }
 
 constexpr uint32_t kPackedMax = 64;  // particles of a packed unit, and of a cell it takes
@@ -1829,6 +2160,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<k
 // pair loop, which spills scalar registers into vector lanes and reloads them
 // in the loop.  Derived from src, the dst pointers stay known to address
 // global memory.
+template <bool kFused, uint32_t kCap>
+__global__ __launch_bounds__(64 * kGroup) __attribute__((amdgpu_waves_per_eu(cell_waves<kCap>()))) void k_step_group(
+    Cells src_arg, int64_t dst_shift, uint32_t n_cells, uint32_t t, PairArgs pa,
+    const Geometry *__restrict__ gp, DevStatus *status) {
+  const GCells src = binning(to_global(src_arg), t);
+  __shared__ CellLds<kFused, kCap> lds[kGroup];
+  __shared__ GroupLds<kGroup> q;
+  group_cells_step<kFused, kCap, kGroup>(src, dst_of(src, dst_shift, t),
+                                         xcd_runs<2>(blockIdx.x, gridDim.x) * kGroup, n_cells, t,
+                                         pa, *gp, status, q, lds, nullptr);
+}
+
 template <bool kFused, bool kTrace, uint32_t kCap>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<kCap>()))) void k_step(
     Cells src_arg, int64_t dst_shift, uint32_t t,
@@ -2228,7 +2571,9 @@ __global__ __launch_bounds__(64 * kW) void k_step_wide(Cells src_arg, int64_t ds
 //           cell > 0, which are stepped in packed units;
 //   scans   64 cells, one wave each, stepping the cells that the units leave
 //           out, for those of these events whose blocks exceed the small LDS;
-//   cells   one cell per wave, for events stepped one wave per cell.
+//   cells   one cell per wave, for events stepped one wave per cell;
+//   groups  kGroup cells, a workgroup each, for those of these events whose
+//           waves share their cells' pairs.
 // The step kernels have no loop over units: a loop keeps the descriptor and
 // lane constants live across iterations, which costs registers and with
 // them the occupancy that hides memory latency.  Within a run of k steps,
@@ -2393,7 +2738,25 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<k
                                  pa, E->g, E->status, TraceArgs{}, lds, obs_target(E, j));
 }
 
-
+// Groups of kGroup consecutive cells of the events whose waves share their
+// cells' pairs.
+template <bool kFused>
+__global__ __launch_bounds__(64 * kGroup) __attribute__((amdgpu_waves_per_eu(cell_waves<kSmallCap>()))) void k_batch_step_group(
+    const BatchEvent *__restrict__ ev, const uint32_t *__restrict__ group_begin,
+    uint32_t n_events, uint32_t j) {
+  __shared__ CellLds<kFused, kSmallCap> lds[kGroup];
+  __shared__ GroupLds<kGroup> q;
+  const uint32_t unit = xcd_runs<2>(blockIdx.x, gridDim.x);
+  const BatchEvent *__restrict__ E = ev + find_event(group_begin, n_events, unit);
+  const uint32_t s = (E->cur ^ (j & 1u)) & 1u;
+  const uint32_t t = E->t + j - 1u;
+  const GCells src = binning(to_global(E->buf[s]), t);
+  const int64_t shift = (const char *)E->buf[s ^ 1u].st.rec - (const char *)E->buf[s].st.rec;
+  const PairArgs pa = E->pa;
+  group_cells_step<kFused, kSmallCap, kGroup>(src, dst_of(src, shift, t),
+                                              (unit - E->cell_begin) * kGroup, E->n_cells, t, pa,
+                                              E->g, E->status, q, lds, obs_target(E, j));
+}
 
 // End of a run of k steps: every event moved k buffers and k step indices.
 __global__ void k_batch_advance(BatchEvent *ev, uint32_t n_events, uint32_t k) {
@@ -2767,6 +3130,14 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
       wide(std::integral_constant<uint32_t, kCap == kSmallCap ? 8 : 16>{});
     return;
   }
+  if constexpr (!kTrace) {
+    if (kCap == kSmallCap && lanes == 0 && dev.group) {
+      launch_timed(k_step_group<kFused, kSmallCap>, dim3((n_cells + kGroup - 1) / kGroup),
+                   dim3(64 * kGroup), s, dev.ev_start, dev.ev_stop, src, shift, n_cells, t, pa,
+                   dev.g, status);
+      return;
+    }
+  }
   if (lanes == 0 || lanes == kWideCells) {
     launch_timed(k_step<kFused, kTrace, kCap>, dim3(n_cells), block, s, dev.ev_start,
                  dev.ev_stop, src, shift, t, pa, dev.g, status, tr);
@@ -2826,8 +3197,9 @@ void launch_step(const Cells &src, const Cells &dst, bool fused, int64_t n_cells
     record_empty(dev.ev_start, dev.ev_stop, s);
     return;
   }
-  // cells of at most 512 slots use the kernels with half the LDS
-  if (src.cap <= kSmallCap)
+  // cells of at most 512 slots, or particles, use the kernels with half the
+  // LDS (the wide kernel by slots alone)
+  if (src.cap <= kSmallCap || (dev.fits_small && lanes != kWideCells && !trace))
     launch_step_any<kSmallCap>(src, dst, fused, (uint32_t)n_cells, lanes, t, pa, g, status,
                                trace, s, side, dev);
   else
@@ -2924,13 +3296,17 @@ void launch_batch_run(BatchEvent *ev, const BatchSpaces &sp, uint32_t n_events, 
   auto step = [&](auto fused, uint32_t j) {
     constexpr bool kF = decltype(fused)::value;
     const bool both =
-        sp.n_tiles > 0 && (sp.n_cells[0] > 0 || sp.n_cells[1] > 0 || sp.n_scans > 0);
+        sp.n_tiles > 0 &&
+        (sp.n_cells[0] > 0 || sp.n_cells[1] > 0 || sp.n_groups > 0 || sp.n_scans > 0);
     const SideStream *sd = both ? side : nullptr;
     const hipStream_t s2 = sd ? sd->stream : s;
     fork(s, sd);
     if (sp.n_tiles > 0)
       hipLaunchKernelGGL((k_batch_step_packed<kF>), dim3(sp.n_tiles), dim3(64 * kPackedWaves), 0,
                          s, cev, sp.tile_begin, n_events, j);
+    if (sp.n_groups > 0)
+      hipLaunchKernelGGL((k_batch_step_group<kF>), dim3(sp.n_groups), dim3(64 * kGroup), 0, s2,
+                         cev, sp.group_begin, n_events, j);
     if (sp.n_cells[0] > 0)
       hipLaunchKernelGGL((k_batch_step_cells<kF, kSmallCap>), dim3(sp.n_cells[0]), wave, 0, s2,
                          cev, sp.cell_begin[0], n_events, j);
