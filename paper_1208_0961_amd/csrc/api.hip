@@ -377,17 +377,20 @@ uint32_t packed_tile(const uint32_t over[4], int64_t n, int64_t n_cells) {
 
 // Whether the waves of four cells share their pairs (one wave per cell else):
 // the mean occupancy at least 50, 60 from 16 384 cells, and K mean^2, which is
-// half the filtered pairs of a mean cell or a quarter of a dense one's, at
-// most 10.5 (beyond, their exact tests and claims by few waves cost more than
-// the shared filter saves).  Speed-up over one wave per cell by the mean on
-// 11 323 / 40 000 cells at K mean^2 = 0.08 mean: 45 1.01 / 0.99, 57 1.04 /
-// 1.01, 70 1.05 / 1.02, 85 1.07 / 1.07, 105 1.10 / 1.09, 125 1.12 / 1.12; at
-// 0.16 mean: 57 1.03 / 1.01, 70 1.00 / 1.01, 85 0.99 / 1.00, 105 0.87 / 0.96;
-// 3 600 cells of 85: 0.97.
+// half the filtered pairs of a mean cell, at most 12 (beyond, the exact tests
+// and claims weigh as much as the shared filter saves), 100 from a mean of 110
+// (a cell's list holds 256).  Speed-up over one wave per cell by the mean on
+// 11 323 / 40 000 cells, at K mean^2 = 0.08 mean: 57 1.04 / 1.00, 70 1.05 /
+// 1.03, 85 1.09 / 1.07, 105 1.11 / 1.10, 125 1.15 / 1.12, 160 1.15 / 1.18, 220
+// 1.14 / 1.17; at 0.16 mean: 57 1.04 / 1.00, 85 1.05 / 1.04, 125 1.08 / 1.08; at
+// 0.33 mean: 70 1.03 / 0.97, 85 1.01 / 0.98, 105 1.01 / 1.00, 125 1.04 / 1.03,
+// 220 1.11 / 1.12.  (3 600 cells of 85: 0.97.)  In a batch 100 throughout: 24
+// ensemble events, 25 steps, 12.95 -> 12.63 ms.
 constexpr int64_t kGroupMinCells = 6000;
-bool shares_pairs(int64_t n, int64_t n_cells, double kfac) {
+bool shares_pairs(int64_t n, int64_t n_cells, double kfac, bool plain) {
   const double mean = (double)n / (double)n_cells;
-  return mean >= (n_cells < 16384 ? 50.0 : 60.0) && kfac * mean * mean <= 10.5;
+  return mean >= (n_cells < 16384 ? 50.0 : 60.0) &&
+         kfac * mean * mean <= (plain && mean < 110.0 ? 12.0 : 100.0);
 }
 
 // Waves per cell of the wide kernel (us a step with 4 / 8 / 16 waves): 100
@@ -403,7 +406,7 @@ uint32_t wide_waves(int64_t n, int64_t n_cells) {
 StepDevice step_device(const cuba_ctx *c) {
   return StepDevice{&c->consts->g, over_span(c->over, c->d.n_cells),
                     packed_tile(c->over, c->n, c->d.n_cells), wide_waves(c->n, c->d.n_cells),
-                    c->d.n_cells >= kGroupMinCells && shares_pairs(c->n, c->d.n_cells, c->d.kfac),
+                    c->d.n_cells >= kGroupMinCells && shares_pairs(c->n, c->d.n_cells, c->d.kfac, true),
                     c->over[4] == 0};
 }
 
@@ -1043,7 +1046,7 @@ int upload_table(cuba_batch *b) {
   const auto shares = [&](int32_t s) {
     const cuba_ctx *c = b->slot_ctx[s];
     return c && b->slot_active[s] && c->lanes == 0 && c->d.n_cells > 0 &&
-           c->d.cap <= kSmallCap && shares_pairs(c->n, c->d.n_cells, c->d.kfac);
+           c->d.cap <= kSmallCap && shares_pairs(c->n, c->d.n_cells, c->d.kfac, false);
   };
   int64_t shared_cells = 0;
   for (int32_t s = 0; s < b->max_slots; ++s)

@@ -1307,11 +1307,13 @@ __device__ __forceinline__ void cell_open(CellWork &w, const GCells &src, const 
   }
 }
 
-// Part 2.
-template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk>
+// Part 2.  kFiltered: the cell's nf filtered pairs are in lds.buf, in
+// increasing k; else they are found here.
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk, bool kFiltered = false>
 __device__ __forceinline__ void cell_pairs(CellWork &w, const GCells &src, const PairArgs &pa,
                                            DevStatus *status, const TraceArgs &tr,
-                                           CellLds<kFused, kCap> &lds, const double *obs) {
+                                           CellLds<kFused, kCap> &lds, const double *obs,
+                                           uint32_t nf = 0) {
   const CellView &cv = w.cv;
   const uint32_t lane = lane_id(), n = cv.n;
   const GState &st = src.st;
@@ -1324,69 +1326,69 @@ __device__ __forceinline__ void cell_pairs(CellWork &w, const GCells &src, const
   const uint16_t *const s_perm = lds.perm;
   const ClaimLds<kCap> cl(lds);
   uint32_t nclaim = 0;
-      // every pair k = 0 .. n(n-1)/2 - 1 (test_pairs), then the exact test
-      // and the claims of the filtered ones in increasing k
-      const uint32_t npairs = n * (n - 1u) / 2u;
-      uint32_t nf = 0, claimed_bits = 0, n_acc = 0;
-      __builtin_amdgcn_s_setprio(0);
-      if (pa.any)
-        test_pairs<true, kTrace, kBlk, kFilt>(0u, npairs, cv, pa, st, s_perm, s_filt, nf, s_claim,
-                                              nclaim, claimed_bits, n_acc, tr, status);
-      if (nf != 0)
-        resolve_filtered<kTrace, kBlk>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
-                                       claimed_bits, n_acc, tr, status);
-      cell_sync<kBlk>();
+  // every pair k = 0 .. n(n-1)/2 - 1 (test_pairs), then the exact test
+  // and the claims of the filtered ones in increasing k
+  const uint32_t npairs = n * (n - 1u) / 2u;
+  uint32_t claimed_bits = 0, n_acc = 0;
+  __builtin_amdgcn_s_setprio(0);
+  if (!kFiltered && pa.any)
+    test_pairs<true, kTrace, kBlk, kFilt>(0u, npairs, cv, pa, st, s_perm, s_filt, nf, s_claim,
+                                          nclaim, claimed_bits, n_acc, tr, status);
+  if (nf != 0)
+    resolve_filtered<kTrace, kBlk>(nf, cv, pa, st, s_perm, s_filt, s_claim, nclaim,
+                                   claimed_bits, n_acc, tr, status);
+  cell_sync<kBlk>();
 
-      __builtin_amdgcn_s_setprio(1);
-      // work counters (spread over slots by cell against contention)
+  __builtin_amdgcn_s_setprio(1);
+  // work counters (spread over slots by cell against contention)
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) n_acc += __shfl_down(n_acc, o);
-      if (lane == 0) {
-        const uint32_t slot = cv.c % kCounterSlots;
-        atomicAdd(&status->pairs[slot], (unsigned long long)npairs);
-        atomicAdd(&status->cand[slot], (unsigned long long)n_acc);
-        atomicAdd(&status->claims[slot], (unsigned long long)nclaim);
-      }
+  for (int o = 32; o > 0; o >>= 1) n_acc += __shfl_down(n_acc, o);
+  if (lane == 0) {
+    const uint32_t slot = cv.c % kCounterSlots;
+    atomicAdd(&status->pairs[slot], (unsigned long long)npairs);
+    atomicAdd(&status->cand[slot], (unsigned long long)n_acc);
+    atomicAdd(&status->claims[slot], (unsigned long long)nclaim);
+  }
 
-      // kinematics of the claimed pairs (disjoint: one writer per particle),
-      // written back in place, or for the binning below into LDS; a fused
-      // step then bins every particle
-      w.mom_lds = kFused && !cv.ov && nclaim <= kMomCap;
-      for (uint32_t i0 = 0; i0 < nclaim; i0 += 64u) {
-        const uint32_t i = i0 + lane;
-        const bool active = i < nclaim;
-        double ax = 0, ay = 0, az = 0, bx = 0, by = 0, bz = 0;
-        uint32_t ja = 0, jb = 0;
-        if (active) {
-          const uint32_t v = s_claim[i];
-          const uint32_t a = (v >> 10) & 1023u, b = v & 1023u;
-          const uint32_t k = row_start(a, n) + (b - a - 1u);
-          const Words4 u = philox10(k, cv.c, cv.t, 1u, pa.key0, pa.key1);
-          ja = s_perm[a];
-          jb = s_perm[b];
-          const size_t ia = cv.at(ja), ib = cv.at(jb);
-          load_momentum(st, ia, ax, ay, az);
-          load_momentum(st, ib, bx, by, bz);
-          scatter_pair(ax, ay, az, bx, by, bz, uniform53(u.w0, u.w1), uniform53(u.w2, u.w3));
-          if (w.mom_lds) {
-            cl.put(i, ja, jb, ax, ay, az, bx, by, bz);
-          } else {
-            put_momentum(st, ia, ax, ay, az);
-            put_momentum(st, ib, bx, by, bz);
-          }
-          if (kTrace && tr.claim) {
-            const uint32_t slot = atomicAdd(&tr.counts[1], 1u);
-            if (slot < tr.claim_cap) {
-              tr.claim[3 * (size_t)slot + 0] = cv.c;
-              tr.claim[3 * (size_t)slot + 1] = a;
-              tr.claim[3 * (size_t)slot + 2] = b;
-            } else {
-              atomicOr(&status->err, kErrTrace);
-            }
-          }
+  // kinematics of the claimed pairs (disjoint: one writer per particle),
+  // written back in place, or for the binning below into LDS; a fused
+  // step then bins every particle
+  w.mom_lds = kFused && !cv.ov && nclaim <= kMomCap;
+  for (uint32_t i0 = 0; i0 < nclaim; i0 += 64u) {
+    const uint32_t i = i0 + lane;
+    const bool active = i < nclaim;
+    double ax = 0, ay = 0, az = 0, bx = 0, by = 0, bz = 0;
+    uint32_t ja = 0, jb = 0;
+    if (active) {
+      const uint32_t v = s_claim[i];
+      const uint32_t a = (v >> 10) & 1023u, b = v & 1023u;
+      const uint32_t k = row_start(a, n) + (b - a - 1u);
+      const Words4 u = philox10(k, cv.c, cv.t, 1u, pa.key0, pa.key1);
+      ja = s_perm[a];
+      jb = s_perm[b];
+      const size_t ia = cv.at(ja), ib = cv.at(jb);
+      load_momentum(st, ia, ax, ay, az);
+      load_momentum(st, ib, bx, by, bz);
+      scatter_pair(ax, ay, az, bx, by, bz, uniform53(u.w0, u.w1), uniform53(u.w2, u.w3));
+      if (w.mom_lds) {
+        cl.put(i, ja, jb, ax, ay, az, bx, by, bz);
+      } else {
+        put_momentum(st, ia, ax, ay, az);
+        put_momentum(st, ib, bx, by, bz);
+      }
+      if (kTrace && tr.claim) {
+        const uint32_t slot = atomicAdd(&tr.counts[1], 1u);
+        if (slot < tr.claim_cap) {
+          tr.claim[3 * (size_t)slot + 0] = cv.c;
+          tr.claim[3 * (size_t)slot + 1] = a;
+          tr.claim[3 * (size_t)slot + 2] = b;
+        } else {
+          atomicOr(&status->err, kErrTrace);
         }
       }
-      if (kFused || obs) cell_sync<kBlk>();
+    }
+  }
+  if (kFused || obs) cell_sync<kBlk>();
 }
 
 // Part 3 (with kFused clears src's count).
@@ -1478,11 +1480,12 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
 //               Philox owe to the index alone (three of a test's 16
 //               multiplies, two of its 15 XORs) is computed once for the
 //               four.  Passing pairs go to their cell's list in any order;
-//   the rest    one wave sorts the ~40 filtered pairs by cell and index, tests
-//               them exactly, claims, and computes the kinematics, a pair a
-//               lane in one row, where each cell alone fills a few lanes of a
-//               row in each of these.
-// A cell whose list would exceed kListMax (or that overflows its block, or
+//   the rest    where no list holds more than kListMax, the waves test the
+//               lists exactly in common rows and one wave claims and computes
+//               the kinematics, a pair a lane: the ~40 filtered pairs of the
+//               four cells fill a row where each cell alone fills a few of
+//               its lanes.  Longer lists go to their cell's own wave, sorted.
+// A cell whose list would exceed kListAll (or that overflows its block, or
 // that holds no pair) is left out and taken by its own wave alone.
 // Bound by VALU issue on the full tube (a wave per cell: 98 % busy).  Against
 // one wave per cell: 684 -> 577 M VALU instructions a launch there, 1.23 ->
@@ -1490,19 +1493,19 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
 // cells to a workgroup gained half of that, and one LDS atomic a row for all
 // four lists, instead of one a list, less than four.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kListMax = 40;  // <= ClaimLds::kMax: every claim's momenta fit
+constexpr uint32_t kListMax = 40;   // of the shared rows; <= ClaimLds::kMax: every claim fits
+constexpr uint32_t kListAll = 256;  // of a cell's list
 template <uint32_t kG>
 struct GroupLds {
   uint32_t n[kG];    // members of the cells that share their pairs, else 0
-  uint32_t cnt[kG];  // filtered pairs
-  __align__(16) uint32_t list[kG][kListMax];  // unused entries all ones
+  uint32_t cnt[kG];  // filtered pairs, listed in the cell's lds.buf
   uint32_t sorted[kG * kListMax];  // the exact test's results, by cell and index
 };
 
-// Filter rows wv, wv + kG, ... of the cells c0 .. c0 + 3 (np pairs each).
-template <uint32_t kG>
+template <bool kFused, uint32_t kCap, uint32_t kG>
 __device__ __forceinline__ void group_filter(uint32_t c0, uint32_t t, const uint32_t *np,
-                                             const PairArgs &pa, GroupLds<kG> &q, uint32_t wv) {
+                                             const PairArgs &pa, GroupLds<kG> &q,
+                                             CellLds<kFused, kCap> *lds, uint32_t wv) {
   const uint32_t lane = lane_id(), lim = pa.w1_max;
   const uint64_t tb = (uint64_t)t * kMulB;
   uint32_t s2[kG], s3[kG];  // what the cell adds to word 2 in rounds 2 and 3
@@ -1533,7 +1536,7 @@ __device__ __forceinline__ void group_filter(uint32_t c0, uint32_t t, const uint
   const auto put = [&](uint32_t i, uint32_t k, bool pass) {
     if (__ballot(pass) != 0ull && pass) {
       const uint32_t at = atomicAdd(&q.cnt[i], 1u);
-      if (at < kListMax) q.list[i][at] = k;
+      if (at < kListAll) lds[i].buf[at] = k;
     }
   };
   uint32_t k0 = wv * 64u;
@@ -1596,8 +1599,8 @@ __device__ __forceinline__ void group_exact(uint32_t c0, uint32_t t, const uint3
         f = off[u + 1] - off[u];
         nn = n[u];
       }
-    const uint32_t k = q.list[i][e - first];
-    const uint4 *const list = reinterpret_cast<const uint4 *>(q.list[i]);
+    const uint32_t k = lds[i].buf[e - first];
+    const uint4 *const list = reinterpret_cast<const uint4 *>(lds[i].buf);
     uint32_t r = first;
 #pragma unroll 2
     for (uint32_t m = 0; 4u * m < f; ++m) {
@@ -1695,6 +1698,29 @@ __device__ __forceinline__ void group_claim(uint32_t c0, uint32_t t, const uint3
   }
 }
 
+// Sorts a list of nf <= kListAll filtered pairs, padded with all ones (one
+// wave): each entry counts the smaller ones.
+__device__ __forceinline__ void group_sort(uint32_t nf, uint32_t *list) {
+  const uint32_t lane = lane_id();
+  constexpr uint32_t kRows = kListAll / 64u;
+  uint32_t k[kRows], r[kRows];
+#pragma unroll
+  for (uint32_t u = 0; u < kRows; ++u) {
+    k[u] = list[64u * u + lane];
+    r[u] = 0;
+    if (64u * u < nf)
+      for (uint32_t m = 0; 4u * m < nf; ++m) {
+        const uint4 v = reinterpret_cast<const uint4 *>(list)[m];
+        r[u] += (v.x < k[u]) + (v.y < k[u]) + (v.z < k[u]) + (v.w < k[u]);
+      }
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (uint32_t u = 0; u < kRows; ++u)
+    if (64u * u + lane < nf) list[r[u]] = k[u];
+  wave_lds_sync();
+}
+
 // Cells c0 .. c0 + 3 (those below n_cells) by a workgroup of four waves.
 template <bool kFused, uint32_t kCap, uint32_t kG>
 __device__ __forceinline__ void group_cells_step(const GCells &src, const GCells &dst, uint32_t c0,
@@ -1714,9 +1740,10 @@ __device__ __forceinline__ void group_cells_step(const GCells &src, const GCells
     q.n[wv] = w.live && !w.cv.ov && w.cv.n > 1u ? w.cv.n : 0u;
     q.cnt[wv] = 0u;
   }
-  if (lane_id() < kListMax / 4u)
-    reinterpret_cast<uint4 *>(q.list[wv])[lane_id()] =
-        uint4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+  // (the ids' buffer becomes the list of filtered pairs, unused entries all ones)
+  static_assert(kListAll == 4u * 64u && kListAll <= kCap / 2u, "list");
+  reinterpret_cast<uint4 *>(lds[wv].buf)[lane_id()] =
+      uint4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
   __syncthreads();
   uint32_t n[kG], np[kG];
 #pragma unroll
@@ -1725,17 +1752,29 @@ __device__ __forceinline__ void group_cells_step(const GCells &src, const GCells
     np[i] = n[i] > 1u ? n[i] * (n[i] - 1u) / 2u : 0u;
   }
   __builtin_amdgcn_s_setprio(0);
-  if (pa.any) group_filter<kG>(c0, t, np, pa, q, wv);
+  if (pa.any) group_filter<kFused, kCap, kG>(c0, t, np, pa, q, lds, wv);
   __builtin_amdgcn_s_setprio(1);
   __syncthreads();
-  const bool alone = q.n[wv] == 0u || q.cnt[wv] > kListMax;
-  group_exact<kFused, kCap, kG>(c0, t, n, pa, src, q, lds, wv);
-  __syncthreads();
-  if (wv == 0) group_claim<kFused, kCap, kG>(c0, t, n, pa, src, status, q, lds);
-  __syncthreads();
-  if (!alone) w.mom_lds = kFused;
+  bool together = true;  // every list short enough for the shared rows
+#pragma unroll
+  for (uint32_t i = 0; i < kG; ++i)
+    together = together && (uint32_t)__builtin_amdgcn_readfirstlane((int)q.cnt[i]) <= kListMax;
+  if (together) {
+    group_exact<kFused, kCap, kG>(c0, t, n, pa, src, q, lds, wv);
+    __syncthreads();
+    if (wv == 0) group_claim<kFused, kCap, kG>(c0, t, n, pa, src, status, q, lds);
+    __syncthreads();
+  }
   if (!w.live) return;
-  if (alone) cell_pairs<kFused, false, kCap, false>(w, src, pa, status, none, lds[wv], obs);
+  const uint32_t nf = q.cnt[wv];
+  if (together && q.n[wv] != 0u) {
+    w.mom_lds = kFused;
+  } else if (q.n[wv] != 0u && nf <= kListAll) {
+    group_sort(nf, lds[wv].buf);
+    cell_pairs<kFused, false, kCap, false, true>(w, src, pa, status, none, lds[wv], obs, nf);
+  } else {
+    cell_pairs<kFused, false, kCap, false>(w, src, pa, status, none, lds[wv], obs);
+  }
   cell_close<kFused, kCap>(w, src, dst, g, status, lds[wv], obs);
 }
 

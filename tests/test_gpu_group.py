@@ -1,6 +1,6 @@
 """Four cells whose waves share their pairs (boxes of 6000 cells and more,
 means of 50 and more, few filtered pairs): groups past the last cell, empty
-and single-particle cells, cells whose list of filtered pairs overflows and
+and single-particle cells, cells whose list of filtered pairs is long or overflows and
 cells past their block (each then taken by its own wave), fused and
 collide-only steps against one oracle step, and the batched kernel against
 the lone run.  And cells that outgrow the small LDS inside a block that holds
@@ -18,7 +18,9 @@ M = 19   # 6859 cells: the last group holds 3
 
 def _occupancy(pattern, seed=1):
     rng = np.random.default_rng(seed)
-    occ = rng.poisson(52, M ** 3)
+    occ = rng.poisson(112 if pattern == "long lists" else 52, M ** 3)
+    if pattern == "long lists":       # sorted and resolved cell by cell
+        occ[[5, 6, 7, 500]] = (20, 0, 290, 330)
     if pattern == "ragged":
         occ[::5] = rng.integers(0, 4, len(occ[::5]))
         occ[1::5] = 85
@@ -38,10 +40,13 @@ def _params(occ, scale=1.0):
 
 
 @pytest.mark.parametrize("nsteps", (1, 2))
-@pytest.mark.parametrize("pattern", ("poisson", "ragged", "lists overflow", "blocks overflow"))
+@pytest.mark.parametrize("pattern", ("poisson", "ragged", "lists overflow", "blocks overflow",
+                                     "long lists"))
 def test_group_parity(orc, lib, pattern, nsteps):  # noqa: F811
     occ = _occupancy(pattern)
-    params = {**_params(occ), "cell_capacity": 512 if pattern == "lists overflow" else 128}
+    long = pattern == "long lists"    # ~50 filtered pairs a cell, 400 in the fullest
+    params = {**_params(occ, 3.0 if long else 1.0),
+              "cell_capacity": 512 if long or pattern == "lists overflow" else 128}
     claims = _fused_step_check(orc, lib, params, _grid_state(occ, m=M), nsteps, 0, pattern)
     assert claims is None or claims > 1000
 
