@@ -860,6 +860,17 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
   return x;
 }
 
+// Inclusive prefix maximum over the wave's lanes (every lane active).
+__device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t x) {
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));
+  return x;
+}
+
 __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
   return wave_reduce(v, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
 }
@@ -1836,17 +1847,23 @@ __device__ __forceinline__ void large_cells_step(const GCells &src, const GCells
 // lanes a cell before, one particle a lane, half the lanes idle), 2 a cell
 // 1.83 -> 1.79 ms; 128 batched events of 5 100 particles, 100 steps: 30.1 ->
 // 7.1 ms (a wave per cell before); 24 ensemble events, 25 steps: 15.4 ->
-// 13.0 ms; 32^3 fm^3 set, 10 steps: 20.1 -> 19.5 ms.
+// 13.0 ms; 32^3 fm^3 set, 10 steps: 20.1 -> 19.5 ms.  Each lane's cell by
+// marks at the cells' first lanes and a prefix maximum, where a binary search
+// of the counts' prefix in LDS took six dependent reads (and the counters
+// summed once a wave): 5.56 -> 5.42 ms, 1.80 -> 1.78, 19.6 -> 19.4 on the set.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kPackedFilt = 256;  // filtered pairs held before a row is resolved
+constexpr uint32_t kRankByFour = 10;   // ids of larger cells are compared four at a time
 
 struct PackedLds {
   __align__(16) uint32_t id[64];   // by lane: the unit's particles, cell by cell
   double x[64], y[64], z[64];      // by lane
   double px[64], py[64], pz[64];   // by canonical position
-  uint32_t filt[kPackedFilt];      // filtered pairs: tile cell << 16 | k
-  uint32_t incl[64];               // by tile cell: inclusive prefix of the packed counts
+  // filtered pairs: tile cell << 16 | k; before, the unit's ids again, each
+  // cell's from a multiple of 4, padded with ids no particle has
+  __align__(16) uint32_t filt[kPackedFilt];
   uint32_t start[64], cnt[64];     // by tile cell: first lane, particles
+  uint32_t quad[64];               // by tile cell: first group of 4 in filt
   uint32_t partner[64];            // by canonical position: the claimed partner's
   SlotTable tab;
 };
@@ -1891,7 +1908,7 @@ __device__ __forceinline__ void packed_resolve_row(
       }
     }
   }
-  n_acc += acc ? 1u : 0u;
+  n_acc += (uint32_t)__popcll(__ballot(acc));
   for (uint64_t m = __ballot(acc); m != 0; m &= m - 1ull) {
     const uint32_t l = (uint32_t)__builtin_ctzll(m);
     const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
@@ -1951,6 +1968,7 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
     double *const out = obs + kCellSums * (size_t)cc;
     out[0] = out[1] = out[2] = out[3] = 0.0;
   }
+  const uint64_t left_out = __ballot(ccnt > kPackedMax || ccnt > src.cap);
   const uint32_t nl = packed ? ccnt : 0u;
   const uint32_t incl = wave_inclusive_sum(nl);  // inclusive prefix of the packed counts
   const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
@@ -1969,26 +1987,20 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
     const uint32_t p = end - base;  // particles of the unit
     const bool in_unit = nl > 0 && incl - nl >= base && lane <= e;
     wave_lds_sync();  // the previous unit's readers of lds are done
-    lds.incl[lane] = incl;
+    // each lane's cell: the unit's cells mark their first lanes, and the
+    // largest mark up to a lane is its cell
+    lds.partner[lane] = 0u;
+    wave_lds_sync();
     if (in_unit) {
       lds.start[lane] = incl - nl - base;
       lds.cnt[lane] = nl;
+      lds.partner[incl - nl - base] = lane;
       cnt_pairs += nl * (nl - 1u) / 2u;
     }
     wave_lds_sync();
-    // each lane's cell: the first tile cell whose particles end beyond it
-    // (binary search of the inclusive prefix)
     const bool mine = lane < p;
-    uint32_t cl = 0;
-    {
-      const uint32_t key = base + lane;
-      uint32_t lo = 0, hi = 63;  // first index with incl > key, in [lo, hi]
-      for (int it = 0; it < 6; ++it) {
-        const uint32_t mid = (lo + hi) / 2u;
-        if (lds.incl[mid] > key) hi = mid; else lo = mid + 1u;
-      }
-      cl = mine ? lo : 0u;
-    }
+    const uint32_t mark = wave_inclusive_max(lds.partner[lane]);
+    const uint32_t cl = mine ? mark : 0u;
     const uint32_t st = mine ? lds.start[cl] : 0u;
     const uint32_t n = mine ? lds.cnt[cl] : 0u;
     const uint32_t gl = lane - st;
@@ -2008,7 +2020,6 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
       }
       lds.id[lane] = id;
     }
-    wave_lds_sync();
     // canonical rank among the cell's ids; the momenta move to their
     // canonical positions
     uint32_t pos;
@@ -2016,6 +2027,7 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
       const uint32_t id = lds.id[lane];
       const uint32_t maxn = wave_max(n);
       uint32_t r = 0;
+      wave_lds_sync();
       for (uint32_t m = 0; m < maxn; ++m)
         if (m < n) r += lds.id[st + m] < id ? 1u : 0u;
       pos = st + r;
@@ -2123,10 +2135,7 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
   }
   // work counters of the wave's units, in one slot
 #pragma unroll
-  for (int s = 32; s > 0; s >>= 1) {
-    cnt_pairs += __shfl_down(cnt_pairs, s);
-    n_acc += __shfl_down(n_acc, s);
-  }
+  for (int s = 32; s > 0; s >>= 1) cnt_pairs += __shfl_down(cnt_pairs, s);
   if (lane == 0 && cnt_pairs != 0) {
     const uint32_t slot = c0 % kCounterSlots;
     atomicAdd(&status->pairs[slot], (unsigned long long)cnt_pairs);
@@ -2134,8 +2143,7 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
     atomicAdd(&status->claims[slot], (unsigned long long)n_claims);
   }
   if (kLarge && large) {
-    for (uint64_t big = __ballot(ccnt > kPackedMax || ccnt > src.cap); big != 0;
-         big &= big - 1ull)
+    for (uint64_t big = left_out; big != 0; big &= big - 1ull)
       if (unit++ % kPackedWaves == wave)
         cell_step<kFused, kTrace, kSmallCap, false>(src, dst,
                                                        c0 + (uint32_t)__builtin_ctzll(big), t, pa,
