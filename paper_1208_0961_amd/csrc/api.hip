@@ -426,7 +426,7 @@ StepDevice timed_step_device(const cuba_ctx *c, const TimedLaunch *t) {
 // and the compact offsets are built before the collisions.
 int run_steps(cuba_ctx *c, int32_t nsteps, const TraceArgs *trace_in) {
   if (nsteps <= 0) return CUBA_OK;
-  // the oversize-cell kernel follows the small-cell kernel on the same
+  // the larger cells' kernel follows the packed kernel on the same
   // stream: a fork to a second stream and back costs more per step than
   // the overlap gains for a single event (measured on MI355X)
   const SideStream *side = nullptr;

@@ -18,6 +18,8 @@
 //                  with F kept in LDS).  With F (fused) the same wave then
 //                  streams and bins its particles for step t+1, so the
 //                  binning traffic overlaps the ALU-bound pair tests.
+//   k_step_group   a workgroup of four waves on four dense cells: the waves
+//                  share the four cells' pair tests.
 //   k_step_packed  whole cells packed into waves of up to 64 particles, one
 //                  a lane (sparse cells); k_step_large / k_step_over step
 //                  larger cells where that kernel does not itself.
@@ -1853,17 +1855,13 @@ __device__ __forceinline__ void large_cells_step(const GCells &src, const GCells
 // summed once a wave): 5.56 -> 5.42 ms, 1.80 -> 1.78, 19.6 -> 19.4 on the set.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kPackedFilt = 256;  // filtered pairs held before a row is resolved
-constexpr uint32_t kRankByFour = 10;   // ids of larger cells are compared four at a time
 
 struct PackedLds {
   __align__(16) uint32_t id[64];   // by lane: the unit's particles, cell by cell
   double x[64], y[64], z[64];      // by lane
   double px[64], py[64], pz[64];   // by canonical position
-  // filtered pairs: tile cell << 16 | k; before, the unit's ids again, each
-  // cell's from a multiple of 4, padded with ids no particle has
-  __align__(16) uint32_t filt[kPackedFilt];
+  uint32_t filt[kPackedFilt];      // filtered pairs: tile cell << 16 | k
   uint32_t start[64], cnt[64];     // by tile cell: first lane, particles
-  uint32_t quad[64];               // by tile cell: first group of 4 in filt
   uint32_t partner[64];            // by canonical position: the claimed partner's
   SlotTable tab;
 };
