@@ -100,8 +100,8 @@ def parse():
                     help="batch: skip the one-at-a-time comparison")
     ap.add_argument("--lanes", type=int, default=None, choices=[0, 1, 8, 16, 32, 64, 128],
                     help="plain workloads: lanes per cell of the cell kernels, 1 for "
-                         "packed cells, 128 for "
-                         "two waves per cell (default: the library's choice from the "
+                         "packed cells, 128 for 4 to "
+                         "16 waves per cell (default: the library's choice from the "
                          "initial occupancy)")
     ap.add_argument("--cpu-steps", type=int, default=None,
                     help="oracle steps for the CPU baseline (0: skip)")
@@ -134,7 +134,14 @@ def parse():
 
 
 KERNEL_SOURCES = ("paper_1208_0961_amd/csrc/kernels.hip", "paper_1208_0961_amd/csrc/device.hpp")
-DOMINANT_KERNEL = "k_step<true, false,"   # the fused step, any cell capacity
+# the fused step, any cell capacity: a wave per cell, or (from 6000 cells on)
+# a workgroup of four waves per four cells
+DOMINANT_KERNELS = ("k_step<true, false,", "k_step_group<true,")
+DOMINANT_KERNEL = " / ".join(DOMINANT_KERNELS)
+
+
+def is_dominant(name: str) -> bool:
+    return any(k.replace(" ", "") in name.replace(" ", "") for k in DOMINANT_KERNELS)
 
 
 def device_copy_gbs(stream, nbytes: int = 1 << 30, reps: int = 5) -> float:
@@ -188,7 +195,7 @@ def write_traffic(a):
     def per_kernel(path, counter):
         rows = [r for r in csv.DictReader(open(path)) if r["Counter_Name"] == counter]
         kern = [float(r["Counter_Value"]) for r in rows
-                if DOMINANT_KERNEL.replace(" ", "") in r["Kernel_Name"].replace(" ", "")]
+                if is_dominant(r["Kernel_Name"])]
         # the profiled run uses the benchmark's workload, whose capacity
         # selects one instantiation
         copy = [float(r["Counter_Value"]) for r in rows
@@ -200,7 +207,7 @@ def write_traffic(a):
 
     fetch, fscale = per_kernel(a.pmc_csv[0], "FETCH_SIZE")
     write, wscale = per_kernel(a.pmc_csv[1], "WRITE_SIZE")
-    out = {"kernel": DOMINANT_KERNEL.rstrip(",") + " ...>", "workload": a.workload,
+    out = {"kernel": DOMINANT_KERNEL, "workload": a.workload,
            "kernel_source_hash": kernel_source_hash(),
            "fetch_bytes_per_launch": fetch, "write_bytes_per_launch": write,
            "bytes_per_launch": fetch + write,
@@ -277,9 +284,9 @@ def valu_busy(sq_csv: str, stats_csv: str) -> dict:
     import csv
     rows = [r for r in csv.DictReader(open(sq_csv))
             if r["Counter_Name"] == "SQ_ACTIVE_INST_VALU"
-            and DOMINANT_KERNEL.replace(" ", "") in r["Kernel_Name"].replace(" ", "")]
+            and is_dominant(r["Kernel_Name"])]
     stats = [r for r in csv.DictReader(open(stats_csv))
-             if DOMINANT_KERNEL.replace(" ", "") in r["Name"].replace(" ", "")]
+             if is_dominant(r["Name"])]
     if not rows or not stats:
         raise SystemExit(f"{sq_csv} / {stats_csv}: no {DOMINANT_KERNEL} entries")
     active = sum(float(r["Counter_Value"]) for r in rows) / len(rows)
@@ -300,7 +307,7 @@ def fp64_executed(csv_path: str) -> dict:
     per = {}
     for r in csv.DictReader(open(csv_path)):
         if (r["Counter_Name"] in weight
-                and DOMINANT_KERNEL.replace(" ", "") in r["Kernel_Name"].replace(" ", "")):
+                and is_dominant(r["Kernel_Name"])):
             per.setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
     if not per:
         raise SystemExit(f"{csv_path}: no FP64 counters of {DOMINANT_KERNEL}")
@@ -677,7 +684,7 @@ def main():
         "fp64_pair_test_flops_per_s": FP64_FLOPS_PER_PAIR * pairs / elapsed,
         "candidates_per_step": cand / a.steps,
         "scatterings_per_step": claims / a.steps,
-        "roofline": {"bound": "alu", "kernel": "k_step (fused): pair stage, FP64 vector",
+        "roofline": {"bound": "alu", "kernel": "k_step / k_step_group (fused): pair stage, FP64 vector",
                      "achieved": fp64_tflops, "peak": FP64_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": fp64_tflops / FP64_PEAK_TFLOPS,
                      "traffic": prof["bytes_per_launch"] if prof else None,
