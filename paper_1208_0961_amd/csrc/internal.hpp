@@ -258,7 +258,8 @@ void launch_observe(const Cells &cur, const Geometry &g, int64_t n, double vol,
 // occupancy of all the others.  persistent_waves
 // > 0 caps the binning grid (persistent waves taking items with a grid
 // stride).  Each step runs the packed tiles on s and, concurrently on
-// side (if not NULL), the one-wave-per-cell events and the scans.
+// side (if not NULL), the one-wave-per-cell events and, in launches that no
+// event observes, the scans (else they follow the tiles on s).
 // between (may be NULL) is called before each step of the run with
 // its kind (0 stream-bin, 1 fused step, 2 collide) and with -1 after the last
 // one: a hook for stage timing.

@@ -3340,9 +3340,15 @@ void launch_batch_run(BatchEvent *ev, const BatchSpaces &sp, uint32_t n_events, 
   // atomics)
   auto step = [&](auto fused, uint32_t j) {
     constexpr bool kF = decltype(fused)::value;
+    // the events due for an observation after this launch
+    const bool observe = sp.obs_nx > 0 && (!obs_at || obs_at[j]);
+    // (an observing launch steps the scans behind the tiles: a scan clears the
+    // counts of the cells that it steps, and a tile that read one of those as
+    // empty would write zeros over the sums of the cell)
+    const bool scan_aside = sp.n_scans > 0 && !observe;
     const bool both =
         sp.n_tiles > 0 &&
-        (sp.n_cells[0] > 0 || sp.n_cells[1] > 0 || sp.n_groups > 0 || sp.n_scans > 0);
+        (sp.n_cells[0] > 0 || sp.n_cells[1] > 0 || sp.n_groups > 0 || scan_aside);
     const SideStream *sd = both ? side : nullptr;
     const hipStream_t s2 = sd ? sd->stream : s;
     fork(s, sd);
@@ -3359,11 +3365,10 @@ void launch_batch_run(BatchEvent *ev, const BatchSpaces &sp, uint32_t n_events, 
       hipLaunchKernelGGL((k_batch_step_cells<kF, kCellCap>), dim3(sp.n_cells[1]), wave, 0, s2,
                          cev, sp.cell_begin[1], n_events, j);
     if (sp.n_scans > 0)
-      hipLaunchKernelGGL((k_batch_step_scan<kF>), dim3(sp.n_scans), wave, 0, s2, cev,
-                         sp.scan_begin, n_events, j);
+      hipLaunchKernelGGL((k_batch_step_scan<kF>), dim3(sp.n_scans), wave, 0,
+                         scan_aside ? s2 : s, cev, sp.scan_begin, n_events, j);
     join(s, sd);
-    // the events due for an observation after this launch
-    if (sp.obs_nx > 0 && (!obs_at || obs_at[j]))
+    if (observe)
       hipLaunchKernelGGL(k_batch_observe, dim3(sp.obs_nx, n_events), dim3(kBlock), 0, s, cev,
                          n_events, j);
   };
