@@ -194,7 +194,9 @@ int cuba_observe(cuba_ctx *ctx, double *T00, double *T0x);
  * Errors: CUBA_EINVAL for NULL. */
 int cuba_observe_moments(cuba_ctx *ctx, double *out);
 
-/* Copies the current state into device arrays of n doubles in id order. */
+/* Copies the current state into device arrays of n doubles in id order.
+ * Writes to no particle of the workspace (from 2^17 particles an index of
+ * their slots goes to its scratch for overflowing cells). */
 int cuba_get_state(cuba_ctx *ctx, double *x, double *y, double *z,
                    double *px, double *py, double *pz);
 

@@ -260,6 +260,7 @@ struct cuba_ctx {
   int cur;
   uint32_t *offsets, *tile_sums;
   double *cell_sums;
+  uint32_t *pool;        // scratch of overflowing cells, more than n words
   DeviceConsts *consts;  // in the workspace
   bool in_library = false;  // set up by cuba_init_static: not freed by cuba_destroy
   // stage timing (cuba_timing_begin / cuba_timing_end)
@@ -560,7 +561,7 @@ int init_context(cuba_ctx *c, const Derived &d, const cuba_params *params, int64
     c->buf[b].sp = (SpillDesc *)(ws + L.spill_desc[b]);
   }
   OverflowPool hpool{};
-  hpool.buf = (uint32_t *)(ws + L.pool);
+  hpool.buf = c->pool = (uint32_t *)(ws + L.pool);
   hpool.hdr = (unsigned long long *)(ws + L.pool_hdr);
   hpool.capacity = L.pool_words;
   SpillDesc hsd[2];
@@ -797,10 +798,10 @@ int cuba_get_state(cuba_ctx *c, double *x, double *y, double *z, double *px,
   if (!c) return fail(CUBA_EINVAL, "ctx is NULL");
   if (c->n > 0 && !(x && y && z && px && py && pz))
     return fail(CUBA_EINVAL, "NULL output array");
-  // the slots' index goes to the idle buffer's ids (no slot of it is in use
-  // between steps, and it holds more than n words)
-  launch_export(c->buf[c->cur], c->d.n_cells, c->n, c->buf[c->cur ^ 1].st.id, x, y, z, px, py,
-                pz, c->next_step - 1u, c->stream);
+  // the slots' index goes to the overflow scratch (more than n words, in use
+  // inside a launch only), so neither buffer of the state is written
+  launch_export(c->buf[c->cur], c->d.n_cells, c->n, c->pool, x, y, z, px, py, pz,
+                c->next_step - 1u, c->stream);
   return check_launch("get_state launch");
 }
 
