@@ -2824,6 +2824,7 @@ __global__ __launch_bounds__(kBlock) void k_observe_cells(Cells cur_arg, uint32_
                                                           double *cell_sums,
                                                           uint32_t binning_step) {
   const GCells cur = binning(to_global(cur_arg), binning_step);
+  constexpr uint32_t kWaveCells = 64u / G;
   const uint32_t gl = lane_id() % G;
   const uint32_t c = (blockIdx.x * kBlock + threadIdx.x) / G;
   const uint32_t cnt = c < n_cells ? cur.count[c] : 0u;
@@ -2835,14 +2836,31 @@ __global__ __launch_bounds__(kBlock) void k_observe_cells(Cells cur_arg, uint32_
     load_momentum(cur.st, base + j, px, py, pz);
     obs_add(px, py, pz, se, sp, sxx);
   }
-  if (cnt > cur.cap) {  // overflowing: its spilled members, in spill order
+  // overflowing cells: one scan of the spill slots by the whole wave, each hit
+  // added in its cell's first lane (a scan by each cell's own G lanes: 357 us
+  // for 321 538 particles, 8 689 of 160 000 cells overflowing, now 113)
+  if (__ballot(cnt > cur.cap) != 0ull) {
     const SpillDesc *const spl = cur.sp;
     const uint32_t ns = min(spl->hdr[2u * cur.q], spl->capacity);
-    for (uint32_t i = gl; i < ns; i += G) {
-      if (spl->cell[i] != c) continue;
-      double px, py, pz;
-      load_momentum(cur.st, spl->base + i, px, py, pz);
-      obs_add(px, py, pz, se, sp, sxx);
+    const uint32_t first = c - lane_id() / G;  // the wave's first cell
+    for (uint32_t i0 = 0; i0 < ns; i0 += 64u) {
+      const uint32_t i = i0 + lane_id();
+      const uint32_t at = i < ns ? spl->cell[i] - first : kWaveCells;
+      double ve = 0.0, vp = 0.0, vxx = 0.0;
+      if (at < kWaveCells) {
+        double px, py, pz;
+        load_momentum(cur.st, spl->base + i, px, py, pz);
+        obs_add(px, py, pz, ve, vp, vxx);
+      }
+      for (uint64_t m = __ballot(at < kWaveCells); m != 0; m &= m - 1ull) {
+        const int l = (int)__builtin_ctzll(m);
+        const double te = __shfl(ve, l), tp = __shfl(vp, l), txx = __shfl(vxx, l);
+        if (lane_id() == G * (uint32_t)__builtin_amdgcn_readlane((int)at, l)) {
+          se += te;
+          sp += tp;
+          sxx += txx;
+        }
+      }
     }
   }
 #pragma unroll
@@ -2988,18 +3006,23 @@ __global__ __launch_bounds__(kBlock) void k_index_by_id(Cells cur_arg, uint32_t 
   const GCells cur = binning(to_global(cur_arg), binning_step);
   const uint32_t gl = lane_id() % G;
   const uint32_t c = (blockIdx.x * kBlock + threadIdx.x) / G;
-  if (c >= n_cells) return;
-  const uint32_t cnt = cur.count[c];
-  const uint32_t n = cnt < cur.cap ? cnt : cur.cap;
-  const size_t base = (size_t)c * cur.cap;
-  for (uint32_t j = gl; j < n; j += G) slot_of[cur.st.id[base + j]] = (uint32_t)(base + j);
-  if (cnt > cur.cap) {  // overflowing: its spilled members
+  // the spilled particles, a thread each, by the first kSpillBlocks blocks (a
+  // search of the spill slots by each overflowing cell: 402 us for 321 538
+  // particles, 8 689 of 160 000 cells overflowing, now 36)
+  constexpr uint32_t kSpillBlocks = 256;
+  if (blockIdx.x < kSpillBlocks) {
     const SpillDesc *const spl = cur.sp;
     const uint32_t ns = min(spl->hdr[2u * cur.q], spl->capacity);
-    for (uint32_t i = gl; i < ns; i += G)
-      if (spl->cell[i] == c)
-        slot_of[cur.st.id[spl->base + i]] = (uint32_t)(spl->base + i);
+    const uint32_t stride = min(gridDim.x, kSpillBlocks) * kBlock;
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < ns; i += stride) {
+      const size_t o = spl->base + i;
+      slot_of[cur.st.id[o]] = (uint32_t)o;
+    }
   }
+  if (c >= n_cells) return;
+  const uint32_t n = occupancy(cur, c);
+  const size_t base = (size_t)c * cur.cap;
+  for (uint32_t j = gl; j < n; j += G) slot_of[cur.st.id[base + j]] = (uint32_t)(base + j);
 }
 
 // Second launch: the records in id order.
