@@ -33,6 +33,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <cstddef>
 #include <type_traits>
 
 #include "internal.hpp"
@@ -679,8 +680,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_carry(uint32_t *offsets,
 // or, in an overflowing cell (ov), for j >= cap spill slot sbase + sidx[j -
 // cap] (at_spill).  ov is uniform over the workgroup, so normal cells take
 // the first form without a per-lane choice.  Once an overflowing cell's
-// slots are listed in LDS (slots), at() reads them there, which keeps fewer
-// values live than the two-part form.
+// slots are listed in LDS (slots, not null), at() reads them there, which
+// keeps fewer values live than the two-part form.
 struct CellView {
   uint32_t c, n, t;
   size_t base;
@@ -694,7 +695,7 @@ struct CellView {
     return base + j;
   }
   __device__ __forceinline__ size_t at(uint32_t j) const {
-    if (ov) return slots[j];
+    if (ov) return slots ? slots[j] : at_spill(j);
     return base + j;
   }
 };
@@ -931,10 +932,10 @@ __device__ __forceinline__ void obs_write_wave(double *obs, uint32_t c, uint32_t
 
 // Wave 0 of an overflowing cell's workgroup: takes scratch from the pool
 // (counter t & 1) for the slots of the cell's spilled members -- and, for a
-// cell larger than the LDS holds, its canonical order, claimed flags and
+// cell of more than kHeld, its canonical order, claimed flags and
 // claims -- and lists those slots (a scan of the spill slots, in increasing
 // order).  Leaves the scratch offset and a success flag in LDS.
-template <bool kFused, uint32_t kCap>
+template <uint32_t kHeld, bool kFused, uint32_t kCap>
 __device__ void find_spilled(const GCells &src, const CellView &cv, CellLds<kFused, kCap> &lds,
                              DevStatus *status) {
   const uint32_t lane = lane_id();
@@ -944,7 +945,7 @@ __device__ void find_spilled(const GCells &src, const CellView &cv, CellLds<kFus
   const uint32_t n = cv.n, nsp = cv.ov ? n - cv.cap : 0u;
   const uint32_t ns = min(sd->hdr[2u * src.q], sd->capacity);
   uint64_t need = nsp;
-  if (n > kCap) need += (uint64_t)n + n / 2u + 1u + (n + 31u) / 32u;
+  if (n > kHeld) need += (uint64_t)n + n / 2u + 1u + (n + 31u) / 32u;
   uint32_t lo = 0, hi = 0;
   if (lane == 0) {
     const unsigned long long b = atomicAdd(&pool->hdr[cv.t & 1u], (unsigned long long)need);
@@ -1177,21 +1178,91 @@ struct ClaimLds {
 struct CellWork {
   CellView cv;
   bool live;     // the later parts are still to do
+  bool mid;      // instead of live: a cell that mid_open took
   bool mom_lds;  // new momenta are in LDS, not written back
 };
 
-// Part 1: the cell's view, and its canonical order in lds.perm.  A cell
-// larger than the LDS holds is stepped here altogether.  Starts with a
-// barrier, so a wave may call it for several cells.
+// A cell of kCap < n <= kCellCap members in the LDS laid out for kCap: the
+// words of CellLds up to its scratch fields hold kCellCap ids (then half as many
+// filtered pairs and as many claims) and kCellCap canonical positions, which
+// leaves no room for the rank's buckets (each lane counts the smaller ids
+// instead, 5 % of the instructions of 700 members), for the claims' momenta
+// (written back to the block) or for an overflowing cell's slots.  So a box
+// whose cells rarely pass kCap keeps the occupancy of kCap's kernels: 24 576
+// cells of 350, half of which hold 700 after every other step, 2.3 ms a step
+// (3.5 with those cells in global scratch, 2.6 in a wave per cell with the LDS
+// for kCellCap); 12 800 such cells of 160 000, the rest empty, 1.40 ms (1.90,
+// 1.34).
+template <uint32_t kCap>
+struct MidLds {
+  uint32_t *id;
+  uint16_t *perm;
+  template <bool kFused>
+  __device__ __forceinline__ explicit MidLds(CellLds<kFused, kCap> &lds)
+      : id(reinterpret_cast<uint32_t *>(&lds)), perm(reinterpret_cast<uint16_t *>(id + kCellCap)) {
+    using Lds = CellLds<kFused, kCap>;
+    static_assert(offsetof(Lds, buf) == 0 && offsetof(Lds, ov_pool_lo) >= kCellCap * 6u,
+                  "ids and positions");
+  }
+};
+
+// Its part 1: the canonical order.
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk>
+__device__ __forceinline__ void mid_open(CellWork &w, const GCells &src, const TraceArgs &tr,
+                                         CellLds<kFused, kCap> &lds) {
+  w.mid = true;
+  uint32_t *const s_id = MidLds<kCap>(lds).id;
+  uint16_t *const s_perm = MidLds<kCap>(lds).perm;
+  CellView &cv = w.cv;
+  const uint32_t lane = lane_id(), n = cv.n, n4 = (n + 3u) & ~3u;
+  const GState &st = src.st;
+  cv.slots = nullptr;
+  cell_sync<kBlk>();
+  for (uint32_t j = lane; j < n4; j += 64u)
+    s_id[j] = j < n ? st.id[cv.at_spill(j)] : 0xFFFFFFFFu;
+  cell_sync<kBlk>();
+  constexpr uint32_t kRows = 4;  // members of a lane ranked together
+  const uint4 *const s_id4 = reinterpret_cast<const uint4 *>(s_id);
+  for (uint32_t j0 = 0; j0 < n; j0 += 64u * kRows) {
+    uint32_t me[kRows], r[kRows];
+#pragma unroll
+    for (uint32_t u = 0; u < kRows; ++u) {
+      const uint32_t j = j0 + 64u * u + lane;
+      me[u] = j < n ? s_id[j] : 0u;
+      r[u] = 0u;
+    }
+    for (uint32_t m = 0; m < n4 / 4u; ++m) {
+      const uint4 v = s_id4[m];
+#pragma unroll
+      for (uint32_t u = 0; u < kRows; ++u)
+        r[u] += (v.x < me[u]) + (v.y < me[u]) + (v.z < me[u]) + (v.w < me[u]);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kRows; ++u) {
+      const uint32_t j = j0 + 64u * u + lane;
+      if (j < n) {
+        s_perm[r[u]] = (uint16_t)j;
+        if (kTrace && tr.perm) tr.perm[tr.offsets[cv.c] + r[u]] = me[u];
+      }
+    }
+  }
+  cell_sync<kBlk>();
+}
+
+// Part 1: the cell's view, and its canonical order in lds.perm.  A cell of
+// more than kCap particles is opened by mid_open up to kCellCap (kMid: kernels
+// of boxes whose blocks exceed kCap; the longer kernels take up to 1 % more),
+// else stepped here altogether.  Starts with a barrier, so a wave may call it
+// for several cells.
 // kBlk: the workgroup is this one wave; else the wave shares it with others
 // and synchronises with itself only.
-template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk>
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk, bool kMid>
 __device__ __forceinline__ void cell_open(CellWork &w, const GCells &src, const GCells &dst,
                                           uint32_t c, uint32_t t, const PairArgs &pa,
                                           const Geometry &g, DevStatus *status,
                                           const TraceArgs &tr, CellLds<kFused, kCap> &lds,
                                           double *obs) {
-  w.live = false;
+  w.live = w.mid = false;
   w.mom_lds = false;
   uint32_t *const s_id = lds.buf;
   uint16_t *const s_perm = lds.perm;
@@ -1213,18 +1284,24 @@ __device__ __forceinline__ void cell_open(CellWork &w, const GCells &src, const 
   // issue ahead of the other waves' pair-test loops, which keep the VALU
   // busy meanwhile; the pair tests run at the base priority.
   __builtin_amdgcn_s_setprio(1);
-  if (cv.ov || cv.n > kCap) {
-    // an overflowing cell: find its spilled members, then step it here, in
-    // LDS if it fits, else (as any cell larger than the LDS) with the
-    // global-memory method
-    find_spilled<kFused, kCap>(src, cv, lds, status);
+  if (kMid ? __builtin_expect(cv.ov, 0) : cv.ov) {
+    // an overflowing cell: find its spilled members, then step it like any
+    // other cell, or if it is too large for that with the global-memory method
+    constexpr uint32_t kHeld = kMid ? kCellCap : kCap;
+    find_spilled<kHeld>(src, cv, lds, status);
     cell_sync<kBlk>();
     if (lds.ov_ok == 0u) return;  // internal error, flagged
     const SpillDesc *const sd = src.sp;
     cv.sbase = sd->base;
     cv.sidx = sd->pool->buf + (((uint64_t)lds.ov_pool_hi << 32) | lds.ov_pool_lo);
-    if (cv.n > kCap) {
+    if (cv.n > kHeld) {
       large_cell_step<kFused, kTrace, kCap>(src, dst, cv, pa, g, status, tr, lds, obs);
+      return;
+    }
+  }
+  if constexpr (kMid) {
+    if (__builtin_expect(cv.n > kCap, 0)) {
+      mid_open<kFused, kTrace, kCap, kBlk>(w, src, tr, lds);
       return;
     }
   }
@@ -1320,31 +1397,26 @@ __device__ __forceinline__ void cell_open(CellWork &w, const GCells &src, const 
   }
 }
 
-// Part 2.  kFiltered: the cell's nf filtered pairs are in lds.buf, in
-// increasing k; else they are found here.
-template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk, bool kFiltered = false>
-__device__ __forceinline__ void cell_pairs(CellWork &w, const GCells &src, const PairArgs &pa,
+// Part 2, on a cell's scratch: its canonical order in s_perm, kFilt filtered
+// pairs in s_filt (filtered: nf of them there already, in increasing k; else
+// they are found here) and its claims, at most n / 2, in s_claim.  kMomCap:
+// claims whose new momenta fit cl.
+template <bool kFused, bool kTrace, bool kBlk, uint32_t kFilt, uint32_t kMomCap, uint32_t kCap>
+__device__ __forceinline__ void pairs_step(CellWork &w, const GCells &src, const PairArgs &pa,
                                            DevStatus *status, const TraceArgs &tr,
-                                           CellLds<kFused, kCap> &lds, const double *obs,
-                                           uint32_t nf = 0) {
+                                           const uint16_t *s_perm, uint32_t *s_filt,
+                                           uint32_t *s_claim, const ClaimLds<kCap> &cl,
+                                           const double *obs, bool filtered, uint32_t nf) {
   const CellView &cv = w.cv;
   const uint32_t lane = lane_id(), n = cv.n;
   const GState &st = src.st;
-  if (n < 2u) return;
-  // filtered pairs and claimed pairs share the id buffer, kCap / 2 each
-  constexpr uint32_t kFilt = kCap / 2, kMomCap = ClaimLds<kCap>::kMax;
-  static_assert(kCap <= kCellCap && kFilt >= 256, "cell capacity");
-  uint32_t *const s_filt = lds.buf;
-  uint32_t *const s_claim = lds.buf + kFilt;
-  const uint16_t *const s_perm = lds.perm;
-  const ClaimLds<kCap> cl(lds);
   uint32_t nclaim = 0;
   // every pair k = 0 .. n(n-1)/2 - 1 (test_pairs), then the exact test
   // and the claims of the filtered ones in increasing k
   const uint32_t npairs = n * (n - 1u) / 2u;
   uint32_t claimed_bits = 0, n_acc = 0;
   __builtin_amdgcn_s_setprio(0);
-  if (!kFiltered && pa.any)
+  if (!filtered && pa.any)
     test_pairs<true, kTrace, kBlk, kFilt>(0u, npairs, cv, pa, st, s_perm, s_filt, nf, s_claim,
                                           nclaim, claimed_bits, n_acc, tr, status);
   if (nf != 0)
@@ -1366,7 +1438,7 @@ __device__ __forceinline__ void cell_pairs(CellWork &w, const GCells &src, const
   // kinematics of the claimed pairs (disjoint: one writer per particle),
   // written back in place, or for the binning below into LDS; a fused
   // step then bins every particle
-  w.mom_lds = kFused && !cv.ov && nclaim <= kMomCap;
+  w.mom_lds = kFused && kMomCap != 0u && !cv.ov && nclaim <= kMomCap;
   for (uint32_t i0 = 0; i0 < nclaim; i0 += 64u) {
     const uint32_t i = i0 + lane;
     const bool active = i < nclaim;
@@ -1402,6 +1474,21 @@ __device__ __forceinline__ void cell_pairs(CellWork &w, const GCells &src, const
     }
   }
   if (kFused || obs) cell_sync<kBlk>();
+}
+
+// Part 2 of a cell that the LDS holds.
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk, bool kFiltered = false>
+__device__ __forceinline__ void cell_pairs(CellWork &w, const GCells &src, const PairArgs &pa,
+                                           DevStatus *status, const TraceArgs &tr,
+                                           CellLds<kFused, kCap> &lds, const double *obs,
+                                           uint32_t nf = 0) {
+  // filtered pairs and claimed pairs share the id buffer, kCap / 2 each
+  constexpr uint32_t kFilt = kCap / 2;
+  static_assert(kCap <= kCellCap && kFilt >= 256, "cell capacity");
+  if (w.cv.n < 2u) return;
+  pairs_step<kFused, kTrace, kBlk, kFilt, ClaimLds<kCap>::kMax, kCap>(
+      w, src, pa, status, tr, lds.perm, lds.buf, lds.buf + kFilt, ClaimLds<kCap>(lds), obs,
+      kFiltered, nf);
 }
 
 // Part 3 (with kFused clears src's count).
@@ -1468,17 +1555,35 @@ __device__ __forceinline__ void cell_close(const CellWork &w, const GCells &src,
   }
 }
 
+// Parts 2 and 3 of a cell that mid_open took.
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk>
+__device__ __forceinline__ void mid_close(CellWork &w, const GCells &src, const GCells &dst,
+                                          const PairArgs &pa, const Geometry &g,
+                                          DevStatus *status, const TraceArgs &tr,
+                                          CellLds<kFused, kCap> &lds, double *obs,
+                                          bool filtered = false, uint32_t nf = 0) {
+  constexpr uint32_t kFilt = kCellCap / 2;
+  const MidLds<kCap> ml(lds);
+  pairs_step<kFused, kTrace, kBlk, kFilt, 0u, kCap>(w, src, pa, status, tr, ml.perm, ml.id,
+                                                    ml.id + kFilt, ClaimLds<kCap>(lds), obs,
+                                                    filtered, nf);
+  cell_close<kFused, kCap>(w, src, dst, g, status, lds, obs);
+}
+
 // Collisions of cell c of src at step t by one wave.  kFused: afterwards
 // stream and bin the cell's particles into dst for step t+1 and clear src's
 // count.
-template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk = true>
+template <bool kFused, bool kTrace, uint32_t kCap, bool kBlk = true, bool kMid = false>
 __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, uint32_t c,
                                           uint32_t t, const PairArgs &pa,
                                           const Geometry &g, DevStatus *status,
                                           const TraceArgs &tr, CellLds<kFused, kCap> &lds,
                                           double *obs = nullptr) {
   CellWork w;
-  cell_open<kFused, kTrace, kCap, kBlk>(w, src, dst, c, t, pa, g, status, tr, lds, obs);
+  cell_open<kFused, kTrace, kCap, kBlk, kMid>(w, src, dst, c, t, pa, g, status, tr, lds, obs);
+  if constexpr (kMid)
+    if (__builtin_expect(w.mid, 0))
+      mid_close<kFused, kTrace, kCap, kBlk>(w, src, dst, pa, g, status, tr, lds, obs);
   if (!w.live) return;
   cell_pairs<kFused, kTrace, kCap, kBlk>(w, src, pa, status, tr, lds, obs);
   cell_close<kFused, kCap>(w, src, dst, g, status, lds, obs);
@@ -1735,7 +1840,7 @@ __device__ __forceinline__ void group_sort(uint32_t nf, uint32_t *list) {
 }
 
 // Cells c0 .. c0 + 3 (those below n_cells) by a workgroup of four waves.
-template <bool kFused, uint32_t kCap, uint32_t kG>
+template <bool kFused, uint32_t kCap, uint32_t kG, bool kMid>
 __device__ __forceinline__ void group_cells_step(const GCells &src, const GCells &dst, uint32_t c0,
                                                 uint32_t n_cells, uint32_t t, const PairArgs &pa,
                                                 const Geometry &g, DevStatus *status,
@@ -1744,14 +1849,16 @@ __device__ __forceinline__ void group_cells_step(const GCells &src, const GCells
   const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
   const TraceArgs none{};
   CellWork w;
-  w.live = false;
+  w.live = w.mid = false;
   w.cv.n = 0u;
   if (c0 + wv < n_cells)
-    cell_open<kFused, false, kCap, false>(w, src, dst, c0 + wv, t, pa, g, status, none, lds[wv],
-                                          obs);
+    cell_open<kFused, false, kCap, false, kMid>(w, src, dst, c0 + wv, t, pa, g, status, none,
+                                                lds[wv], obs);
   if (lane_id() == 0) {
-    q.n[wv] = w.live && !w.cv.ov && w.cv.n > 1u ? w.cv.n : 0u;
-    q.cnt[wv] = 0u;
+    q.n[wv] = (w.live || w.mid) && !w.cv.ov && w.cv.n > 1u ? w.cv.n : 0u;
+    // (a mid cell's group never goes together: its canonical positions lie
+    // elsewhere; the first kListMax + 1 entries of its list stay unused)
+    q.cnt[wv] = w.mid ? kListMax + 1u : 0u;
   }
   // (the ids' buffer becomes the list of filtered pairs, unused entries all ones)
   static_assert(kListAll == 4u * 64u && kListAll <= kCap / 2u, "list");
@@ -1778,6 +1885,15 @@ __device__ __forceinline__ void group_cells_step(const GCells &src, const GCells
     if (wv == 0) group_claim<kFused, kCap, kG>(c0, t, n, pa, src, status, q, lds);
     __syncthreads();
   }
+  if constexpr (kMid) {
+    if (__builtin_expect(w.mid, 0)) {
+      const uint32_t entries = q.cnt[wv];
+      const bool filtered = q.n[wv] != 0u && entries <= kListAll;
+      if (filtered) group_sort(entries, lds[wv].buf);  // (unused ones last)
+      mid_close<kFused, false, kCap, false>(w, src, dst, pa, g, status, none, lds[wv], obs,
+                                            filtered, filtered ? entries - (kListMax + 1u) : 0u);
+    }
+  }
   if (!w.live) return;
   const uint32_t nf = q.cnt[wv];
   if (together && q.n[wv] != 0u) {
@@ -1796,7 +1912,7 @@ constexpr uint32_t kPackedMax = 64;  // particles of a packed unit, and of a cel
 // The cells among c0 .. c_end - 1 (at most 64) that a packed launch left
 // alone (more than kPackedMax particles, or overflowing), stepped one after
 // another by the whole wave.
-template <bool kFused, bool kTrace, uint32_t kCap>
+template <bool kFused, bool kTrace, uint32_t kCap, bool kMid = false>
 __device__ __forceinline__ void large_cells_step(const GCells &src, const GCells &dst,
                                                  uint32_t c0, uint32_t c_end, uint32_t t,
                                                  const PairArgs &pa,
@@ -1810,7 +1926,7 @@ __device__ __forceinline__ void large_cells_step(const GCells &src, const GCells
   while (big != 0) {
     const uint32_t l = (uint32_t)__builtin_ctzll(big);
     big &= big - 1ull;
-    cell_step<kFused, kTrace, kCap>(src, dst, c0 + l, t, pa, g, status, tr, lds, obs);
+    cell_step<kFused, kTrace, kCap, true, kMid>(src, dst, c0 + l, t, pa, g, status, tr, lds, obs);
   }
 }
 
@@ -1941,7 +2057,7 @@ __device__ __forceinline__ void packed_resolve_row(
 // units (more than 64 particles, or overflowing) follow in the same count,
 // each stepped by one wave as in cell_step (if `large`).  The waves meet once, after all
 // have read the tile's counts and before those are cleared.
-template <bool kFused, bool kTrace, bool kLarge>
+template <bool kFused, bool kTrace, bool kLarge, bool kMid>
 __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCells &dst,
                                                   uint32_t c0, uint32_t c_end, uint32_t t,
                                                   const PairArgs &pa, const Geometry &g,
@@ -2143,9 +2259,9 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
   if (kLarge && large) {
     for (uint64_t big = left_out; big != 0; big &= big - 1ull)
       if (unit++ % kPackedWaves == wave)
-        cell_step<kFused, kTrace, kSmallCap, false>(src, dst,
-                                                       c0 + (uint32_t)__builtin_ctzll(big), t, pa,
-                                                       g, status, tr, wlds.cell, obs);
+        cell_step<kFused, kTrace, kSmallCap, false, kMid>(src, dst,
+                                                          c0 + (uint32_t)__builtin_ctzll(big), t,
+                                                          pa, g, status, tr, wlds.cell, obs);
   }
 }
 
@@ -2154,7 +2270,7 @@ __device__ __forceinline__ void packed_cells_step(const GCells &src, const GCell
 // loops).  Five waves per SIMD: the compiler's choice (4, 101-104 VGPRs)
 // made the 32^3 fm^3 set's fused step 5 % slower, six (80 VGPRs, 12
 // spilled) 4 %.
-template <bool kFused, bool kTrace, bool kLarge>
+template <bool kFused, bool kTrace, bool kLarge, bool kMid>
 __global__ __launch_bounds__(64 * kPackedWaves) __attribute__((amdgpu_waves_per_eu(5))) void k_step_packed(
     Cells src_arg, int64_t dst_shift, uint32_t n_cells, uint32_t tile, uint32_t t, PairArgs pa,
     const Geometry *__restrict__ gp, DevStatus *status, TraceArgs tr) {
@@ -2163,12 +2279,12 @@ __global__ __launch_bounds__(64 * kPackedWaves) __attribute__((amdgpu_waves_per_
   const uint32_t c0 = xcd_runs<8>(blockIdx.x, gridDim.x) * tile;
   const uint32_t c_end = min(c0 + tile, n_cells);
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
-  packed_cells_step<kFused, kTrace, kLarge>(src, dst_of(src, dst_shift, t), c0, c_end, t, pa,
+  packed_cells_step<kFused, kTrace, kLarge, kMid>(src, dst_of(src, dst_shift, t), c0, c_end, t, pa,
                                             *gp, status, tr, lds[wave], wave, true);
 }
 
 // One wave per 64 consecutive cells: the cells that the packed launch left.
-template <bool kFused, bool kTrace, uint32_t kCap>
+template <bool kFused, bool kTrace, uint32_t kCap, bool kMid>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_step_large(
     Cells src_arg, Cells dst_arg, uint32_t n_cells,
                                                    uint32_t t, PairArgs pa,
@@ -2179,12 +2295,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   __shared__ CellLds<kFused, kCap> lds;
   const uint32_t c0 = blockIdx.x * 64u;
   const uint32_t c_end = c0 + 64u < n_cells ? c0 + 64u : n_cells;
-  large_cells_step<kFused, kTrace, kCap>(src, dst, c0, c_end, t, pa, g, status, tr, lds);
+  large_cells_step<kFused, kTrace, kCap, kMid>(src, dst, c0, c_end, t, pa, g, status, tr, lds);
 }
 
 // One wave per cell, for the cells that the packed launch left when they are
 // common (a wave that scans 64 of them would step them one after another).
-template <bool kFused, bool kTrace, uint32_t kCap>
+template <bool kFused, bool kTrace, uint32_t kCap, bool kMid>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<kCap>()))) void k_step_over(
     Cells src_arg, int64_t dst_shift,
                                                   uint32_t t, PairArgs pa,
@@ -2195,7 +2311,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<k
   const uint32_t c = xcd_runs<8>(blockIdx.x, gridDim.x);
   const uint32_t cnt = src.count[c];
   if (cnt <= kPackedMax && cnt <= src.cap) return;
-  cell_step<kFused, kTrace, kCap>(src, dst_of(src, dst_shift, t), c, t, pa, *gp, status, tr,
+  cell_step<kFused, kTrace, kCap, true, kMid>(src, dst_of(src, dst_shift, t), c, t, pa, *gp, status, tr,
                                   lds);
 }
 
@@ -2205,26 +2321,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<k
 // pair loop, which spills scalar registers into vector lanes and reloads them
 // in the loop.  Derived from src, the dst pointers stay known to address
 // global memory.
-template <bool kFused, uint32_t kCap>
+template <bool kFused, uint32_t kCap, bool kMid>
 __global__ __launch_bounds__(64 * kGroup) __attribute__((amdgpu_waves_per_eu(cell_waves<kCap>()))) void k_step_group(
     Cells src_arg, int64_t dst_shift, uint32_t n_cells, uint32_t t, PairArgs pa,
     const Geometry *__restrict__ gp, DevStatus *status) {
   const GCells src = binning(to_global(src_arg), t);
   __shared__ CellLds<kFused, kCap> lds[kGroup];
   __shared__ GroupLds<kGroup> q;
-  group_cells_step<kFused, kCap, kGroup>(src, dst_of(src, dst_shift, t),
+  group_cells_step<kFused, kCap, kGroup, kMid>(src, dst_of(src, dst_shift, t),
                                          xcd_runs<2>(blockIdx.x, gridDim.x) * kGroup, n_cells, t,
                                          pa, *gp, status, q, lds, nullptr);
 }
 
-template <bool kFused, bool kTrace, uint32_t kCap>
+template <bool kFused, bool kTrace, uint32_t kCap, bool kMid>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<kCap>()))) void k_step(
     Cells src_arg, int64_t dst_shift, uint32_t t,
                                              PairArgs pa, const Geometry *__restrict__ gp,
                                              DevStatus *status, TraceArgs tr) {
   const GCells src = binning(to_global(src_arg), t);
   __shared__ CellLds<kFused, kCap> lds;
-  cell_step<kFused, kTrace, kCap>(src, dst_of(src, dst_shift, t),
+  cell_step<kFused, kTrace, kCap, true, kMid>(src, dst_of(src, dst_shift, t),
                                   xcd_runs<8>(blockIdx.x, gridDim.x), t, pa, *gp, status, tr,
                                   lds);
 }
@@ -2739,7 +2855,7 @@ __global__ __launch_bounds__(64 * kPackedWaves) __attribute__((amdgpu_waves_per_
   const uint32_t c0 = (unit - E->tile_begin) * E->tile;
   const uint32_t c_end = min(c0 + E->tile, E->n_cells);
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64u));
-  packed_cells_step<kFused, false, true>(src, dst_of(src, shift, t), c0, c_end, t, pa, E->g,
+  packed_cells_step<kFused, false, true, false>(src, dst_of(src, shift, t), c0, c_end, t, pa, E->g,
                                          E->status, TraceArgs{}, lds[wave], wave,
                                          src.cap <= kSmallCap, obs_target(E, j));
 }
@@ -2798,7 +2914,7 @@ __global__ __launch_bounds__(64 * kGroup) __attribute__((amdgpu_waves_per_eu(cel
   const GCells src = binning(to_global(E->buf[s]), t);
   const int64_t shift = (const char *)E->buf[s ^ 1u].st.rec - (const char *)E->buf[s].st.rec;
   const PairArgs pa = E->pa;
-  group_cells_step<kFused, kSmallCap, kGroup>(src, dst_of(src, shift, t),
+  group_cells_step<kFused, kSmallCap, kGroup, false>(src, dst_of(src, shift, t),
                                               (unit - E->cell_begin) * kGroup, E->n_cells, t, pa,
                                               E->g, E->status, q, lds, obs_target(E, j));
 }
@@ -3180,7 +3296,8 @@ void join(hipStream_t s, const SideStream *side) {
   (void)hipStreamWaitEvent(s, side->join, 0);
 }
 
-template <bool kFused, bool kTrace, uint32_t kCap>
+// kMid: blocks larger than kCap (see cell_open).
+template <bool kFused, bool kTrace, uint32_t kCap, bool kMid>
 void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint32_t lanes,
                      uint32_t t, const PairArgs &pa, const Geometry &g, DevStatus *status,
                      const TraceArgs &tr, hipStream_t s, const SideStream *side,
@@ -3205,14 +3322,14 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
   }
   if constexpr (!kTrace) {
     if (kCap == kSmallCap && lanes == 0 && dev.group) {
-      launch_timed(k_step_group<kFused, kSmallCap>, dim3((n_cells + kGroup - 1) / kGroup),
+      launch_timed(k_step_group<kFused, kSmallCap, kMid>, dim3((n_cells + kGroup - 1) / kGroup),
                    dim3(64 * kGroup), s, dev.ev_start, dev.ev_stop, src, shift, n_cells, t, pa,
                    dev.g, status);
       return;
     }
   }
   if (lanes == 0 || lanes == kWideCells) {
-    launch_timed(k_step<kFused, kTrace, kCap>, dim3(n_cells), block, s, dev.ev_start,
+    launch_timed(k_step<kFused, kTrace, kCap, kMid>, dim3(n_cells), block, s, dev.ev_start,
                  dev.ev_stop, src, shift, t, pa, dev.g, status, tr);
     return;
   }
@@ -3221,7 +3338,7 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
   // steps them itself
   if constexpr (!kTrace && kCap == kSmallCap) {
     if (dev.over_span != 1) {
-      launch_timed(k_step_packed<kFused, kTrace, true>, grid, wide, s, dev.ev_start, dev.ev_stop,
+      launch_timed(k_step_packed<kFused, kTrace, true, kMid>, grid, wide, s, dev.ev_start, dev.ev_stop,
                    src, shift, n_cells, dev.tile, t, pa, dev.g, status, tr);
       return;
     }
@@ -3231,32 +3348,32 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
   // by events recorded around the whole launch
   if (dev.ev_start) (void)hipEventRecord(dev.ev_start, s);
   fork(s, side);
-  hipLaunchKernelGGL((k_step_packed<kFused, kTrace, false>), grid, wide, 0, s, src, shift,
+  hipLaunchKernelGGL((k_step_packed<kFused, kTrace, false, false>), grid, wide, 0, s, src, shift,
                      n_cells, dev.tile, t, pa, dev.g, status, tr);
   hipStream_t so = side ? side->stream : s;
   if (dev.over_span == 1)
-    hipLaunchKernelGGL((k_step_over<kFused, kTrace, kCap>), dim3(n_cells), block, 0, so, src,
+    hipLaunchKernelGGL((k_step_over<kFused, kTrace, kCap, kMid>), dim3(n_cells), block, 0, so, src,
                        shift, t, pa, dev.g, status, tr);
   else
-    hipLaunchKernelGGL((k_step_large<kFused, kTrace, kCap>), dim3((n_cells + 63) / 64), block,
+    hipLaunchKernelGGL((k_step_large<kFused, kTrace, kCap, kMid>), dim3((n_cells + 63) / 64), block,
                        0, so, src, dst, n_cells, t, pa, g, status, tr);
   join(s, side);
   if (dev.ev_stop) (void)hipEventRecord(dev.ev_stop, s);
 }
 
-template <uint32_t kCap>
+template <uint32_t kCap, bool kMid>
 void launch_step_any(const Cells &src, const Cells &dst, bool fused, uint32_t n_cells,
                      uint32_t lanes, uint32_t t, const PairArgs &pa, const Geometry &g,
                      DevStatus *status, const TraceArgs *trace, hipStream_t s,
                      const SideStream *side, const StepDevice &dev) {
   if (trace)
-    launch_step_cap<false, true, kCap>(src, dst, n_cells, lanes, t, pa, g, status, *trace, s,
+    launch_step_cap<false, true, kCap, false>(src, dst, n_cells, lanes, t, pa, g, status, *trace, s,
                                        side, dev);
   else if (fused)
-    launch_step_cap<true, false, kCap>(src, dst, n_cells, lanes, t, pa, g, status,
+    launch_step_cap<true, false, kCap, kMid>(src, dst, n_cells, lanes, t, pa, g, status,
                                        TraceArgs{}, s, side, dev);
   else
-    launch_step_cap<false, false, kCap>(src, dst, n_cells, lanes, t, pa, g, status,
+    launch_step_cap<false, false, kCap, kMid>(src, dst, n_cells, lanes, t, pa, g, status,
                                         TraceArgs{}, s, side, dev);
 }
 
@@ -3272,12 +3389,15 @@ void launch_step(const Cells &src, const Cells &dst, bool fused, int64_t n_cells
   }
   // cells of at most 512 slots, or particles, use the kernels with half the
   // LDS (the wide kernel by slots alone)
-  if (src.cap <= kSmallCap || (dev.fits_small && lanes != kWideCells && !trace))
-    launch_step_any<kSmallCap>(src, dst, fused, (uint32_t)n_cells, lanes, t, pa, g, status,
-                               trace, s, side, dev);
+  if (src.cap <= kSmallCap)
+    launch_step_any<kSmallCap, false>(src, dst, fused, (uint32_t)n_cells, lanes, t, pa, g, status,
+                                      trace, s, side, dev);
+  else if (dev.fits_small && lanes != kWideCells && !trace)
+    launch_step_any<kSmallCap, true>(src, dst, fused, (uint32_t)n_cells, lanes, t, pa, g, status,
+                                     trace, s, side, dev);
   else
-    launch_step_any<kCellCap>(src, dst, fused, (uint32_t)n_cells, lanes, t, pa, g, status,
-                              trace, s, side, dev);
+    launch_step_any<kCellCap, false>(src, dst, fused, (uint32_t)n_cells, lanes, t, pa, g, status,
+                                     trace, s, side, dev);
 }
 
 namespace {
