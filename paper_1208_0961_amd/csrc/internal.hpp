@@ -216,6 +216,7 @@ struct StepDevice {
   uint32_t over_span;
   uint32_t tile;   // cells a workgroup of the packed kernel takes (4 .. 64)
   uint32_t waves;  // waves per cell of the wide kernel: 4, 8 or 16
+  uint32_t ahead;  // slots of a cell that it loads before it knows the count
   bool group;      // waves of four cells share their pairs (lanes = 0, small LDS)
   bool fits_small; // the cells hold at most kFitsSmall particles at init
   // stage timing: events that the launch records at its start and end (on

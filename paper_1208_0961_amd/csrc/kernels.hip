@@ -2350,7 +2350,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<k
 // cell leaves most SIMDs idle and the step is one cell's chain of phases.
 // A workgroup of kW waves:
 //   1. loads every particle into registers (kCap / 64 kW per thread; the
-//      slots' loads do not wait for the count), ids into LDS;
+//      first `ahead` slots without waiting for the count), ids into LDS;
 //   2. ranks the ids and stores the momenta in canonical order in LDS, where
 //      the later phases read them: no further global load;
 //   3. tests the pairs in rounds: wave w filters the w-th of kW consecutive
@@ -2465,8 +2465,9 @@ __device__ __forceinline__ void wide_claim(uint32_t na, const uint32_t *list, Ld
 
 template <bool kFused, uint32_t kCap, uint32_t kW>
 __device__ __forceinline__ void wide_cell_step(const GCells &src, const GCells &dst, uint32_t c,
-                                               uint32_t t, const PairArgs &pa, const Geometry &g,
-                                               DevStatus *status, WideLds<kFused, kCap, kW> &lds) {
+                                               uint32_t ahead, uint32_t t, const PairArgs &pa,
+                                               const Geometry &g, DevStatus *status,
+                                               WideLds<kFused, kCap, kW> &lds) {
   constexpr uint32_t kT = 64u * kW, kPer = kCap / kT;
   static_assert(kPer * kT == kCap && kCap <= kCellCap, "whole particles per thread");
   const uint32_t tid = threadIdx.x, lane = lane_id();
@@ -2476,7 +2477,7 @@ __device__ __forceinline__ void wide_cell_step(const GCells &src, const GCells &
 #pragma unroll
   for (uint32_t i = 0; i < kPer; ++i) {
     q[i] = Particle{};
-    if (tid + i * kT < src.cap) q[i] = load_particle(src.st, base + tid + i * kT);
+    if (tid + i * kT < ahead) q[i] = load_particle(src.st, base + tid + i * kT);
   }
   const uint32_t n = src.count[c];
   if (n > src.cap) {
@@ -2485,6 +2486,13 @@ __device__ __forceinline__ void wide_cell_step(const GCells &src, const GCells &
     return;
   }
   if (c == 0 && tid == 0) clear_idle_scratch(src, t);
+  if (__builtin_expect(n > ahead, 0)) {
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      const uint32_t j = tid + i * kT;
+      if (j >= ahead && j < n) q[i] = load_particle(src.st, base + j);
+    }
+  }
 
   // ids to LDS, padded to a multiple of 4 with an id no particle has
   uint32_t *const s_id = lds.cell.buf;
@@ -2709,16 +2717,25 @@ __device__ __forceinline__ void wide_cell_step(const GCells &src, const GCells &
   if (tid == 0) src.count[c] = 0u;
 }
 
+// Waves per SIMD: four waves a cell with four particles a thread would take
+// 133 VGPRs and three waves, which leaves the last of 900 cells for a second
+// round (900 cells of 40 in blocks of 600: 15.9 -> 12.2 us a step).
+template <uint32_t kCap, uint32_t kW>
+constexpr int wide_min_waves() {
+  return kCap / (64u * kW) == 4u ? 4 : (int)(kW / 4u);
+}
+
 template <bool kFused, uint32_t kCap, uint32_t kW>
-__global__ __launch_bounds__(64 * kW) void k_step_wide(Cells src_arg, int64_t dst_shift,
-                                                       uint32_t t, PairArgs pa,
+__global__ __launch_bounds__(64 * kW) __attribute__((amdgpu_waves_per_eu(wide_min_waves<kCap, kW>()))) void k_step_wide(Cells src_arg, int64_t dst_shift,
+                                                       uint32_t ahead, uint32_t t, PairArgs pa,
                                                        const Geometry *__restrict__ gp,
                                                        DevStatus *status) {
   const GCells src = binning(to_global(src_arg), t);
   __shared__ WideLds<kFused, kCap, kW> lds;
   const Geometry g = *gp;
   wide_cell_step<kFused, kCap, kW>(src, dst_of(src, dst_shift, t),
-                                   xcd_runs<8>(blockIdx.x, gridDim.x), t, pa, g, status, lds);
+                                   xcd_runs<8>(blockIdx.x, gridDim.x), ahead, t, pa, g,
+                                   status, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -3310,7 +3327,8 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
     const auto wide = [&](auto waves) {
       constexpr uint32_t kW = decltype(waves)::value;
       launch_timed(k_step_wide<kFused, kCap, kW>, dim3(n_cells), dim3(64 * kW), s, dev.ev_start,
-                   dev.ev_stop, src, shift, t, pa, dev.g, status);
+                   dev.ev_stop, src, shift, src.cap < dev.ahead ? src.cap : dev.ahead, t, pa,
+                   dev.g, status);
     };
     if (dev.waves == 4)
       wide(std::integral_constant<uint32_t, 4>{});
