@@ -680,13 +680,13 @@ __global__ __launch_bounds__(kBlock) void k_scan_carry(uint32_t *offsets,
 // or, in an overflowing cell (ov), for j >= cap spill slot sbase + sidx[j -
 // cap] (at_spill).  ov is uniform over the workgroup, so normal cells take
 // the first form without a per-lane choice.  Once an overflowing cell's
-// slots are listed in LDS (slots, not null), at() reads them there, which
-// keeps fewer values live than the two-part form.
+// slots are listed in LDS (slots; unless unlisted), at() reads them there,
+// which keeps fewer values live than the two-part form.
 struct CellView {
   uint32_t c, n, t;
   size_t base;
   uint32_t cap;
-  bool ov;
+  bool ov, unlisted;
   size_t sbase;
   const uint32_t *sidx;
   const uint32_t *slots;
@@ -695,7 +695,7 @@ struct CellView {
     return base + j;
   }
   __device__ __forceinline__ size_t at(uint32_t j) const {
-    if (ov) return slots ? slots[j] : at_spill(j);
+    if (ov) return unlisted ? at_spill(j) : slots[j];
     return base + j;
   }
 };
@@ -1216,7 +1216,7 @@ __device__ __forceinline__ void mid_open(CellWork &w, const GCells &src, const T
   CellView &cv = w.cv;
   const uint32_t lane = lane_id(), n = cv.n, n4 = (n + 3u) & ~3u;
   const GState &st = src.st;
-  cv.slots = nullptr;
+  cv.unlisted = true;
   cell_sync<kBlk>();
   for (uint32_t j = lane; j < n4; j += 64u)
     s_id[j] = j < n ? st.id[cv.at_spill(j)] : 0xFFFFFFFFu;
@@ -1275,6 +1275,7 @@ __device__ __forceinline__ void cell_open(CellWork &w, const GCells &src, const 
   cv.cap = src.cap;
   cv.n = src.count[cv.c];
   cv.ov = cv.n > src.cap;
+  cv.unlisted = false;
   cv.sbase = 0;
   cv.sidx = nullptr;
   cv.slots = lds.sorted;
@@ -1284,7 +1285,7 @@ __device__ __forceinline__ void cell_open(CellWork &w, const GCells &src, const 
   // issue ahead of the other waves' pair-test loops, which keep the VALU
   // busy meanwhile; the pair tests run at the base priority.
   __builtin_amdgcn_s_setprio(1);
-  if (kMid ? __builtin_expect(cv.ov, 0) : cv.ov) {
+  if (kMid ? __builtin_expect(cv.ov, 0) : cv.ov || cv.n > kCap) {
     // an overflowing cell: find its spilled members, then step it like any
     // other cell, or if it is too large for that with the global-memory method
     constexpr uint32_t kHeld = kMid ? kCellCap : kCap;
@@ -2350,7 +2351,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<k
 // cell leaves most SIMDs idle and the step is one cell's chain of phases.
 // A workgroup of kW waves:
 //   1. loads every particle into registers (kCap / 64 kW per thread; the
-//      first `ahead` slots without waiting for the count), ids into LDS;
+//      slots' loads do not wait for the count, with kSome only those of the
+//      first `ahead` slots), ids into LDS;
 //   2. ranks the ids and stores the momenta in canonical order in LDS, where
 //      the later phases read them: no further global load;
 //   3. tests the pairs in rounds: wave w filters the w-th of kW consecutive
@@ -2463,7 +2465,7 @@ __device__ __forceinline__ void wide_claim(uint32_t na, const uint32_t *list, Ld
   }
 }
 
-template <bool kFused, uint32_t kCap, uint32_t kW>
+template <bool kFused, uint32_t kCap, uint32_t kW, bool kSome>
 __device__ __forceinline__ void wide_cell_step(const GCells &src, const GCells &dst, uint32_t c,
                                                uint32_t ahead, uint32_t t, const PairArgs &pa,
                                                const Geometry &g, DevStatus *status,
@@ -2477,7 +2479,7 @@ __device__ __forceinline__ void wide_cell_step(const GCells &src, const GCells &
 #pragma unroll
   for (uint32_t i = 0; i < kPer; ++i) {
     q[i] = Particle{};
-    if (tid + i * kT < ahead) q[i] = load_particle(src.st, base + tid + i * kT);
+    if (tid + i * kT < (kSome ? ahead : src.cap)) q[i] = load_particle(src.st, base + tid + i * kT);
   }
   const uint32_t n = src.count[c];
   if (n > src.cap) {
@@ -2486,7 +2488,7 @@ __device__ __forceinline__ void wide_cell_step(const GCells &src, const GCells &
     return;
   }
   if (c == 0 && tid == 0) clear_idle_scratch(src, t);
-  if (__builtin_expect(n > ahead, 0)) {
+  if (kSome && __builtin_expect(n > ahead, 0)) {
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) {
       const uint32_t j = tid + i * kT;
@@ -2719,13 +2721,13 @@ __device__ __forceinline__ void wide_cell_step(const GCells &src, const GCells &
 
 // Waves per SIMD: four waves a cell with four particles a thread would take
 // 133 VGPRs and three waves, which leaves the last of 900 cells for a second
-// round (900 cells of 40 in blocks of 600: 15.9 -> 12.2 us a step).
+// round (900 cells of 40 in blocks of 600: 15.8 -> 12.5 us a step).
 template <uint32_t kCap, uint32_t kW>
 constexpr int wide_min_waves() {
   return kCap / (64u * kW) == 4u ? 4 : (int)(kW / 4u);
 }
 
-template <bool kFused, uint32_t kCap, uint32_t kW>
+template <bool kFused, uint32_t kCap, uint32_t kW, bool kSome>
 __global__ __launch_bounds__(64 * kW) __attribute__((amdgpu_waves_per_eu(wide_min_waves<kCap, kW>()))) void k_step_wide(Cells src_arg, int64_t dst_shift,
                                                        uint32_t ahead, uint32_t t, PairArgs pa,
                                                        const Geometry *__restrict__ gp,
@@ -2733,7 +2735,7 @@ __global__ __launch_bounds__(64 * kW) __attribute__((amdgpu_waves_per_eu(wide_mi
   const GCells src = binning(to_global(src_arg), t);
   __shared__ WideLds<kFused, kCap, kW> lds;
   const Geometry g = *gp;
-  wide_cell_step<kFused, kCap, kW>(src, dst_of(src, dst_shift, t),
+  wide_cell_step<kFused, kCap, kW, kSome>(src, dst_of(src, dst_shift, t),
                                    xcd_runs<8>(blockIdx.x, gridDim.x), ahead, t, pa, g,
                                    status, lds);
 }
@@ -3326,9 +3328,14 @@ void launch_step_cap(const Cells &src, const Cells &dst, uint32_t n_cells, uint3
   if (lanes == kWideCells && !kTrace) {
     const auto wide = [&](auto waves) {
       constexpr uint32_t kW = decltype(waves)::value;
-      launch_timed(k_step_wide<kFused, kCap, kW>, dim3(n_cells), dim3(64 * kW), s, dev.ev_start,
-                   dev.ev_stop, src, shift, src.cap < dev.ahead ? src.cap : dev.ahead, t, pa,
-                   dev.g, status);
+      const auto launch = [&](auto kernel) {
+        launch_timed(kernel, dim3(n_cells), dim3(64 * kW), s, dev.ev_start, dev.ev_stop, src,
+                     shift, dev.ahead, t, pa, dev.g, status);
+      };
+      if (dev.ahead < src.cap)
+        launch(k_step_wide<kFused, kCap, kW, true>);
+      else
+        launch(k_step_wide<kFused, kCap, kW, false>);
     };
     if (dev.waves == 4)
       wide(std::integral_constant<uint32_t, 4>{});
