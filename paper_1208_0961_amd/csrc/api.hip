@@ -377,21 +377,21 @@ uint32_t packed_tile(const uint32_t over[4], int64_t n, int64_t n_cells) {
 }
 
 // Whether the waves of four cells share their pairs (one wave per cell else):
-// the mean occupancy at least 50, 60 from 16 384 cells, and K mean^2, which is
-// half the filtered pairs of a mean cell, at most 12 (beyond, the exact tests
-// and claims weigh as much as the shared filter saves), 100 from a mean of 110
-// (a cell's list holds 256).  Speed-up over one wave per cell by the mean on
-// 11 323 / 40 000 cells, at K mean^2 = 0.08 mean: 57 1.04 / 1.00, 70 1.05 /
-// 1.03, 85 1.09 / 1.07, 105 1.11 / 1.10, 125 1.15 / 1.12, 160 1.15 / 1.18, 220
-// 1.14 / 1.17; at 0.16 mean: 57 1.04 / 1.00, 85 1.05 / 1.04, 125 1.08 / 1.08; at
-// 0.33 mean: 70 1.03 / 0.97, 85 1.01 / 0.98, 105 1.01 / 1.00, 125 1.04 / 1.03,
-// 220 1.11 / 1.12.  (3 600 cells of 85: 0.97.)  In a batch 100 throughout: 24
-// ensemble events, 25 steps, 12.95 -> 12.63 ms.
+// dense cells of few filtered pairs.  A cell of n has K n^2 of them (a share 2K
+// of its n^2 / 2 pairs passes the filter), K n a particle, whose exact tests
+// and claims sharing does not shorten: up to 0.3 a particle of the mean cell, and
+// a mean of 50, from 16 384 cells and in batches 66.  Speed-up over one wave per
+// cell at 0.05 / 0.2 / 0.3 / 0.4 / 0.6 / 0.9 a particle, on 10 000 cells: mean 50
+// 1.01 / 1.02 / 1.02 / 1.01 / 0.93 / 0.89, 75 1.09 / 1.06 / 1.03 / 0.98 / 0.94 /
+// 0.90, 125 1.14 / 1.10 / 1.05 / 1.02 / 0.97 / 0.93, 220 1.15 / 1.10 / 1.09 / 1.07 /
+// 1.02 / 0.80; on 40 000: mean 60 0.97 / 0.97 / 0.96 / 0.94 / 0.88 / 0.83, 75 1.03 /
+// 1.02 / 0.99 / 0.95 / 0.89 / 0.86, 125 1.12 / 1.10 / 1.03 / 0.99 / 0.96 / 0.91.  24
+// events of 2 500 cells: mean 50 0.96 at 0.06, 70 1.04 / 1.00 / 0.81 at 0.04 / 0.36
+// / 1.4, 100 1.09 / 1.08 / 0.89 at 0.03 / 0.25 / 1.  (3 600 cells of 85: 0.97.)
 constexpr int64_t kGroupMinCells = 6000;
 bool shares_pairs(int64_t n, int64_t n_cells, double kfac, bool plain) {
   const double mean = (double)n / (double)n_cells;
-  return mean >= (n_cells < 16384 ? 50.0 : 60.0) &&
-         kfac * mean * mean <= (plain && mean < 110.0 ? 12.0 : 100.0);
+  return mean >= (plain && n_cells < 16384 ? 50.0 : 66.0) && kfac * mean <= 0.3;
 }
 
 // Waves per cell of the wide kernel (us a step with 4 / 8 / 16 waves): 100
