@@ -355,12 +355,18 @@ int apply_dt(cuba_ctx *c, double dt) {
 // Cells a workgroup (four waves) of the packed kernel takes: 64, or fewer
 // while the box has too few workgroups to fill the chip and a workgroup of
 // its dense cells more particles than four units hold.  10 000 cells of 16:
-// 64 us a step in 157 tiles of 64 cells, 20 us in 1 250 of 8; 160 000 cells of
-// 2: 32 us in tiles of 64, 36 us in tiles of 32, whose waves are half idle.
+// 64 us a step in 157 tiles of 64 cells, 17 us in 1 250 of 8; 160 000 cells of
+// 2: 31 us in tiles of 64, 82 us in tiles of 8, whose waves are half idle.  Some
+// 1 280 workgroups run at once, and a few more take the time of twice as many:
+// so not past that number, unless each wave has two units to step one after
+// the other.  us a step in the larger / the smaller tiles: 10 000 cells of 16, 8
+// / 4 cells a tile, 17.3 / 24.1; 13 000 of 10, 16 / 8, 14.1 / 19.1; 40 000 of 4, 32
+// / 16, 13.7 / 18.1; but 10 500 in halves of 2 and 17, 16 / 8, 19.1 / 14.7, 44 100
+// in halves of 4 and 30, 64 / 32, 102 / 64.
 // The dense cells' occupancy: 7/4 of the mean, or a value of the densest class
-// of the initial histogram that holds an eighth of the cells (halves of 17
-// and 2 a cell on 6 848 cells: 21 us a step with tiles by the mean, 15 us with
-// tiles by the dense half, 17 us with one wave per cell).
+// of the initial histogram that holds an eighth of the cells, if that is more
+// (halves of 17 and 2 a cell on 6 848 cells: 21 us a step with tiles by the mean,
+// 15 us with tiles by the dense half, 17 us with one wave per cell).
 constexpr int64_t kPackedTiles = 1280, kPackedTileParticles = 224;
 uint32_t packed_tile(const uint32_t over[4], int64_t n, int64_t n_cells) {
   int64_t dense = 7 * n / (4 * n_cells) + 1;
@@ -369,11 +375,11 @@ uint32_t packed_tile(const uint32_t over[4], int64_t n, int64_t n_cells) {
       dense = 14 << k < dense ? dense : 14 << k;
       break;
     }
-  uint32_t tile = 64;
-  while (tile > 4 && n_cells < (int64_t)tile * kPackedTiles &&
-         (int64_t)tile * dense > kPackedTileParticles)
+  int64_t tile = 64;
+  while (tile > 4 && n_cells < tile * kPackedTiles && tile * dense > kPackedTileParticles &&
+         (n_cells <= tile / 2 * kPackedTiles || tile * dense >= 2 * kPackedTileParticles))
     tile /= 2;
-  return tile;
+  return (uint32_t)tile;
 }
 
 // Whether the waves of four cells share their pairs (one wave per cell else):
