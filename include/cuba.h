@@ -237,8 +237,9 @@ int cuba_sync(cuba_ctx *ctx);
  * most 64 particles, one wave a unit and one lane a particle, testing pairs
  * with the Philox filter first and the exact test in compacted rows; cells
  * of more than 64 particles take a wave each.  For sparse boxes and boxes of
- * dense and sparse regions.  The number is the lanes per cell of the kernel
- * that streams and bins a run's first step (1: 16).  128: a workgroup of 4, 8
+ * dense and sparse regions; with 8 to 64 a box of more than 30 particles a cell
+ * takes a wave per cell as with 0.  The number is the lanes per cell of the
+ * kernel that streams and bins a run's first step (1: 16).  128: a workgroup of 4, 8
  * or 16 waves per cell, which split its pair tests (the first wave claims
  * every accepted pair in increasing pair order); for boxes of few dense
  * cells.  cuba_init chooses from the initial occupancy and
