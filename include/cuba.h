@@ -339,7 +339,7 @@ size_t cuba_batch_workspace_bytes(int32_t max_slots);
  * cuba_batch_workspace_bytes(max_slots), 256-byte aligned, owned by the
  * caller.  max_slots: 1 .. 65535, else CUBA_EINVAL.  stream: hipStream_t (must not be NULL if graphs are enabled).
  * The batch also creates one stream of its own (default priority), on which
- * the kernels of a step that are independent of the small-cell kernel run
+ * the kernels of a step that are independent of the packed kernel run
  * concurrently, joined back into `stream` before the next step, and two
  * pinned host buffers through which a changed event table is uploaded
  * without waiting for the stream. */

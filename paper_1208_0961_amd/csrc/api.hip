@@ -321,7 +321,6 @@ void drop_timing(cuba_ctx *c) {
   c->step_launches = 0;
 }
 
-// Device copy of the geometry.
 // The cells that the packed kernel's units leave out take a launch with a
 // wave per cell once they average more than one in 64 (by the initial
 // histogram).

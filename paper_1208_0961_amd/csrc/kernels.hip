@@ -2895,9 +2895,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                                             TraceArgs{}, lds, obs_target(E, j));
 }
 
-// One wave per cell of the events stepped one wave per cell.  Held to the
-// register budget of 5 waves per SIMD, as the plain kernel (it fits without
-// scratch; the event lookup would otherwise push it 1 register over).
+// One wave per cell of the events stepped one wave per cell, held to the
+// register budget of the plain kernel (cell_waves).
 template <bool kFused, uint32_t kCap>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(cell_waves<kCap>()))) void k_batch_step_cells(
     const BatchEvent *__restrict__ ev,

@@ -1,10 +1,10 @@
-"""Four cells whose waves share their pairs (boxes of 6000 cells and more,
-means of 50 and more, few filtered pairs): groups past the last cell, empty
-and single-particle cells, cells whose list of filtered pairs is long or overflows and
-cells past their block (each then taken by its own wave), fused and
-collide-only steps against one oracle step, and the batched kernel against
-the lone run.  And cells that outgrow the small LDS inside a block that holds
-them, which take the global-memory path."""
+"""Boxes of 6000 cells and more with means around 50 and 110 and few filtered
+pairs, most of which take the kernel in which four cells share their pairs
+(test_gpu_group_lists.py asserts that its boxes do, and overflows the lists):
+groups past the last cell, cells whose list of filtered pairs is long and cells
+past their block (each then taken by its own wave), fused and collide-only
+steps against one oracle step, and a batched event against the lone run.  And
+cells that outgrow the small LDS inside a block that holds them."""
 import numpy as np
 import pytest
 

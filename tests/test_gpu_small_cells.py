@@ -1,6 +1,6 @@
-"""Parity of the small-cell kernels (several cells per wave, one particle per
-lane, larger cells stepped by the whole wave) with the CPU oracle, for every
-lanes-per-cell setting.
+"""Parity of the packed kernel (whole cells packed into units of up to 64
+particles, one particle per lane, larger cells stepped by a wave each) with the
+CPU oracle, for every lanes-per-cell setting, 0 and 128 beside it.
 
 cuba_trace_step runs the collision kernel of the context's setting, so the
 trace comparison checks that kernel's decisions (cells, canonical order,

@@ -1,15 +1,12 @@
-"""Two waves per cell (cuba_set_cell_lanes(ctx, 128)): the pair range of a
-cell split over a workgroup of two waves, the second filtering its half
-into its own buffer and the first resolving and claiming every filtered pair
-in increasing pair order.  The decisions and the arithmetic are those of one
-wave per cell, so:
+"""Several waves per cell (cuba_set_cell_lanes(ctx, 128)): a workgroup of 4,
+8 or 16 waves per cell, each filtering and testing its share of the pairs into
+a list of its own, the first claiming every accepted pair in increasing pair
+order.  The decisions and the arithmetic are those of one wave per cell, so:
 
 * fused steps (and the collide-only step that ends a run) match one oracle
-  step from the GPU's previous state, on a dense tube, on ragged cells (the
-  counting rank below 64 particles, fewer pairs than one 128-pair block),
-  and on a cell at the 1024 cap with 2K = 1, where every pair passes the
-  Philox filter and the second wave's buffer fills, so that the first wave
-  resumes the tests where it stopped;
+  step from the GPU's previous state, on a dense tube, on ragged cells, and on
+  a cell at the 1024 cap with 2K = 1, where every pair passes the Philox filter
+  and the pairs take many rounds;
 * 30 steps give states and work counters identical to one wave per cell.
 """
 import numpy as np
