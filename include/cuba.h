@@ -196,7 +196,10 @@ int cuba_observe_moments(cuba_ctx *ctx, double *out);
 
 /* Copies the current state into device arrays of n doubles in id order.
  * Writes to no particle of the workspace (from 2^17 particles an index of
- * their slots goes to its scratch for overflowing cells). */
+ * their slots goes to its scratch for overflowing cells).  Captured in a
+ * graph, it reads the buffer that holds the state then: its outputs are
+ * unspecified when a replay finds the state in the other one (an odd number
+ * of steps later). */
 int cuba_get_state(cuba_ctx *ctx, double *x, double *y, double *z,
                    double *px, double *py, double *pz);
 

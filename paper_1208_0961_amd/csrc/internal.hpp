@@ -272,8 +272,7 @@ void launch_batch_run(BatchEvent *ev, const BatchSpaces &spaces, uint32_t n_even
                       uint32_t persistent_waves, hipStream_t s, const SideStream *side,
                       void (*between)(void *, int), void *ctx,
                       const uint8_t *obs_at = nullptr);
-// The state in id order; slot_of: scratch of n words.  An output whose
-// particle no cell of cur holds is not written.
+// The state in id order; slot_of: scratch of n words.
 void launch_export(const Cells &cur, int64_t n_cells, int64_t n, uint32_t *slot_of, double *x,
                    double *y, double *z, double *px, double *py, double *pz,
                    uint32_t binning_step, hipStream_t s);

@@ -3128,10 +3128,11 @@ __global__ __launch_bounds__(kBlock) void k_gather_by_id(Cells cur_arg, uint32_t
 // particle, not six 8-byte writes (each a partial line): 16.3 M particles
 // 3.42 -> 0.96 ms, 24.9 M in 2.1 M cells 5.99 -> 1.46 ms, 0.33 M 46 -> 20
 // us; below some 10^5 particles the second launch costs more than it saves
-// (10 000: 6 us in one launch, 8 in two).  slot_of starts at kNoSlot and the
-// outputs of a particle that no cell holds stay as they were (a replayed
-// capture of an export may read the buffer that holds no state by then).
-constexpr uint32_t kNoSlot = 0xFFFFFFFFu;  // slots stay below 2^32 - 1
+// (10 000: 6 us in one launch, 8 in two).  The second takes only slots of the
+// buffer: a particle that no cell holds was not listed, as when a captured
+// export is replayed while the other buffer holds the state.  (Filling slot_of
+// first, to tell those apart, took 3 us of 0.33 M particles' 36, 30 of 9.6 M's
+// 535.)
 constexpr int64_t kIndexedExportMin = 1 << 17;
 template <uint32_t G>
 __global__ __launch_bounds__(kBlock) void k_index_by_id(Cells cur_arg, uint32_t n_cells,
@@ -3161,6 +3162,7 @@ __global__ __launch_bounds__(kBlock) void k_index_by_id(Cells cur_arg, uint32_t 
 
 // Second launch: the records in id order.
 __global__ __launch_bounds__(kBlock) void k_export_by_id(Cells cur_arg, int64_t n,
+                                                         uint32_t n_slots,
                                                          const uint32_t *slot_of, double *x,
                                                          double *y, double *z, double *px,
                                                          double *py, double *pz) {
@@ -3168,7 +3170,7 @@ __global__ __launch_bounds__(kBlock) void k_export_by_id(Cells cur_arg, int64_t 
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
   const uint32_t o = slot_of[i];
-  if (o == kNoSlot) return;
+  if (o >= n_slots) return;
   const gptr<Double2> r = record(cur.st, o);
   const Double2 a = r[0], b = r[1], c = r[2];
   px[i] = a.x;
@@ -3566,13 +3568,13 @@ void launch_export(const Cells &cur, int64_t n_cells, int64_t n, uint32_t *slot_
                        (uint32_t)n_cells, x, y, z, px, py, pz, binning_step);
     return;
   }
-  launch_fill_u32(slot_of, kNoSlot, n, s);
   const uint32_t G = walk_lanes(n, n_cells);
   with_walk_lanes(G, [&](auto lanes) {
     hipLaunchKernelGGL((k_index_by_id<lanes.value>), dim3(grid_for(n_cells * G)), dim3(kBlock),
                        0, s, cur, (uint32_t)n_cells, slot_of, binning_step);
   });
-  hipLaunchKernelGGL(k_export_by_id, dim3(grid_for(n)), dim3(kBlock), 0, s, cur, n,
+  const uint32_t n_slots = (uint32_t)(n_cells * (int64_t)cur.cap + n);  // blocks, spill slots
+  hipLaunchKernelGGL(k_export_by_id, dim3(grid_for(n)), dim3(kBlock), 0, s, cur, n, n_slots,
                      (const uint32_t *)slot_of, x, y, z, px, py, pz);
 }
 
