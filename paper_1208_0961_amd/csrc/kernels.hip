@@ -1606,9 +1606,9 @@ __device__ __forceinline__ void cell_step(const GCells &src, const GCells &dst, 
 //               its lanes.  Longer lists go to their cell's own wave, sorted.
 // A cell whose list would exceed kListAll (or that overflows its block, or
 // that holds no pair) is left out and taken by its own wave alone.
-// Bound by VALU issue on the full tube (a wave per cell: 98 % busy).  Against
-// one wave per cell: 684 -> 577 M VALU instructions a launch there, 1.23 ->
-// 1.12 ms; 3-D tube's 50 steps 4.82 -> 4.33 ms (96 -> 87 us a step).  Two
+// Bound by VALU issue on the full tube (93 % busy; a wave per cell: all the
+// time).  Against one wave per cell: 727 -> 578 M VALU instructions a launch
+// there, 1.23 -> 1.11 ms; 3-D tube's 50 steps 4.82 -> 4.33 ms (96 -> 87 us a step).  Two
 // cells to a workgroup gained half of that, and one LDS atomic a row for all
 // four lists, instead of one a list, less than four.
 // ---------------------------------------------------------------------------
